@@ -368,17 +368,17 @@ __global__ __launch_bounds__(kFillThreads) void k_front(
   if (threadIdx.x == 0 && s_last >= 0) atomicMax(&we[j], s_last + 1);
 }
 
-// optarg of every cell of targets [lb, lb + gridDim.y) from the final
-// table: the smallest predecessor index whose cell passes the budget test
-// and reproduces the target value (Algorithm 1's first writer).
+// optarg of every cell from the final table: the smallest predecessor index
+// whose cell passes the budget test and reproduces the target value
+// (Algorithm 1's first writer).
 template <class T>
 __global__ __launch_bounds__(kFillThreads) void k_arg_all(
-    int64_t lb, const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
+    const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
     const int64_t* __restrict__ pred_ptr, const int32_t* __restrict__ pidx,
     const int32_t* __restrict__ pdt, const int32_t* __restrict__ pdm,
     const int32_t* __restrict__ pc, int32_t Beff, const T* __restrict__ m,
     uint16_t* __restrict__ arg) {
-  const int64_t j = lb + blockIdx.y;
+  const int64_t j = blockIdx.y;
   const int32_t wj = w[j];
   const int32_t tp = blockIdx.x * kFillThreads + threadIdx.x;
   if (tp >= wj) return;
@@ -578,6 +578,60 @@ __global__ __launch_bounds__(kTraceThreads) void k_trace(
 constexpr int kArgWaves = 4;
 constexpr uint32_t kNoNext = 0xFFFFFFFFu;
 
+// The first hit of one wave's share of target j's predecessor list for the
+// target cell (j, t) of each lane with value mj (need: the lane has one):
+// groups of 64 pairs, every kArgWaves-th from `wave` on.  Returns the index
+// in the list, INT32_MAX without a hit.  Every lane of the wave calls it.
+template <class Cell>
+__device__ __forceinline__ int32_t wave_first_hit(
+    int32_t t, uint32_t mj, bool need, int wave, int64_t p0, int64_t p1,
+    const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
+    const int32_t* __restrict__ pidx, const int32_t* __restrict__ pdt,
+    const int32_t* __restrict__ pdm, const int32_t* __restrict__ pc, int32_t Beff,
+    const Cell* __restrict__ m) {
+  const int lane = threadIdx.x & (kWave - 1);
+  int32_t hit = INT32_MAX;
+  if (!__any(need)) return hit;
+  for (int64_t g = p0 + (int64_t)wave * kWave; g < p1; g += kArgWaves * kWave) {
+    // lane l holds pair g + l: the source row's cell of target t at
+    // base + t, in the row when t - dt lies in [0, w_L); past the list w = 0
+    const int64_t p = g + lane;
+    const int64_t pq = p < p1 ? p : p0;
+    const int32_t i = pidx[pq], dt = pdt[pq], c = pc[pq], dm = pdm[pq];
+    const int64_t base = row_off[i] - dt;
+    const int32_t wi = p < p1 ? w[i] : 0;
+    const uint32_t blo = (uint32_t)base, bhi = (uint32_t)((uint64_t)base >> 32);
+    const int32_t cnt = (int32_t)std::min<int64_t>(kWave, p1 - g);
+    for (int32_t k0 = 0; k0 < cnt; k0 += 8) {
+      // eight source cells loaded before any test (a cell outside its row
+      // is read at the row's first cell and not used)
+      uint32_t x[8];
+      bool in[8];
+#pragma unroll
+      for (int u = 0; u < 8; u++) {
+        const int k = k0 + u;
+        const int32_t dtk = __builtin_amdgcn_readlane(dt, k);
+        const int32_t wk = __builtin_amdgcn_readlane(wi, k);
+        const int64_t bk = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(bhi, k) << 32) |
+                                     (uint32_t)__builtin_amdgcn_readlane(blo, k));
+        in[u] = (uint32_t)(t - dtk) < (uint32_t)wk;
+        x[u] = m[bk + (in[u] ? t : dtk)];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; u++) {
+        const int k = k0 + u;
+        const int32_t ck = __builtin_amdgcn_readlane(c, k);
+        const int32_t dmk = __builtin_amdgcn_readlane(dm, k);
+        if (hit == INT32_MAX && in[u] && x[u] != cell_inf<Cell>() &&
+            (int64_t)x[u] <= (int64_t)Beff - ck && (uint32_t)(x[u] + dmk) == mj)
+          hit = (int32_t)(g - p0) + k;
+      }
+    }
+    if (!__any(need && hit == INT32_MAX)) break;
+  }
+  return hit;
+}
+
 template <class Cell>
 __global__ __launch_bounds__(kArgWaves* kWave) void k_trace_args(
     int32_t S, const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
@@ -593,46 +647,8 @@ __global__ __launch_bounds__(kArgWaves* kWave) void k_trace_args(
   const uint32_t mj = m[row_off[j] + (t < wj ? t : 0)];
   const bool need = j > 0 && t < S && t < wj && mj != cell_inf<Cell>();
   const int64_t p0 = pred_ptr[j], p1 = pred_ptr[j + 1];
-  int32_t hit = INT32_MAX;
-  if (__any(need)) {
-    for (int64_t g = p0 + (int64_t)wave * kWave; g < p1; g += kArgWaves * kWave) {
-      // lane l holds pair g + l: the source row's cell of target t at
-      // base + t, in the row when t - dt lies in [0, w_L); past the list w = 0
-      const int64_t p = g + lane;
-      const int64_t pq = p < p1 ? p : p0;
-      const int32_t i = pidx[pq], dt = pdt[pq], c = pc[pq], dm = pdm[pq];
-      const int64_t base = row_off[i] - dt;
-      const int32_t wi = p < p1 ? w[i] : 0;
-      const uint32_t blo = (uint32_t)base, bhi = (uint32_t)((uint64_t)base >> 32);
-      const int32_t cnt = (int32_t)std::min<int64_t>(kWave, p1 - g);
-      for (int32_t k0 = 0; k0 < cnt; k0 += 8) {
-        // eight source cells loaded before any test (a cell outside its row
-        // is read at the row's first cell and not used)
-        uint32_t x[8];
-        bool in[8];
-#pragma unroll
-        for (int u = 0; u < 8; u++) {
-          const int k = k0 + u;
-          const int32_t dtk = __builtin_amdgcn_readlane(dt, k);
-          const int32_t wk = __builtin_amdgcn_readlane(wi, k);
-          const int64_t bk = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(bhi, k) << 32) |
-                                       (uint32_t)__builtin_amdgcn_readlane(blo, k));
-          in[u] = (uint32_t)(t - dtk) < (uint32_t)wk;
-          x[u] = m[bk + (in[u] ? t : dtk)];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; u++) {
-          const int k = k0 + u;
-          const int32_t ck = __builtin_amdgcn_readlane(c, k);
-          const int32_t dmk = __builtin_amdgcn_readlane(dm, k);
-          if (hit == INT32_MAX && in[u] && x[u] != cell_inf<Cell>() &&
-              (int64_t)x[u] <= (int64_t)Beff - ck && (uint32_t)(x[u] + dmk) == mj)
-            hit = (int32_t)(g - p0) + k;
-        }
-      }
-      if (!__any(need && hit == INT32_MAX)) break;
-    }
-  }
+  const int32_t hit = wave_first_hit(t, mj, need, wave, p0, p1, w, row_off, pidx, pdt, pdm, pc,
+                                     Beff, m);
   s_hit[wave][lane] = need ? hit : INT32_MAX;
   __syncthreads();
   if (wave != 0 || t >= S) return;
@@ -645,6 +661,35 @@ __global__ __launch_bounds__(kArgWaves* kWave) void k_trace_args(
     e = (uint32_t)pidx[p] | ((uint32_t)(t - pdt[p]) << 16);
   }
   nxt[j * S + t] = e;
+}
+
+// optarg of the whole table when it is small: 64 cells of target blockIdx.y
+// per workgroup, its predecessor list over the workgroup's waves as in
+// k_trace_args.
+template <class Cell>
+__global__ __launch_bounds__(kArgWaves* kWave) void k_arg_split(
+    const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
+    const int64_t* __restrict__ pred_ptr, const int32_t* __restrict__ pidx,
+    const int32_t* __restrict__ pdt, const int32_t* __restrict__ pdm,
+    const int32_t* __restrict__ pc, int32_t Beff, const Cell* __restrict__ m,
+    uint16_t* __restrict__ arg) {
+  __shared__ int32_t s_hit[kArgWaves][kWave];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int64_t j = blockIdx.y;
+  const int32_t wj = w[j];
+  const int32_t t = blockIdx.x * kWave + lane;
+  if ((int32_t)(blockIdx.x * kWave) >= wj) return;      // the whole workgroup leaves
+  const uint32_t mj = m[row_off[j] + (t < wj ? t : 0)];
+  const bool need = j > 0 && t < wj && mj != cell_inf<Cell>();
+  const int64_t p0 = pred_ptr[j], p1 = pred_ptr[j + 1];
+  s_hit[wave][lane] = wave_first_hit(t, mj, need, wave, p0, p1, w, row_off, pidx, pdt, pdm, pc,
+                                     Beff, m);
+  __syncthreads();
+  if (wave != 0 || t >= wj) return;
+  int32_t h = INT32_MAX;
+#pragma unroll
+  for (int q = 0; q < kArgWaves; q++) h = min(h, s_hit[q][lane]);
+  arg[row_off[j] + t] = (uint16_t)(need && h != INT32_MAX ? (uint32_t)pidx[p0 + h] : kNoArg);
 }
 
 // The walk over the slice of k_trace_args from (V, t*), then Eq. 1 and
@@ -908,18 +953,33 @@ hipError_t launch_trace(rc_solution sol, hipStream_t s) {
   return sol->cell32 ? trace_t<uint32_t>(sol, sol->m32, s) : trace_t<uint16_t>(sol, sol->m, s);
 }
 
+// optarg of the whole table in one launch: no cell's optarg depends on
+// another's, so the rows need no order (one launch per size level, each
+// waiting for its longest predecessor list, took 5.4 ms on resnet50_t10's
+// 167 levels).  A list of at least 64 pairs on average is split over the
+// waves of a workgroup, and so are the lists of a table too small to fill
+// the chip: there the longest list decides the time.  On long rows with
+// short lists (U-Net: 25 pairs, 61 M cells) the extra waves only repeat the
+// cells' loads, and one thread per cell is better.  rc_export_table of one
+// row, split against one thread per cell: resnet50_t10 57 us against 110,
+// densenet121_t10 134 against 265, DenseNet-121 9.7 ms against 16.7,
+// ResNet-50 2.2 against 2.9, U-Net 4.8 against 3.2.
+constexpr int64_t kSplitCells = (int64_t)1 << 20;
+
 template <class T>
 static void arg_all_t(rc_solution sol, const T* m, hipStream_t s) {
   rc_family f = sol->f;
-  const int64_t L = (int64_t)f->level_ptr.size() - 1;
-  for (int64_t l = 0; l < L; l++) {
-    const int64_t lb = f->level_ptr[l], le = f->level_ptr[l + 1];
-    const int64_t tiles = (f->level_maxw[l] + kFillThreads - 1) / kFillThreads;
-    if (tiles <= 0 || le <= lb) continue;
-    hipLaunchKernelGGL(k_arg_all<T>, dim3((unsigned)tiles, (unsigned)(le - lb)),
-                       dim3(kFillThreads), 0, s, lb, f->w, f->row_off, f->pred_ptr, f->pidx,
+  const unsigned rows = (unsigned)f->F;
+  if (f->P >= kWave * f->F || f->cells <= kSplitCells) {
+    hipLaunchKernelGGL(k_arg_split<T>, dim3((unsigned)((f->max_row + kWave - 1) / kWave), rows),
+                       dim3(kArgWaves * kWave), 0, s, f->w, f->row_off, f->pred_ptr, f->pidx,
                        f->pdt, f->pdm, f->pc, (int32_t)sol->Beff, m, sol->arg);
+    return;
   }
+  hipLaunchKernelGGL(k_arg_all<T>, dim3((unsigned)((f->max_row + kFillThreads - 1) / kFillThreads),
+                                        rows),
+                     dim3(kFillThreads), 0, s, f->w, f->row_off, f->pred_ptr, f->pidx, f->pdt,
+                     f->pdm, f->pc, (int32_t)sol->Beff, m, sol->arg);
 }
 
 hipError_t launch_arg_all(rc_solution sol, hipStream_t s) {
