@@ -258,11 +258,12 @@ int rc_solve(rc_family f, int64_t B, int32_t objective, void* stream, rc_solutio
 /*
  * rc_solve_dominance -- rc_solve (time-centric) with the skip of Section
  * 4.2's last paragraph: a cell opt[L, t'] is not propagated when some t < t'
- * of the same row has opt[L, t] < opt[L, t'].  The table is filled one size
- * level at a time; once a level is done, each of its rows keeps only its
- * weak front (the cells whose m is no larger than every earlier cell of the
- * row) and stores every other cell as infinity, and later levels read no
- * source cell past the end of that front.
+ * of the same row has opt[L, t] < opt[L, t'].  The table keeps of each row
+ * its weak front (the cells whose m is no larger than every earlier cell of
+ * the row) and stores every other cell as infinity.  A front cell's value
+ * comes from a front cell, so the fronts are those of rc_solve's table: it
+ * is filled by rc_solve's choice of fill and its rows reduced afterwards
+ * (rc_solution_fill_ms covers both).
  *  t* and opt[V, t*] equal rc_solve's.  The exported table holds, at every
  *  front cell, the value of Algorithm 1 run with the skip (it is the same
  *  front as rc_solve's table), infinity elsewhere; the optarg of a front

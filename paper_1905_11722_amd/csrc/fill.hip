@@ -27,7 +27,6 @@
 #include <cstring>
 
 #include "rc_internal.h"
-#include "dominance.h"
 #include "schedule.h"
 #include "wavefront.h"
 
@@ -69,6 +68,7 @@ __global__ void k_solve_init(T* m, const int64_t* row_off, int objective, DevSta
     st->t_sel = objective == RC_TIME_CENTRIC ? INT32_MAX : -1;
     st->m_sel = -1;
     st->k = 0;
+    st->done = 0;
   }
 }
 
@@ -76,15 +76,12 @@ __global__ void k_solve_init(T* m, const int64_t* row_off, int objective, DevSta
 // other).  Block (x, y): cells [x * kTile, (x + 1) * kTile) of target
 // lb + y; each thread owns kCellsPerThread cells strided by the block size
 // so that every source read and every store of a wave is contiguous.
-// ws[i]: the source row's cells that may be read, t < ws[i] (its width w[i],
-// or the end of its weak front under the dominance skip).
 template <class T>
 __global__ __launch_bounds__(kFillThreads) void k_fill_level(
     int64_t lb, const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
     const int64_t* __restrict__ pred_ptr, const int32_t* __restrict__ pidx,
     const int32_t* __restrict__ pdt, const int32_t* __restrict__ pdm,
-    const int32_t* __restrict__ pc, int32_t Beff, const int32_t* __restrict__ ws,
-    T* __restrict__ m) {
+    const int32_t* __restrict__ pc, int32_t Beff, T* __restrict__ m) {
   const int64_t j = lb + blockIdx.y;
   const int32_t wj = w[j];
   const int32_t tile0 = blockIdx.x * kTile;
@@ -99,7 +96,7 @@ __global__ __launch_bounds__(kFillThreads) void k_fill_level(
     if (tau < 0) continue;                    // no source cell can pass
     const int32_t dt = pdt[p];
     const int32_t i = pidx[p];
-    const int32_t wi = ws[i];                 // cells of the source row that can be read
+    const int32_t wi = w[i];                  // cells of the source row
     if (dt >= tile0 + kTile || dt + wi <= tile0) continue;  // window misses the tile
     const T* src = m + row_off[i];
     const uint32_t dm = (uint32_t)pdm[p];
@@ -128,7 +125,7 @@ __global__ __launch_bounds__(kFillThreads) void k_fill_level(
 // D = row_off[i] - row_off[j] - dt, the same for every cell of the pair.
 // So a pair's eight source cells start D mod 8 cells past an aligned
 // 16-byte word: two aligned loads and a shift by that uniform amount.
-// Source cells outside [0, ws[i]) and target cells before the row's first
+// Source cells outside [0, w[i]) and target cells before the row's first
 // cell read as infinity.
 //
 // The NW waves of a workgroup own the same 512 cells and take every NW-th
@@ -137,8 +134,7 @@ __global__ __launch_bounds__(kFillThreads) void k_fill_level(
 // scalar registers, then every source load of the group goes out before the
 // first is used (a pair a lane skips loads the lane's own cells instead),
 // so that a lane waits for memory twice per group, and the chain of groups
-// a wave walks is 1/NW of the target's pairs.  With kFront the
-// readable part of a source row is ws[i] (the dominance skip's front).
+// a wave walks is 1/NW of the target's pairs.
 constexpr int kVecCells = 8;
 constexpr int kVecTile = kWave * kVecCells;          // cells per workgroup
 constexpr int kLevelGroup = 4;
@@ -157,11 +153,11 @@ __device__ __forceinline__ void take8(const uint32_t (&w)[8], uint32_t (&out)[4]
   }
 }
 
-template <bool kFront, int NW>
+template <int NW>
 __global__ __launch_bounds__(NW * kWave) void k_fill_level_vec(
     int64_t lb, const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
     const int64_t* __restrict__ pred_ptr, const LevelPair* __restrict__ lp, int32_t Beff,
-    const int32_t* __restrict__ ws, uint16_t* __restrict__ m) {
+    uint16_t* __restrict__ m) {
   using wf::u16x2;
   constexpr int kLevelWaves = NW;
   __shared__ uint4 s_acc[kLevelWaves > 1 ? kLevelWaves - 1 : 1][kWave];
@@ -196,7 +192,6 @@ __global__ __launch_bounds__(NW * kWave) void k_fill_level_vec(
       r[q].c = rd(4);
       r[q].dm = rd(5);
       r[q].w = rd(6);
-      r[q].src = rd(7);
     }
     int64_t src[kLevelGroup], hi[kLevelGroup];
     bool use[kLevelGroup];
@@ -205,7 +200,7 @@ __global__ __launch_bounds__(NW * kWave) void k_fill_level_vec(
     for (int q = 0; q < kLevelGroup; q++) {
       // source cell of the group's first cell; readable cells [lo, hi)
       src[q] = dst - rj + r[q].base;
-      hi[q] = r[q].lo + (kFront ? ws[r[q].src] : r[q].w);
+      hi[q] = r[q].lo + r[q].w;
       use[q] = pg + q < p1 && Beff - r[q].c >= 0 && src[q] + kVecCells > r[q].lo && src[q] < hi[q];
       const uint4* v = reinterpret_cast<const uint4*>(
           m + (use[q] ? src[q] - (src[q] & (kVecCells - 1)) : dst));
@@ -281,91 +276,129 @@ __global__ void k_level_pairs(int64_t P, const int32_t* __restrict__ pidx,
   r.c = pc[p];
   r.dm = pdm[p];
   r.w = w[i];
-  r.src = i;
+  r.pad = 0;
   lp[p] = r;
 }
 
-// The dominance skip of Section 4.2 (last paragraph) on finished rows
-// lb + blockIdx.y: a cell t of row L is never propagated when an earlier
-// cell of the same row holds strictly less memory.  Such a cell is stored as
-// infinity, which leaves each row as its weak front (the cells with m no
-// larger than every earlier m), the only cells that a later level, the
-// selection of t* or the traceback reads.  we[L] = 1 + the last finite
-// cell kept (0 when none): the level fill reads no source cell beyond it.
-// Two passes over segments of kSeg cells, every (segment, row) a block:
-// k_front_min stores each segment's least m, then k_front takes the least m
-// of the segments before its own as the carry and scans its segment in
-// chunks of kFillThreads cells, each cell read and rewritten by one thread.
-constexpr int kSeg = 2048;
+// The dominance skip of Section 4.2 (last paragraph): a cell t of row L is
+// never propagated when an earlier cell of the same row holds strictly less
+// memory.  Such a cell is stored as infinity, which leaves each row as its
+// weak front (the cells with m no larger than every earlier m), the only
+// cells that the selection of t* or the traceback reads.
+//
+// The fronts are taken from the whole finished table, not level by level: a
+// front cell's value comes from a front cell (a dominated source cell has an
+// earlier cell with strictly less memory, which passes the same budget test
+// and lands earlier on the target with strictly less), so a row's front is
+// the same whether the rows before it were reduced or not, and the table is
+// filled by the fastest path with no order between a row's front and the
+// rows after it.
+//
+// Two passes over segments of kSeg cells, a workgroup each (rows lb + y):
+// k_front_min stores each segment's least m; k_front takes the least m of
+// the row's segments before its own as the carry and scans its own.  A
+// thread owns 8 consecutive cells, one 16-byte load and at most one such
+// store.  Bound by the table's bytes, read twice: U-Net's 61 M cells 28 and
+// 49 us (4.4 TB/s of reads in the first); two launches after every size
+// level, with the carry read by every thread, took 225 us and 1.72 ms.
+// Segment x of row j, counted from the row's first cell
+// rounded down to 8 cells, has the slot (row_off[j] >> kSegShift) + j + x.
+constexpr int kSegShift = 11;
+constexpr int kSeg = 1 << kSegShift;
+static_assert(kSeg == 8 * kFillThreads, "eight cells per thread");
+
+// The cells of segment blockIdx.x of row j that a thread owns, outside the
+// row infinite; t = the first one's t.
+__device__ __forceinline__ uint16_t* front_cells(int64_t off, int32_t wj, uint16_t* m, int32_t& t,
+                                                 uint16_t (&c)[8]) {
+  const int32_t a = (int32_t)(off & 7);
+  t = (int32_t)blockIdx.x * kSeg + 8 * (int32_t)threadIdx.x - a;
+  uint16_t* p = m + off + t;
+  union {
+    uint4 q;
+    uint16_t v[8];
+  } x;
+  x.q = make_uint4(~0u, ~0u, ~0u, ~0u);
+  if (t < wj) x.q = *reinterpret_cast<const uint4*>(p);
+#pragma unroll
+  for (int k = 0; k < 8; k++) c[k] = t + k >= 0 && t + k < wj ? x.v[k] : (uint16_t)kInfM;
+  return p;
+}
 
 __global__ __launch_bounds__(kFillThreads) void k_front_min(
     int64_t lb, const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
-    const uint16_t* __restrict__ m, int32_t nseg, uint32_t* __restrict__ segmin,
-    int32_t* __restrict__ we) {
+    uint16_t* __restrict__ m, uint16_t* __restrict__ segmin) {
   __shared__ uint32_t s_wave[kFillThreads / kWave];
   const int64_t j = lb + blockIdx.y;
   const int32_t wj = w[j];
-  const int32_t t0 = blockIdx.x * kSeg;
-  const uint16_t* row = m + row_off[j];
+  const int64_t off = row_off[j];
+  if ((int64_t)blockIdx.x * kSeg >= wj + (off & 7)) return;   // the whole block leaves together
+  int32_t t;
+  uint16_t c[8];
+  front_cells(off, wj, m, t, c);
   uint32_t x = kInfM;
-  for (int32_t t = t0 + (int32_t)threadIdx.x; t < min(wj, t0 + kSeg); t += kFillThreads)
-    x = min(x, (uint32_t)row[t]);
-  for (int off = kWave / 2; off > 0; off >>= 1) x = min(x, (uint32_t)__shfl_xor(x, off, kWave));
+#pragma unroll
+  for (int k = 0; k < 8; k++) x = min(x, (uint32_t)c[k]);
+  for (int o = kWave / 2; o > 0; o >>= 1) x = min(x, (uint32_t)__shfl_xor(x, o, kWave));
   if (threadIdx.x % kWave == 0) s_wave[threadIdx.x / kWave] = x;
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int q = 1; q < kFillThreads / kWave; q++) x = min(x, s_wave[q]);
-    segmin[blockIdx.y * (int64_t)nseg + blockIdx.x] = x;
-    if (blockIdx.x == 0) we[j] = 0;
+    segmin[(off >> kSegShift) + j + blockIdx.x] = (uint16_t)x;
   }
 }
 
 __global__ __launch_bounds__(kFillThreads) void k_front(
     int64_t lb, const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
-    uint16_t* __restrict__ m, int32_t nseg, const uint32_t* __restrict__ segmin,
-    int32_t* __restrict__ we) {
-  __shared__ uint32_t s_wave[kFillThreads / kWave];
-  __shared__ int32_t s_last;
+    uint16_t* __restrict__ m, const uint16_t* __restrict__ segmin) {
+  __shared__ uint32_t s_carry[kFillThreads / kWave], s_wave[kFillThreads / kWave];
   const int64_t j = lb + blockIdx.y;
   const int32_t wj = w[j];
-  const int32_t s0 = blockIdx.x * kSeg;
-  if (s0 >= wj) return;                     // the whole block leaves together
-  const int32_t s1 = min(wj, s0 + kSeg);
-  uint16_t* row = m + row_off[j];
+  const int64_t off = row_off[j];
+  if ((int64_t)blockIdx.x * kSeg >= wj + (off & 7)) return;   // the whole block leaves together
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  if (threadIdx.x == 0) s_last = -1;
-  uint32_t carry = kInfM;                   // least m of the earlier segments, then chunks
-  for (int32_t q = 0; q < (int32_t)blockIdx.x; q++)
-    carry = min(carry, segmin[blockIdx.y * (int64_t)nseg + q]);
-  int32_t last = -1;
-  for (int32_t c0 = s0; c0 < s1; c0 += kFillThreads) {
-    const int32_t t = c0 + (int32_t)threadIdx.x;
-    const uint32_t x = t < s1 ? row[t] : kInfM;
-    uint32_t inc = x;                       // inclusive minimum along the wave
-    for (int off = 1; off < kWave; off <<= 1) {
-      const uint32_t y = __shfl_up(inc, off, kWave);
-      if (lane >= off) inc = min(inc, y);
-    }
-    uint32_t exc = __shfl_up(inc, 1, kWave);
-    if (lane == 0) exc = kInfM;
-    if (lane == kWave - 1) s_wave[wave] = inc;
-    __syncthreads();
-    uint32_t before = carry;                // earlier chunks and earlier waves
-    for (int q = 0; q < wave; q++) before = min(before, s_wave[q]);
-    uint32_t chunk = carry;
-    for (int q = 0; q < kFillThreads / kWave; q++) chunk = min(chunk, s_wave[q]);
-    __syncthreads();                        // s_wave is rewritten by the next chunk
-    const uint32_t least = min(before, exc);
-    if (t < s1) {
-      const bool keep = x != kInfM && x <= least;
-      if (!keep && x != kInfM) row[t] = (uint16_t)kInfM;
-      if (keep) last = t;
-    }
-    carry = chunk;
+  int32_t t;
+  uint16_t c[8];
+  uint16_t* p = front_cells(off, wj, m, t, c);
+  // least m of the segments before, over the workgroup
+  uint32_t before = kInfM;
+  const uint16_t* sm = segmin + (off >> kSegShift) + j;
+  for (uint32_t q = threadIdx.x; q < blockIdx.x; q += kFillThreads)
+    before = min(before, (uint32_t)sm[q]);
+  for (int o = kWave / 2; o > 0; o >>= 1)
+    before = min(before, (uint32_t)__shfl_xor(before, o, kWave));
+  uint32_t own = kInfM;                     // least of the thread's cells, then of the lanes before
+#pragma unroll
+  for (int k = 0; k < 8; k++) own = min(own, (uint32_t)c[k]);
+  for (int o = 1; o < kWave; o <<= 1) {
+    const uint32_t y = __shfl_up(own, o, kWave);
+    if (lane >= o) own = min(own, y);
   }
-  if (last >= 0) atomicMax(&s_last, last);
+  if (lane == kWave - 1) {
+    s_carry[wave] = before;
+    s_wave[wave] = own;
+  }
+  uint32_t least = __shfl_up(own, 1, kWave);
+  if (lane == 0) least = kInfM;
   __syncthreads();
-  if (threadIdx.x == 0 && s_last >= 0) atomicMax(&we[j], s_last + 1);
+  for (int q = 0; q < kFillThreads / kWave; q++) {
+    least = min(least, s_carry[q]);
+    if (q < wave) least = min(least, s_wave[q]);
+  }
+  // one 16-byte store; the cells before the row's first one are padding
+  union {
+    uint4 q;
+    uint16_t v[8];
+  } x;
+  bool changed = false;
+#pragma unroll
+  for (int k = 0; k < 8; k++) {
+    const bool dominated = c[k] > least;
+    x.v[k] = dominated ? (uint16_t)kInfM : c[k];
+    changed |= dominated && c[k] != kInfM;
+    least = min(least, (uint32_t)c[k]);
+  }
+  if (changed) *reinterpret_cast<uint4*>(p) = x.q;
 }
 
 // optarg of every cell from the final table: the smallest predecessor index
@@ -373,12 +406,12 @@ __global__ __launch_bounds__(kFillThreads) void k_front(
 // (Algorithm 1's first writer).
 template <class T>
 __global__ __launch_bounds__(kFillThreads) void k_arg_all(
-    const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
+    int64_t lb, const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
     const int64_t* __restrict__ pred_ptr, const int32_t* __restrict__ pidx,
     const int32_t* __restrict__ pdt, const int32_t* __restrict__ pdm,
     const int32_t* __restrict__ pc, int32_t Beff, const T* __restrict__ m,
     uint16_t* __restrict__ arg) {
-  const int64_t j = blockIdx.y;
+  const int64_t j = lb + blockIdx.y;
   const int32_t wj = w[j];
   const int32_t tp = blockIdx.x * kFillThreads + threadIdx.x;
   if (tp >= wj) return;
@@ -400,47 +433,62 @@ __global__ __launch_bounds__(kFillThreads) void k_arg_all(
   arg[row_off[j] + tp] = (uint16_t)a;
 }
 
-// t* = min (time-centric) or max (memory-centric) finite t of row V.
-// A few workgroups stride over the row, reduce within the wave and then the
-// workgroup, and issue one atomic each (one atomic per wave serialised on
-// the one address).
+// t* = min (time-centric) or max (memory-centric) finite t of row V, and
+// opt[V, t*].  A lane reads 16 bytes of the row at a time, counted from the
+// row's end (aligned to kRowAlign cells); a workgroup reduces to one atomic,
+// and the last workgroup to finish (st->done) reads the result back.  Bound
+// by its loads in flight: U-Net's 2.4 M cells take 10 us (13 with 512
+// workgroups, whose atomics meet on one address), against 48 us with one
+// cell per load and 64 workgroups and 5 more in a second launch.
 constexpr int kSelectThreads = 256;
-constexpr int kSelectBlocks = 64;
+constexpr int kSelectBlocks = 128;
 
 template <class T>
 __global__ __launch_bounds__(kSelectThreads) void k_select(const T* m, const int64_t* row_off,
                                                           int64_t v, const int32_t* w,
                                                           int objective, DevStatus* st) {
+  constexpr int kVec = 16 / (int)sizeof(T);
   __shared__ int32_t s_best[kSelectThreads / kWave];
   const int64_t off = row_off[v];
   const int32_t wv = w[v];
   const bool tc = objective == RC_TIME_CENTRIC;
   int32_t best = tc ? INT32_MAX : -1;
-  for (int32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < wv; t += gridDim.x * blockDim.x)
-    if (m[off + t] != cell_inf<T>()) best = tc ? min(best, t) : max(best, t);
+  const int32_t groups = (wv + kVec - 1) / kVec;
+  for (int32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < groups;
+       g += gridDim.x * blockDim.x) {
+    const int32_t t0 = wv - kVec * (g + 1);           // may start before the row's first cell
+    union {
+      uint4 q;
+      T c[kVec];
+    } x;
+    x.q = *reinterpret_cast<const uint4*>(m + off + t0);
+#pragma unroll
+    for (int k = 0; k < kVec; k++)
+      if (t0 + k >= 0 && x.c[k] != (T)cell_inf<T>())
+        best = tc ? min(best, t0 + k) : max(best, t0 + k);
+  }
   for (int o = kWave / 2; o > 0; o >>= 1) {
     const int32_t y = __shfl_xor(best, o, kWave);
     best = tc ? min(best, y) : max(best, y);
   }
   if ((threadIdx.x & (kWave - 1)) == 0) s_best[threadIdx.x / kWave] = best;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int q = 1; q < kSelectThreads / kWave; q++)
-      best = tc ? min(best, s_best[q]) : max(best, s_best[q]);
-    if (tc ? best != INT32_MAX : best >= 0) {
-      if (tc)
-        atomicMin(&st->t_sel, best);
-      else
-        atomicMax(&st->t_sel, best);
-    }
-  }
-}
-
-template <class T>
-__global__ void k_select_finish(const T* m, const int64_t* row_off, int64_t v, DevStatus* st) {
   if (threadIdx.x != 0) return;
-  if (st->t_sel == INT32_MAX) st->t_sel = -1;
-  st->m_sel = st->t_sel >= 0 ? (int32_t)m[row_off[v] + st->t_sel] : -1;
+  for (int q = 1; q < kSelectThreads / kWave; q++)
+    best = tc ? min(best, s_best[q]) : max(best, s_best[q]);
+  if (tc ? best != INT32_MAX : best >= 0) {
+    if (tc)
+      atomicMin(&st->t_sel, best);
+    else
+      atomicMax(&st->t_sel, best);
+  }
+  __threadfence();
+  if (atomicAdd(&st->done, 1) != (int32_t)gridDim.x - 1) return;
+  __threadfence();
+  int32_t t = __hip_atomic_load(&st->t_sel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (t == INT32_MAX) t = -1;
+  st->t_sel = t;
+  st->m_sel = t >= 0 ? (int32_t)m[off + t] : -1;
 }
 
 // Traceback from (V, t*) (Section 4.2), then Eq. 1 and Eq. 2 of the chain
@@ -668,14 +716,14 @@ __global__ __launch_bounds__(kArgWaves* kWave) void k_trace_args(
 // k_trace_args.
 template <class Cell>
 __global__ __launch_bounds__(kArgWaves* kWave) void k_arg_split(
-    const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
+    int64_t lb, const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
     const int64_t* __restrict__ pred_ptr, const int32_t* __restrict__ pidx,
     const int32_t* __restrict__ pdt, const int32_t* __restrict__ pdm,
     const int32_t* __restrict__ pc, int32_t Beff, const Cell* __restrict__ m,
     uint16_t* __restrict__ arg) {
   __shared__ int32_t s_hit[kArgWaves][kWave];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int64_t j = blockIdx.y;
+  const int64_t j = lb + blockIdx.y;
   const int32_t wj = w[j];
   const int32_t t = blockIdx.x * kWave + lane;
   if ((int32_t)(blockIdx.x * kWave) >= wj) return;      // the whole workgroup leaves
@@ -775,9 +823,8 @@ hipError_t launch_solve_init(rc_solution sol, hipStream_t s) {
 // walks at most two groups of the level's longest pair list (1 to 16), but
 // no more than keep eight waves per SIMD busy: wide rows already fill the
 // chip with workgroups, and their levels are bound by the source reads.
-template <bool kFront>
 static void launch_level_vec(rc_family f, int64_t l, dim3 grid, int64_t lb, int32_t Beff,
-                             const int32_t* ws, uint16_t* m, hipStream_t s) {
+                             uint16_t* m, hipStream_t s) {
   const int64_t most = f->level_pairs[l];
   const int64_t blocks = (int64_t)grid.x * grid.y;
   const int64_t cap = 8 * 4 * (int64_t)num_cus();        // eight waves per SIMD
@@ -785,8 +832,8 @@ static void launch_level_vec(rc_family f, int64_t l, dim3 grid, int64_t lb, int3
   while (nw < 16 && (int64_t)nw * 2 * kLevelGroup < most) nw *= 2;
   while (nw > 1 && blocks * nw > cap) nw /= 2;
 #define RCDP_LEVEL_VEC(NW)                                                                  \
-  hipLaunchKernelGGL((k_fill_level_vec<kFront, NW>), grid, dim3(NW * kWave), 0, s, lb, f->w, \
-                     f->row_off, f->pred_ptr, f->lpair, Beff, ws, m)
+  hipLaunchKernelGGL((k_fill_level_vec<NW>), grid, dim3(NW * kWave), 0, s, lb, f->w, \
+                     f->row_off, f->pred_ptr, f->lpair, Beff, m)
   switch (nw) {
     case 1: RCDP_LEVEL_VEC(1); break;
     case 2: RCDP_LEVEL_VEC(2); break;
@@ -807,14 +854,14 @@ static void fill_levels(rc_solution sol, T* m, hipStream_t s) {
     if (sizeof(T) == 2) {
       const int64_t tiles = (f->level_maxw[l] + kVecTile - 1) / kVecTile;
       if (tiles <= 0) continue;
-      launch_level_vec<false>(f, l, dim3((unsigned)tiles, (unsigned)(le - lb)), lb,
-                              (int32_t)sol->Beff, f->w, reinterpret_cast<uint16_t*>(m), s);
+      launch_level_vec(f, l, dim3((unsigned)tiles, (unsigned)(le - lb)), lb, (int32_t)sol->Beff,
+                       reinterpret_cast<uint16_t*>(m), s);
     } else {
       const int64_t tiles = (f->level_maxw[l] + kTile - 1) / kTile;
       if (tiles <= 0) continue;
       hipLaunchKernelGGL(k_fill_level<T>, dim3((unsigned)tiles, (unsigned)(le - lb)),
                          dim3(kFillThreads), 0, s, lb, f->w, f->row_off, f->pred_ptr, f->pidx,
-                         f->pdt, f->pdm, f->pc, (int32_t)sol->Beff, f->w, m);
+                         f->pdt, f->pdm, f->pc, (int32_t)sol->Beff, m);
     }
   }
 }
@@ -842,34 +889,47 @@ hipError_t launch_fill(rc_solution sol, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_fill_dominance(rc_solution sol, int32_t* we, hipStream_t s) {
-  rc_family f = sol->f;
-  const hipError_t le = ensure_level_pairs(f, s);
-  if (le != hipSuccess) return le;
+// Launches over all rows, `per` cells of a row to a workgroup, as
+// launch(first row, grid): one launch for consecutive levels while their
+// longest row leaves at most half of the grid's workgroups without cells.
+template <class Launch>
+static void for_row_groups(rc_family f, int64_t per, Launch launch) {
   const int64_t L = (int64_t)f->level_ptr.size() - 1;
-  int64_t most = 1;                         // segment minima of the largest level
-  for (int64_t l = 0; l < L; l++)
-    most = std::max<int64_t>(most, (f->level_ptr[l + 1] - f->level_ptr[l]) *
-                                       ((f->level_maxw[l] + kSeg - 1) / kSeg));
-  uint32_t* segmin = sol->arena.get_n<uint32_t>(most);
-  if (!segmin) return hipErrorOutOfMemory;
-  auto front = [&](int64_t lb, int64_t rows, int32_t maxw) {
-    const int32_t nseg = std::max<int32_t>(1, (maxw + kSeg - 1) / kSeg);
-    const dim3 grid((unsigned)nseg, (unsigned)rows);
-    hipLaunchKernelGGL(k_front_min, grid, dim3(kFillThreads), 0, s, lb, f->w, f->row_off,
-                       (const uint16_t*)sol->m, nseg, segmin, we);
-    hipLaunchKernelGGL(k_front, grid, dim3(kFillThreads), 0, s, lb, f->w, f->row_off, sol->m,
-                       nseg, (const uint32_t*)segmin, we);
-  };
-  front(0, 1, f->level_maxw[0]);            // the empty set
-  for (int64_t l = 1; l < L; l++) {
-    const int64_t lb = f->level_ptr[l], le = f->level_ptr[l + 1];
-    const int64_t tiles = (f->level_maxw[l] + kVecTile - 1) / kVecTile;
-    if (tiles <= 0 || le <= lb) continue;
-    launch_level_vec<true>(f, l, dim3((unsigned)tiles, (unsigned)(le - lb)), lb,
-                           (int32_t)sol->Beff, (const int32_t*)we, sol->m, s);
-    front(lb, le - lb, f->level_maxw[l]);
+  for (int64_t l = 0; l < L;) {
+    const int64_t first = f->level_ptr[l];
+    int64_t most = 0, used = 0, end = l;
+    for (; end < L; end++) {
+      const int64_t tiles = (f->level_maxw[end] + per - 1) / per;
+      const int64_t rows = f->level_ptr[end + 1] - first;
+      const int64_t now = used + tiles * (f->level_ptr[end + 1] - f->level_ptr[end]);
+      const int64_t wide = std::max(most, tiles);
+      if (end > l && wide * rows > 2 * now + 65536) break;
+      most = wide;
+      used = now;
+    }
+    launch(first, dim3((unsigned)most, (unsigned)(f->level_ptr[end] - first)));
+    l = end;
   }
+}
+
+hipError_t launch_fronts(rc_solution sol, hipStream_t s) {
+  rc_family f = sol->f;
+  uint16_t* segmin = sol->arena.get_n<uint16_t>((f->cells >> kSegShift) + f->F + 1);
+  if (!segmin) return hipErrorOutOfMemory;
+  // a row starts up to 7 cells into its first segment
+  auto pass = [&](bool last) {
+    for_row_groups(f, kSeg, [&](int64_t lb, dim3 grid) {
+      grid.x += 1;
+      if (last)
+        hipLaunchKernelGGL(k_front, grid, dim3(kFillThreads), 0, s, lb, f->w, f->row_off, sol->m,
+                           (const uint16_t*)segmin);
+      else
+        hipLaunchKernelGGL(k_front_min, grid, dim3(kFillThreads), 0, s, lb, f->w, f->row_off,
+                           sol->m, segmin);
+    });
+  };
+  pass(false);
+  pass(true);
   return hipGetLastError();
 }
 
@@ -877,12 +937,11 @@ template <class T>
 static void select_t(rc_solution sol, const T* m, hipStream_t s) {
   rc_family f = sol->f;
   const int64_t v = f->F - 1;
-  const int64_t wv = f->w_host[v];
-  const unsigned blocks =
-      (unsigned)std::min<int64_t>((wv + kSelectThreads - 1) / kSelectThreads, kSelectBlocks);
-  hipLaunchKernelGGL(k_select<T>, dim3(blocks > 0 ? blocks : 1), dim3(kSelectThreads), 0, s, m,
-                     f->row_off, v, f->w, sol->objective, sol->status);
-  hipLaunchKernelGGL(k_select_finish<T>, dim3(1), dim3(64), 0, s, m, f->row_off, v, sol->status);
+  const int64_t groups = (f->w_host[v] * (int64_t)sizeof(T) + 15) / 16;
+  const unsigned blocks = (unsigned)std::max<int64_t>(
+      1, std::min<int64_t>((groups + kSelectThreads - 1) / kSelectThreads, kSelectBlocks));
+  hipLaunchKernelGGL(k_select<T>, dim3(blocks), dim3(kSelectThreads), 0, s, m, f->row_off, v,
+                     f->w, sol->objective, sol->status);
 }
 
 hipError_t launch_select(rc_solution sol, hipStream_t s) {
@@ -953,7 +1012,7 @@ hipError_t launch_trace(rc_solution sol, hipStream_t s) {
   return sol->cell32 ? trace_t<uint32_t>(sol, sol->m32, s) : trace_t<uint16_t>(sol, sol->m, s);
 }
 
-// optarg of the whole table in one launch: no cell's optarg depends on
+// optarg of the whole table in as few launches as the rows' lengths allow: no cell's optarg depends on
 // another's, so the rows need no order (one launch per size level, each
 // waiting for its longest predecessor list, took 5.4 ms on resnet50_t10's
 // 167 levels).  A list of at least 64 pairs on average is split over the
@@ -969,17 +1028,17 @@ constexpr int64_t kSplitCells = (int64_t)1 << 20;
 template <class T>
 static void arg_all_t(rc_solution sol, const T* m, hipStream_t s) {
   rc_family f = sol->f;
-  const unsigned rows = (unsigned)f->F;
-  if (f->P >= kWave * f->F || f->cells <= kSplitCells) {
-    hipLaunchKernelGGL(k_arg_split<T>, dim3((unsigned)((f->max_row + kWave - 1) / kWave), rows),
-                       dim3(kArgWaves * kWave), 0, s, f->w, f->row_off, f->pred_ptr, f->pidx,
-                       f->pdt, f->pdm, f->pc, (int32_t)sol->Beff, m, sol->arg);
-    return;
-  }
-  hipLaunchKernelGGL(k_arg_all<T>, dim3((unsigned)((f->max_row + kFillThreads - 1) / kFillThreads),
-                                        rows),
-                     dim3(kFillThreads), 0, s, f->w, f->row_off, f->pred_ptr, f->pidx, f->pdt,
-                     f->pdm, f->pc, (int32_t)sol->Beff, m, sol->arg);
+  const bool split = f->P >= kWave * f->F || f->cells <= kSplitCells;
+  for_row_groups(f, split ? kWave : kFillThreads, [&](int64_t lb, dim3 grid) {
+    if (split)
+      hipLaunchKernelGGL(k_arg_split<T>, grid, dim3(kArgWaves * kWave), 0, s, lb, f->w, f->row_off,
+                         f->pred_ptr, f->pidx, f->pdt, f->pdm, f->pc, (int32_t)sol->Beff, m,
+                         sol->arg);
+    else
+      hipLaunchKernelGGL(k_arg_all<T>, grid, dim3(kFillThreads), 0, s, lb, f->w, f->row_off,
+                         f->pred_ptr, f->pidx, f->pdt, f->pdm, f->pc, (int32_t)sol->Beff, m,
+                         sol->arg);
+  });
 }
 
 hipError_t launch_arg_all(rc_solution sol, hipStream_t s) {

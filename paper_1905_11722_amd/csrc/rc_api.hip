@@ -14,7 +14,6 @@
 #include <vector>
 
 #include "rc_internal.h"
-#include "dominance.h"
 #include "dual.h"
 
 using namespace rcdp;
@@ -874,8 +873,7 @@ static int choose_fill_path(rc_family f) {
 }  // extern "C"
 
 // A solution handle with its buffers and events; nothing enqueued yet.
-static int new_solution(rc_family f, int64_t B, int32_t objective, rc_solution* out,
-                        bool level_only = false) {
+static int new_solution(rc_family f, int64_t B, int32_t objective, rc_solution* out) {
   if (!f || B < 0) return RC_E_ARG;
   if (objective != RC_TIME_CENTRIC && objective != RC_MEMORY_CENTRIC) return RC_E_ARG;
   const int64_t Beff = std::min<int64_t>(B, 2 * f->g->M_total);
@@ -910,7 +908,7 @@ static int new_solution(rc_family f, int64_t B, int32_t objective, rc_solution* 
     return fail(RC_E_NOMEM);
   if (hipEventCreate(&sol->ev0) != hipSuccess || hipEventCreate(&sol->ev1) != hipSuccess)
     return fail(RC_E_DEVICE);
-  sol->fill_path = level_only || cell32 ? 0 : choose_fill_path(f);
+  sol->fill_path = cell32 ? 0 : choose_fill_path(f);
   if (sol->fill_path != 0 &&
       (hipEventCreate(&sol->evk0) != hipSuccess || hipEventCreate(&sol->evk1) != hipSuccess))
     return fail(RC_E_DEVICE);
@@ -989,7 +987,7 @@ static int solve_one(rc_family f, int64_t B, int32_t objective, void* stream, rc
   if (!f || !out) return RC_E_ARG;
   hipStream_t s = as_stream(stream);
   rc_solution sol = nullptr;
-  const int st0 = new_solution(f, B, objective, &sol, dominance);
+  const int st0 = new_solution(f, B, objective, &sol);
   if (st0 != RC_OK) return st0;
   if (dominance && sol->cell32) {      // the weak-front kernels take 16-bit cells only
     drop_solution(sol);
@@ -1001,14 +999,12 @@ static int solve_one(rc_family f, int64_t B, int32_t objective, void* stream, rc
     return st;
   };
   if (launch_solve_init(sol, s) != hipSuccess) return fail(RC_E_DEVICE);
-  int32_t* we = nullptr;              // the skip: end of each row's weak front
-  if (dominance && !(we = sol->arena.get_n<int32_t>(f->F))) return fail(RC_E_NOMEM);
   if (hipEventRecord(sol->ev0, s) != hipSuccess) return fail(RC_E_DEVICE);
-  const hipError_t fe = dominance               ? launch_fill_dominance(sol, we, s)
-                        : sol->fill_path == 3   ? launch_fill_wide(sol, s)
-                        : sol->fill_path == 2   ? launch_fill_ghost(sol, s)
-                        : sol->fill_path == 1 ? launch_fill_blocked(sol, s)
-                                              : launch_fill(sol, s);
+  hipError_t fe = sol->fill_path == 3   ? launch_fill_wide(sol, s)
+                  : sol->fill_path == 2 ? launch_fill_ghost(sol, s)
+                  : sol->fill_path == 1 ? launch_fill_blocked(sol, s)
+                                        : launch_fill(sol, s);
+  if (fe == hipSuccess && dominance) fe = launch_fronts(sol, s);
   if (fe != hipSuccess) {
     set_last_error(sol->fill_path == 3   ? "split-panel fill launch"
                    : sol->fill_path == 2 ? "ghost fill launch"

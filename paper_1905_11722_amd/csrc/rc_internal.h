@@ -98,19 +98,20 @@ struct DevStatus {
   int32_t pad0;
   int64_t overhead, peak, cache_mem;
   int64_t bmin;          // smallest feasible budget (rc_min_budget)
+  int32_t done;          // workgroups of the selection that have finished
+  int32_t pad1;
 };
 
 // One pair (L, L') of the level fill (fill.hip): the source row's first
 // cell lo, the source cell of target cell t' of L' at base - row_off(L') + t'
-// (base = lo - dt), the budget term, the addition, the source row's width
-// and index.
+// (base = lo - dt), the budget term, the addition and the source row's width.
 struct LevelPair {
   int64_t lo;
   int64_t base;
   int32_t c;
   int32_t dm;
   int32_t w;
-  int32_t src;
+  int32_t pad;
 };
 
 // Panel / triangle records of the blocked fill (blocks.hip).
@@ -330,6 +331,9 @@ hipError_t launch_fill(rc_solution sol, hipStream_t s);
 hipError_t launch_select(rc_solution sol, hipStream_t s);
 hipError_t launch_trace(rc_solution sol, hipStream_t s);
 hipError_t launch_arg_all(rc_solution sol, hipStream_t s);
+// The dominance skip: every row of the filled 16-bit table reduced to its
+// weak front (dominated cells stored as infinity).
+hipError_t launch_fronts(rc_solution sol, hipStream_t s);
 
 // ---- blocked fill (blocks.hip, blocked.hip)
 hipError_t launch_row_align(rc_family f, hipStream_t s);

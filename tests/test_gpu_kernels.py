@@ -6,6 +6,7 @@ import pytest
 
 from paper_1905_11722_amd import workloads as W
 
+from tests.test_gpu_dominance import compare as compare_dominance
 from tests.test_gpu_parity import compare
 
 pytestmark = pytest.mark.gpu
@@ -35,3 +36,27 @@ def test_optarg_table_long_rows_short_lists(rc, oracle_mod):
     fam = rc.Graph.create(g).build_family("pruned")
     assert fam.info["table_cells"] > 1 << 20 and fam.info["num_pairs"] < 64 * fam.info["num_sets"]
     compare(rc, oracle_mod, g, "pruned", (3 * sum(g.M)) // 2, objectives=("tc",))
+
+
+@pytest.mark.parametrize("path", ["level", "wavefront", "wide", "ghost"])
+@pytest.mark.parametrize("total", [2040, 2048, 2049, 4097, 6151])
+def test_dominance_segments(rc, monkeypatch, path, total):
+    """The weak fronts of rows that end just before, on and after a segment of
+    2048 cells, from the table of every fill."""
+    monkeypatch.setenv("RCDP_FILL", path)
+    g = W.chain(9, seed=total, tmax=total // 9, mmax=40)
+    g.T[4] += total - sum(g.T)
+    for B in (2 * max(g.M) + 8, sum(g.M), 2 * sum(g.M)):
+        compare_dominance(rc, g, "exact", B)
+
+
+@pytest.mark.parametrize("width", [1, 7, 8, 9, 64, 65, 2048, 2049, 131073])
+@pytest.mark.parametrize("scale", [1, 4096])
+def test_selection_row_lengths(rc, oracle_mod, width, scale):
+    """t* and opt[V, t*] of a row V of `width` + 1 cells for both objectives,
+    in 16-bit cells and (sizes scaled) in 32-bit cells."""
+    g = W.chain(5, seed=width, tmax=max(1, width // 5), mmax=40)
+    g.T[0] = max(1, width - sum(g.T[1:]))
+    g.M = [m * scale for m in g.M]
+    for B in ((3 * sum(g.M)) // 2, 2 * sum(g.M)):
+        compare(rc, oracle_mod, g, "exact", B, table=width < 4096)
