@@ -858,15 +858,17 @@ static int choose_fill_path(rc_family f) {
   // The wavefront against the level launches, by their measured costs on
   // this GPU.  The wavefront runs its 256-cell columns at most three (the
   // split-panel fill: four) per compute unit at a time, each through every
-  // row of the table at about 2.5 us per row.  A level launch costs about 6 us, plus the source reads
-  // of its pairs (2 bytes per relaxation) at about 4 TB/s.  Few levels of
-  // many sets or of very long rows (the ladder and U-Net shapes) take the
-  // level launches; many levels take the wavefront.
+  // row of the table at about 2.5 us per row.  A level launch costs about
+  // 4 us, plus the source reads of its pairs (2 bytes per relaxation) at
+  // about 6 TB/s, partly beside each other.  Few levels of many sets or of
+  // very long rows take the level launches (ms, level against wavefront:
+  // ladder40 0.17 / 0.49, layered36 1.7, U-Net 0.44 / 1.05), many levels the
+  // wavefront (ResNet-50 0.85 / 0.61).
   const int64_t levels = (int64_t)f->level_ptr.size() - 1;
   const int64_t slots = (wave == 3 ? wide_slots_per_cu(3) : 3) * (int64_t)num_cus();
   const int64_t col_rounds = ((f->max_row + kWC - 1) / kWC + slots - 1) / slots;
   const double wave_us = 2.5 * (double)f->F * (double)col_rounds;
-  const double level_us = 6.0 * (double)levels + 2.0 * (double)f->relax / 4.0e6;
+  const double level_us = 4.0 * (double)levels + 2.0 * (double)f->relax / 6.0e6;
   return level_us < wave_us ? 0 : wave;
 }
 

@@ -103,15 +103,13 @@ struct DevStatus {
 };
 
 // One pair (L, L') of the level fill (fill.hip): the source row's first
-// cell lo, the source cell of target cell t' of L' at base - row_off(L') + t'
-// (base = lo - dt), the budget term, the addition and the source row's width.
+// cell lo, the shift dt (source t = target t - dt), the source row's width,
+// the budget term and the addition.
 struct LevelPair {
   int64_t lo;
-  int64_t base;
-  int32_t c;
-  int32_t dm;
-  int32_t w;
-  int32_t pad;
+  int32_t dt, w;
+  int32_t c, dm;
+  int32_t pad0, pad1;
 };
 
 // Panel / triangle records of the blocked fill (blocks.hip).

@@ -60,3 +60,27 @@ def test_selection_row_lengths(rc, oracle_mod, width, scale):
     g.M = [m * scale for m in g.M]
     for B in ((3 * sum(g.M)) // 2, 2 * sum(g.M)):
         compare(rc, oracle_mod, g, "exact", B, table=width < 4096)
+
+
+@pytest.mark.parametrize("scale", [1, 8192])
+@pytest.mark.parametrize("nodes,tmax", [(1, 3), (9, 400), (12, 129), (65, 9), (129, 3), (300, 2),
+                                        (1100, 1)])
+def test_level_fill_lists_and_tiles(rc, oracle_mod, monkeypatch, nodes, tmax, scale):
+    """The level fill in 16- and 32-bit cells (sizes scaled): predecessor lists
+    from one pair to more than sixteen waves hold in a round, rows of a few
+    cells to several tiles with ragged ends."""
+    monkeypatch.setenv("RCDP_FILL", "level")
+    g = W.chain(nodes, seed=nodes, tmax=tmax, mmax=15)
+    g.M = [m * scale for m in g.M]
+    compare(rc, oracle_mod, g, "pruned", (3 * sum(g.M)) // 2, objectives=("tc",))
+
+
+@pytest.mark.parametrize("scale", [1, 8192])
+@pytest.mark.parametrize("seed", range(3))
+def test_level_fill_wide_levels(rc, oracle_mod, monkeypatch, seed, scale):
+    """Levels of many targets, lists that mix passing and failing budgets."""
+    monkeypatch.setenv("RCDP_FILL", "level")
+    g = W.layered(4, 4, seed, tmax=60, mmax=30)
+    g.M = [m * scale for m in g.M]
+    for share in (1.2, 1.6, 2.0):
+        compare(rc, oracle_mod, g, "exact", int(share * sum(g.M)))
