@@ -208,94 +208,177 @@ __global__ __launch_bounds__(kClosureThreads) void k_ancestors_closure(int n, in
   }
 }
 
-// Candidates of the pruned family, set-major: [0] = empty set,
-// [1 + v] = L^v, [n + 1] = V.
-__global__ void k_pruned_candidates(int n, int words, const uint64_t* anc, uint64_t* cand) {
-  const int64_t total = (int64_t)(n + 2) * words;
-  for (int64_t it = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; it < total;
-       it += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t c = it / words;
-    const int w = (int)(it % words);
-    uint64_t x;
-    if (c == 0) {
-      x = 0;
-    } else if (c <= n) {
-      x = anc[(c - 1) * words + w];
-    } else {
-      const int lo = w * 64;
-      const int cnt = n - lo;
-      x = cnt >= 64 ? ~0ull : ((1ull << cnt) - 1);
+// ---------------------------------------------------- exact enumeration
+
+// Reverse search over lower sets, one size level after the other.  A lower
+// set X != {} has the canonical parent X \ {x}, x the largest node id of X
+// with no successor inside X (removing such an x keeps delta^-(X \ {x})
+// inside).  For every parent P of size s and node v with v not in P and
+// delta^-(v) inside P, the child X = P + {v} is kept iff v is X's canonical
+// element.  With S(P) the nodes of P without a successor in P, those of X
+// are S(X) = (S(P) \ delta^-(v)) + {v} (no node of P has v's successors: a
+// successor of v inside P would put v in P), so v is canonical iff no node
+// of S(P) \ delta^-(v) has a larger id.  S travels with each candidate
+// (top), and a test costs a few words instead of a walk over P's nodes.
+// Children are appended through an atomic counter; their order within the
+// level is fixed afterwards by the rank kernel.  Level s is
+// cand[lvl[s] .. lvl[s] + cnt[s]).
+//
+// Word w of the test of (P, v): bit 1 = a predecessor of v is missing, bit 2
+// = a node of S(P) \ delta^-(v) above v, bit 4 = v is in P.
+__device__ __forceinline__ int enum_word(uint64_t Pw, uint64_t Sw, uint64_t pred, int w, int v) {
+  const int vw = v >> 6;
+  const uint64_t vb = w == vw ? 1ull << (v & 63) : 0ull;
+  const uint64_t above = w > vw ? ~0ull : (w == vw ? ~((vb << 1) - 1) : 0ull);
+  return ((pred & ~Pw) != 0 ? 1 : 0) | ((Sw & ~pred & above) != 0 ? 2 : 0) |
+         ((Pw & vb) != 0 ? 4 : 0);
+}
+
+// The first levels in one workgroup, while the frontier fits LDS (frontier
+// sets x words <= kEnumWords): two barriers a level instead of two launches.
+// Small graphs end here: a 16-node chain, 16 levels, 14 us against 60, the
+// 40-node ladder's 40 levels 37 us against 247.  stop[0] = the first level
+// not expanded (n when done), stop[1] = sets found, stop[2] = overflow (host
+// memory).
+constexpr int kEnumWords = 1024;
+constexpr int kEnumMasks = 3072;          // n * words of the graphs taken
+constexpr int kEnumThreads = 1024;
+
+__global__ __launch_bounds__(kEnumThreads) void k_enum_block(int n, int words,
+                                                             const uint64_t* pred_g,
+                                                             uint64_t* cand, uint64_t* top,
+                                                             int64_t cap, int32_t* lvl,
+                                                             int32_t* cnt, DevStatus* st,
+                                                             int32_t* stop) {
+  __shared__ uint64_t s_pred[kEnumMasks];
+  __shared__ uint64_t s_set[2][kEnumWords], s_top[2][kEnumWords];
+  __shared__ int32_t s_n[2];
+  const int tid = threadIdx.x;
+  for (int x = tid; x < (int)(sizeof(DevStatus) / 4); x += kEnumThreads)
+    reinterpret_cast<int32_t*>(st)[x] = 0;
+  for (int x = tid; x < n * words; x += kEnumThreads) s_pred[x] = pred_g[x];
+  for (int x = tid; x < n + 2; x += kEnumThreads) cnt[x] = 0;
+  for (int x = tid; x < words; x += kEnumThreads) {
+    s_set[0][x] = 0;
+    s_top[0][x] = 0;
+    cand[x] = 0;                          // the empty set
+    top[x] = 0;
+  }
+  if (tid == 0) s_n[0] = 1;
+  __syncthreads();
+  int64_t base = 0;                       // first set of the level
+  int lev = 0, here = 1;
+  bool over = false;
+  for (; lev < n; lev++) {
+    const int f = lev & 1;
+    if (tid == 0) {
+      s_n[f ^ 1] = 0;
+      lvl[lev] = (int32_t)base;
+      cnt[lev] = here;
     }
-    cand[it] = x;
+    __syncthreads();
+    const uint32_t items = (uint32_t)here * (uint32_t)n;
+    for (uint32_t it = tid; it < items; it += kEnumThreads) {
+      const int p = (int)(it / (uint32_t)n), v = (int)(it - (uint32_t)p * n);
+      int bad = 0;
+      for (int w = 0; w < words; w++)
+        bad |= enum_word(s_set[f][p * words + w], s_top[f][p * words + w], s_pred[v * words + w],
+                         w, v);
+      if (bad) continue;
+      const int slot = atomicAdd(&s_n[f ^ 1], 1);
+      const int64_t g = base + here + slot;
+      for (int w = 0; w < words; w++) {
+        const uint64_t vb = w == (v >> 6) ? 1ull << (v & 63) : 0ull;
+        const uint64_t X = s_set[f][p * words + w] | vb;
+        const uint64_t S = (s_top[f][p * words + w] & ~s_pred[v * words + w]) | vb;
+        if ((slot + 1) * words <= kEnumWords) {
+          s_set[f ^ 1][slot * words + w] = X;
+          s_top[f ^ 1][slot * words + w] = S;
+        }
+        if (g < cap) {
+          cand[g * words + w] = X;
+          top[g * words + w] = S;
+        }
+      }
+    }
+    __syncthreads();
+    const int next = s_n[f ^ 1];
+    base += here;
+    here = next;
+    over = base + here > cap;
+    if (over || here * words > kEnumWords) {
+      lev++;
+      break;
+    }
+  }
+  if (tid == 0) {
+    lvl[lev] = (int32_t)base;
+    cnt[lev] = over ? 0 : here;
+    lvl[lev + 1] = (int32_t)(base + here);
+    st->count = over ? cap : base + here;
+    st->overflow = over;
+    stop[0] = over ? n : lev;
+    stop[1] = over ? 0 : (int32_t)(base + here);
+    stop[2] = over;
   }
 }
 
-// ---------------------------------------------------- exact enumeration
-
-// One size level of reverse search over lower sets.  A lower set X != {}
-// has the canonical parent X \ {x}, x the largest node id of X with no
-// successor inside X (removing such an x keeps delta^-(X \ {x}) inside).
-// For every parent P of size s and node v with v not in P and
-// delta^-(v) inside P, the child X = P + {v} is kept iff v is X's
-// canonical element: every node of P with a larger id has a successor in X
-// (v itself has none: a successor of v inside P would put v in P).
-// Children are appended through an atomic counter; their order within the
-// level is fixed afterwards by the rank kernel.
-__global__ __launch_bounds__(256) void k_enum_level(int n, int words, int s, const uint64_t* succ,
-                                                    const uint64_t* pred, uint64_t* cand,
-                                                    int64_t cap, int32_t* lvl, DevStatus* st) {
-  const int64_t pb = lvl[s], pe = lvl[s + 1];
-  const int64_t items = (pe - pb) * n;
-  for (int64_t it = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; it < items;
-       it += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t p = pb + it / n;
-    const int v = (int)(it % n);
-    const uint64_t* P = cand + p * words;
-    const int vw = v >> 6;
-    const uint64_t vb = 1ull << (v & 63);
-    if (P[vw] & vb) continue;
-    bool ok = true;
-    for (int w = 0; w < words && ok; w++) ok = (pred[(int64_t)v * words + w] & ~P[w]) == 0;
-    if (!ok) continue;
-    // every x in P with x > v needs a successor in X = P + {v}
-    for (int w = words - 1; w >= vw && ok; w--) {
-      uint64_t bits = P[w];
-      if (w == vw) bits &= ~((vb << 1) - 1);  // ids > v only
-      while (bits && ok) {
-        const int x = w * 64 + __builtin_ctzll(bits);
-        bits &= bits - 1;
-        bool has = false;
-        for (int u = 0; u < words && !has; u++) {
-          uint64_t X = P[u] | (u == vw ? vb : 0ull);
-          has = (succ[(int64_t)x * words + u] & X) != 0;
-        }
-        ok = has;
-      }
-    }
-    if (!ok) continue;
-    const unsigned long long slot = atomicAdd((unsigned long long*)&st->count, 1ull);
-    if ((int64_t)slot >= cap) {
+// One size level over the whole chip; cnt[s + 1] starts at 0.
+__global__ __launch_bounds__(256) void k_enum_level(int n, int words, int s, const uint64_t* pred,
+                                                    uint64_t* cand, uint64_t* top, int64_t cap,
+                                                    int32_t* lvl, int32_t* cnt, DevStatus* st) {
+  const int64_t pb = lvl[s];
+  const int32_t here = (int32_t)max((int64_t)0, min((int64_t)cnt[s], cap - pb));  // stored sets
+  const int64_t nb = pb + here;            // first set of the next level
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    lvl[s + 1] = (int32_t)nb;
+    st->count = nb;                        // the last level's own launch adds nothing
+  }
+  const uint32_t items = (uint32_t)here * (uint32_t)n;     // at most 65535 * 4096
+  for (uint32_t it = blockIdx.x * blockDim.x + threadIdx.x; it < items;
+       it += gridDim.x * blockDim.x) {
+    const uint32_t p = it / (uint32_t)n;
+    const int v = (int)(it - p * (uint32_t)n);
+    const uint64_t* P = cand + (pb + p) * words;
+    const uint64_t* S = top + (pb + p) * words;
+    const uint64_t* pv = pred + (int64_t)v * words;
+    int bad = 0;
+    for (int w = 0; w < words && !bad; w++) bad = enum_word(P[w], S[w], pv[w], w, v);
+    if (bad) continue;
+    const int64_t g = nb + atomicAdd(&cnt[s + 1], 1);
+    if (g >= cap) {
       st->overflow = 1;
       continue;
     }
-    for (int w = 0; w < words; w++) cand[(int64_t)slot * words + w] = P[w] | (w == vw ? vb : 0ull);
+    for (int w = 0; w < words; w++) {
+      const uint64_t vb = w == (v >> 6) ? 1ull << (v & 63) : 0ull;
+      cand[g * words + w] = P[w] | vb;
+      top[g * words + w] = (S[w] & ~pv[w]) | vb;
+    }
   }
 }
 
-__global__ void k_enum_start(int words, uint64_t* cand, int32_t* lvl, DevStatus* st) {
-  for (int w = threadIdx.x; w < words; w += blockDim.x) cand[w] = 0;  // the empty set
-  if (threadIdx.x == 0) {
-    st->count = 1;
-    st->overflow = 0;
-    lvl[0] = 0;
-    lvl[1] = 1;
+// The empty set as level 0, for graphs that k_enum_block does not take.
+__global__ void k_enum_start(int n, int words, uint64_t* cand, uint64_t* top, int32_t* lvl,
+                             int32_t* cnt, DevStatus* st) {
+  for (int x = threadIdx.x; x < (int)(sizeof(DevStatus) / 4); x += blockDim.x)
+    reinterpret_cast<int32_t*>(st)[x] = 0;
+  for (int w = threadIdx.x; w < words; w += blockDim.x) {
+    cand[w] = 0;
+    top[w] = 0;
   }
+  for (int x = threadIdx.x; x < n + 2; x += blockDim.x) cnt[x] = x == 0 ? 1 : 0;
+  if (threadIdx.x == 0) lvl[0] = 0;
 }
 
-// After level s: sets of size s + 1 occupy [lvl[s+1], count).
-__global__ void k_enum_close(int s, int64_t cap, int32_t* lvl, DevStatus* st) {
-  const int64_t c = st->count;
-  lvl[s + 2] = (int32_t)(c < cap ? c : cap);
+// The size of the enumerated family to the host.
+__global__ void k_enum_end(int n, const int32_t* lvl, const int32_t* cnt, DevStatus* st,
+                           int32_t* stop) {
+  const int32_t total = lvl[n] + cnt[n];
+  st->count = total;
+  stop[0] = n;
+  stop[1] = total;
+  stop[2] = st->overflow;
 }
 
 // --------------------------------------------------------------- ranking
@@ -308,33 +391,32 @@ __device__ __forceinline__ int cmp_value(const uint64_t* a, const uint64_t* b, i
   return 0;
 }
 
-__device__ __forceinline__ int popcnt_set(const uint64_t* a, int words) {
-  int c = 0;
-  for (int w = 0; w < words; w++) c += __popcll(a[w]);
-  return c;
-}
-
 // Canonical order: ascending size, then ascending numeric value.  Exact
 // family: candidates are grouped by size level (reverse search yields no
-// duplicates) and ranked within their level.  Output is word-major:
+// duplicates) and ranked within their level, a wave per candidate with the
+// level's other sets over its lanes (6199 sets in levels of up to 583: 10 us
+// against 132 with a thread per candidate).  Output is word-major:
 // bits[w * fstride + index].
-__global__ __launch_bounds__(256) void k_rank(int words, int n, const uint64_t* cand,
-                                              const int32_t* lvl, uint64_t* bits, int64_t fstride,
-                                              DevStatus* st) {
-  const int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t total = lvl[n + 1];
-  if (x >= total) return;
+__global__ __launch_bounds__(256) void k_rank(int words, int64_t F, const uint64_t* cand,
+                                              const int32_t* lvl, const int32_t* cnt,
+                                              uint64_t* bits, int64_t fstride, DevStatus* st) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t x = blockIdx.x * (int64_t)(blockDim.x / kWave) + threadIdx.x / kWave;
+  if (x >= F) return;
   const uint64_t* X = cand + x * words;
-  const int s = popcnt_set(X, words);
-  int64_t rank = lvl[s];
-  for (int64_t y = lvl[s]; y < lvl[s + 1]; y++)
-    if (y != x && cmp_value(cand + y * words, X, words) < 0) rank++;
-  if (x == 0) st->count = st->overflow ? st->count : total;
+  int sz = lane < words ? __popcll(X[lane]) : 0;
+  for (int off = 32; off > 0; off >>= 1) sz += __shfl_xor(sz, off, kWave);
+  const int64_t b = lvl[sz], e = b + cnt[sz];
+  int less = 0;
+  for (int64_t y = b + lane; y < e; y += kWave)
+    less += cmp_value(cand + y * words, X, words) < 0 ? 1 : 0;
+  for (int off = 32; off > 0; off >>= 1) less += __shfl_xor(less, off, kWave);
+  const int64_t rank = b + less;
   if (rank >= fstride) {
-    st->error = 1;
+    if (lane == 0) st->error = 1;
     return;
   }
-  for (int w = 0; w < words; w++) bits[(int64_t)w * fstride + rank] = X[w];
+  if (lane < words) bits[(int64_t)lane * fstride + rank] = X[lane];
 }
 
 // Pruned family: candidates are [0] the empty set, [1..n] the sets L^v
@@ -342,7 +424,8 @@ __global__ __launch_bounds__(256) void k_rank(int words, int n, const uint64_t* 
 // equals V.  One workgroup: the candidates are bucketed by size (a counting
 // sort in LDS), and a candidate's index is the number of candidates of
 // smaller size plus those of its own size with a smaller numeric value.
-__global__ __launch_bounds__(1024) void k_rank_pruned(int words, int n, const uint64_t* cand,
+// anc[v] = L^v; the empty set and V are formed here.  Clears the status.
+__global__ __launch_bounds__(1024) void k_rank_pruned(int words, int n, const uint64_t* anc,
                                                       uint64_t* bits, int64_t fstride,
                                                       DevStatus* st) {
   constexpr int kThreads = 1024;
@@ -355,9 +438,20 @@ __global__ __launch_bounds__(1024) void k_rank_pruned(int words, int n, const ui
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wave = tid / kWave;
   const int total = n + 2, bins = n + 2;       // sizes 0..n, counted one bin up
+  auto word = [&](int x, int w) -> uint64_t {
+    if (x == 0) return 0;
+    if (x <= n) return anc[(int64_t)(x - 1) * words + w];
+    const int left = n - w * 64;
+    return left >= 64 ? ~0ull : (1ull << left) - 1;
+  };
+  if (tid < (int)(sizeof(DevStatus) / 4)) reinterpret_cast<int32_t*>(st)[tid] = 0;
   if (tid == 0) s_vdup = n == 0;                 // V is the empty set itself
   for (int x = tid; x < bins; x += kThreads) s_start[x] = 0;
-  for (int x = tid; x < total; x += kThreads) s_sz[x] = popcnt_set(cand + (int64_t)x * words, words);
+  for (int x = tid; x < total; x += kThreads) {
+    int c = 0;
+    for (int w = 0; w < words; w++) c += __popcll(word(x, w));
+    s_sz[x] = c;
+  }
   __syncthreads();
   for (int x = 1 + tid; x <= n; x += kThreads)
     if (s_sz[x] == n) s_vdup = 1;                 // some L^v is V already
@@ -390,18 +484,20 @@ __global__ __launch_bounds__(1024) void k_rank_pruned(int words, int n, const ui
   for (int x = tid; x < valid; x += kThreads) s_list[atomicAdd(&s_next[s_sz[x]], 1)] = x;
   __syncthreads();
   for (int x = tid; x < valid; x += kThreads) {
-    const uint64_t* X = cand + (int64_t)x * words;
     const int sx = s_sz[x];
     int64_t rank = s_start[sx];
     for (int q = s_start[sx]; q < s_start[sx + 1]; q++) {
       const int y = s_list[q];
-      if (y != x && cmp_value(cand + (int64_t)y * words, X, words) < 0) rank++;
+      if (y == x) continue;
+      int w = words - 1;
+      while (w > 0 && word(y, w) == word(x, w)) w--;
+      if (word(y, w) < word(x, w)) rank++;
     }
     if (rank >= fstride) {
       st->error = 1;
       continue;
     }
-    for (int w = 0; w < words; w++) bits[(int64_t)w * fstride + rank] = X[w];
+    for (int w = 0; w < words; w++) bits[(int64_t)w * fstride + rank] = word(x, w);
   }
   if (tid == 0) st->count = valid;
 }
@@ -607,20 +703,6 @@ __global__ __launch_bounds__(256) void k_set_quantities_lanes(
   }
 }
 
-__global__ void k_row_widths(int64_t F, const int32_t* w, int64_t* padded) {
-  const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (s < F) padded[s] = row_slot(w[s]);
-}
-
-// Rows are right-aligned inside their padded slots: row s ends on a
-// kRowAlign boundary, so every column counted from the row end is made of
-// whole 128-byte lines, and at least kGuard padding cells separate it from
-// the previous row.
-__global__ void k_row_align(int64_t F, const int32_t* w, int64_t* row_off) {
-  const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (s < F) row_off[s] += row_slot(w[s]) - w[s];
-}
-
 // ------------------------------------------------------------------ pairs
 
 // Subset test of family members i and j (word-major storage).
@@ -633,21 +715,41 @@ __device__ __forceinline__ bool is_subset(const uint64_t* bits, int64_t fstride,
 
 // Predecessors of target j: i < j with L_i a proper subset of L_j.  The
 // family is sorted by size, so every proper subset has a smaller index;
-// equal sizes are never proper subsets.
+// equal sizes are never proper subsets.  counts[j] = their number, walg[j] =
+// the sum of their w_i (relaxations of Algorithm 1's loop), and with mask
+// [F][mw] (mw = ceil(F / 64); null: not kept) their bits, which k_pair_write
+// reads instead of testing the subsets again.
 __global__ __launch_bounds__(256) void k_pair_count(int64_t F, int words, int64_t fstride,
-                                                    const uint64_t* bits, const int32_t* size,
-                                                    int64_t* counts) {
+                                                    const uint64_t* __restrict__ bits,
+                                                    const int32_t* __restrict__ size,
+                                                    const int32_t* __restrict__ w, int64_t* counts,
+                                                    int64_t* walg, uint64_t* mask, int64_t mw) {
   const int64_t j = blockIdx.x;
-  __shared__ int64_t acc;
-  if (threadIdx.x == 0) acc = 0;
-  __syncthreads();
-  int64_t c = 0;
+  __shared__ int64_t s_c[4], s_w[4];
+  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+  int64_t c = 0, ws = 0;
   const int sj = size[j];
-  for (int64_t i = threadIdx.x; i < j; i += blockDim.x)
-    if (size[i] < sj && is_subset(bits, fstride, words, i, j)) c++;
-  atomicAdd((unsigned long long*)&acc, (unsigned long long)c);
+  for (int64_t i0 = 0; i0 < j; i0 += blockDim.x) {
+    const int64_t i = i0 + threadIdx.x;
+    const bool is = i < j && size[i] < sj && is_subset(bits, fstride, words, i, j);
+    const uint64_t b = __ballot(is);
+    if (mask && lane == 0 && i < j) mask[j * mw + i / kWave] = b;
+    if (is) {
+      c++;
+      ws += w[i];
+    }
+  }
+  c = wave_sum_i64(c);
+  ws = wave_sum_i64(ws);
+  if (lane == 0) {
+    s_c[wv] = c;
+    s_w[wv] = ws;
+  }
   __syncthreads();
-  if (threadIdx.x == 0) counts[j] = acc;
+  if (threadIdx.x == 0) {
+    counts[j] = s_c[0] + s_c[1] + s_c[2] + s_c[3];
+    walg[j] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+  }
 }
 
 // Pair data of (L = L_i, L' = L_j), in ascending i for every target j:
@@ -656,98 +758,187 @@ __global__ __launch_bounds__(256) void k_pair_count(int64_t F, int words, int64_
 //   c  = 2 M(L' \ L) + A(L')  = 2 (M(L') - M(L)) + A(L')
 // so that the step of Algorithm 1 from (L, t, m) is admitted iff
 // m + c <= B and then lands on (L', t + dt) with cache m + dm.  Only the
-// two sums over L & bd(L') depend on the pair; bd(L') is small.
-// walg[j] = sum over predecessors of w_i.
+// two sums over L & bd(L') depend on the pair; bd(L') is small: its nodes,
+// the same for every pair of the workgroup, are walked with their costs in
+// scalars while each thread tests its own L_i.  kMask: the pairs come from
+// k_pair_count's bits (prefix of their counts in LDS, no barrier per chunk).
+constexpr int64_t kMaskSets = 8192;      // families whose pair bits are kept (8 MB)
+
+template <bool kMask>
 __global__ __launch_bounds__(256) void k_pair_write(
-    int64_t F, int words, int64_t fstride, const uint64_t* bits, const uint64_t* bd,
-    const int32_t* size, const int32_t* Tsum, const int32_t* Msum, const int32_t* Tbd,
-    const int32_t* Mbd, const int32_t* A, const int32_t* w, const int32_t* T, const int32_t* M,
-    const int64_t* pred_ptr, int32_t* pidx, int32_t* pdt, int32_t* pdm, int32_t* pc,
-    int64_t* walg) {
+    int64_t F, int words, int64_t fstride, const uint64_t* __restrict__ bits,
+    const uint64_t* __restrict__ bd, const int32_t* __restrict__ size,
+    const int32_t* __restrict__ Tsum, const int32_t* __restrict__ Msum,
+    const int32_t* __restrict__ Tbd, const int32_t* __restrict__ Mbd,
+    const int32_t* __restrict__ A, const int32_t* __restrict__ T, const int32_t* __restrict__ M,
+    const int64_t* __restrict__ pred_ptr, const uint64_t* __restrict__ mask, int64_t mw,
+    int32_t* pidx, int32_t* pdt, int32_t* pdm, int32_t* pc) {
   const int64_t j = blockIdx.x;
   __shared__ int64_t base;
-  __shared__ int64_t wsum;
   __shared__ int32_t wave_cnt[4];
-  if (threadIdx.x == 0) {
-    base = pred_ptr[j];
-    wsum = 0;
+  __shared__ int32_t s_pre[kMask ? kMaskSets / kWave + 1 : 1];
+  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+  const int64_t p0 = pred_ptr[j];
+  if (kMask) {
+    // exclusive prefix of the mask words' counts, wave 0
+    if (wv == 0) {
+      const int nw = (int)((j + kWave - 1) / kWave);
+      int run = 0;
+      for (int x0 = 0; x0 < nw; x0 += kWave) {
+        const int x = x0 + lane;
+        const int v = x < nw ? __popcll(mask[j * mw + x]) : 0;
+        int incl = v;
+        for (int off = 1; off < kWave; off <<= 1) {
+          const int y = __shfl_up(incl, off, kWave);
+          if (lane >= off) incl += y;
+        }
+        if (x < nw) s_pre[x] = run + incl - v;
+        run += __shfl(incl, kWave - 1, kWave);
+      }
+    }
+  } else if (threadIdx.x == 0) {
+    base = p0;
   }
   __syncthreads();
   const int sj = size[j];
-  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-  int64_t my_w = 0;
+  const int64_t tj = (int64_t)Tsum[j] - Tbd[j], mbj = Mbd[j], cj = 2 * (int64_t)Msum[j] + A[j];
   for (int64_t i0 = 0; i0 < j; i0 += blockDim.x) {
     const int64_t i = i0 + threadIdx.x;
-    const bool is = i < j && size[i] < sj && is_subset(bits, fstride, words, i, j);
-    const uint64_t mask = __ballot(is);
-    const int before = __popcll(mask & ((1ull << lane) - 1));
-    if (lane == 0) wave_cnt[wv] = __popcll(mask);
-    __syncthreads();
-    int64_t off = base;
-    for (int q = 0; q < wv; q++) off += wave_cnt[q];
-    if (is) {
+    bool is;
+    int64_t p = 0;
+    if (kMask) {
+      const uint64_t b = i < j ? mask[j * mw + i / kWave] : 0ull;
+      is = (b >> lane) & 1;
+      if (is) p = p0 + s_pre[i / kWave] + __popcll(b & ((1ull << lane) - 1));
+    } else {
+      is = i < j && size[i] < sj && is_subset(bits, fstride, words, i, j);
+      const uint64_t b = __ballot(is);
+      if (lane == 0) wave_cnt[wv] = __popcll(b);
+      __syncthreads();
+      p = base + __popcll(b & ((1ull << lane) - 1));
+      for (int q = 0; q < wv; q++) p += wave_cnt[q];
+    }
+    if (__any(is)) {
       int64_t ti = 0, mi = 0;
       for (int ww = 0; ww < words; ww++) {
-        const uint64_t x = bits[(int64_t)ww * fstride + i] & bd[(int64_t)ww * fstride + j];
-        ti += word_cost(x, ww, T);
-        mi += word_cost(x, ww, M);
+        uint64_t Bw = bd[(int64_t)ww * fstride + j];
+        if (!Bw) continue;
+        const uint64_t x = is ? bits[(int64_t)ww * fstride + i] : 0ull;
+        for (; Bw; Bw &= Bw - 1) {
+          const int v = __builtin_ctzll(Bw);
+          const int64_t hit = -(int64_t)((x >> v) & 1);
+          ti += hit & T[ww * 64 + v];
+          mi += hit & M[ww * 64 + v];
+        }
       }
-      const int64_t p = off + before;
-      pidx[p] = (int32_t)i;
-      pdt[p] = (int32_t)((int64_t)Tsum[j] - Tbd[j] - Tsum[i] + ti);
-      pdm[p] = (int32_t)((int64_t)Mbd[j] - mi);
-      pc[p] = (int32_t)(2 * ((int64_t)Msum[j] - Msum[i]) + A[j]);
-      my_w += w[i];
+      if (is) {
+        pidx[p] = (int32_t)i;
+        pdt[p] = (int32_t)(tj - Tsum[i] + ti);
+        pdm[p] = (int32_t)(mbj - mi);
+        pc[p] = (int32_t)(cj - 2 * (int64_t)Msum[i]);
+      }
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int64_t tot = 0;
-      for (int q = 0; q < (int)(blockDim.x / kWave); q++) tot += wave_cnt[q];
-      base += tot;
+    if (!kMask) {
+      __syncthreads();
+      if (threadIdx.x == 0)
+        for (int q = 0; q < (int)(blockDim.x / kWave); q++) base += wave_cnt[q];
+      __syncthreads();
     }
-    __syncthreads();
   }
-  atomicAdd((unsigned long long*)&wsum, (unsigned long long)my_w);
-  __syncthreads();
-  if (threadIdx.x == 0) walg[j] = wsum;
 }
 
 // ------------------------------------------------------------ scan / sum
 
-// Exclusive scan of in[0..count) into out[0..count]; one workgroup.
-__global__ __launch_bounds__(1024) void k_scan(const int64_t* in, int64_t* out, int64_t count) {
-  __shared__ int64_t buf[1024];
-  __shared__ int64_t carry;
-  if (threadIdx.x == 0) carry = 0;
+// Sum over the workgroup's lanes before this one, and the workgroup's total.
+constexpr int kScanThreads = 1024;
+__device__ __forceinline__ int64_t block_scan(int64_t x, int64_t* s_part, int64_t* total) {
+  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+  int64_t incl = x;
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int64_t y = __shfl_up(incl, off, kWave);
+    if (lane >= off) incl += y;
+  }
+  if (lane == kWave - 1) s_part[wv] = incl;
   __syncthreads();
-  for (int64_t b = 0; b < count; b += 1024) {
+  int64_t before = 0, all = 0;
+  for (int q = 0; q < kScanThreads / kWave; q++) {
+    const int64_t v = s_part[q];
+    if (q < wv) before += v;
+    all += v;
+  }
+  __syncthreads();
+  *total = all;
+  return before + incl - x;
+}
+
+// Exclusive scan of in[0..count) into out[0..count]; one workgroup.
+__global__ __launch_bounds__(kScanThreads) void k_scan(const int64_t* in, int64_t* out,
+                                                       int64_t count) {
+  __shared__ int64_t s_part[kScanThreads / kWave];
+  int64_t carry = 0;
+  for (int64_t b = 0; b < count; b += kScanThreads) {
     const int64_t i = b + threadIdx.x;
-    const int64_t x = i < count ? in[i] : 0;
-    buf[threadIdx.x] = x;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-      const int64_t y = threadIdx.x >= (unsigned)off ? buf[threadIdx.x - off] : 0;
-      __syncthreads();
-      buf[threadIdx.x] += y;
-      __syncthreads();
-    }
-    if (i < count) out[i] = carry + buf[threadIdx.x] - x;
-    __syncthreads();
-    if (threadIdx.x == 1023) carry += buf[1023];
-    __syncthreads();
+    int64_t total;
+    const int64_t pre = block_scan(i < count ? in[i] : 0, s_part, &total);
+    if (i < count) out[i] = carry + pre;
+    carry += total;
   }
   if (threadIdx.x == 0) out[count] = carry;
 }
 
-__global__ __launch_bounds__(1024) void k_sum(const int64_t* in, int64_t count, int64_t* out) {
-  __shared__ int64_t acc;
-  if (threadIdx.x == 0) acc = 0;
-  __syncthreads();
-  int64_t s = 0;
-  for (int64_t i = threadIdx.x; i < count; i += blockDim.x) s += in[i];
-  atomicAdd((unsigned long long*)&acc, (unsigned long long)s);
-  __syncthreads();
-  if (threadIdx.x == 0) *out = acc;
+// The family's shape in one launch: row offsets (rows right-aligned inside
+// their padded slots: row s ends on a kRowAlign boundary, so every column
+// counted from the row end is made of whole 128-byte lines, and at least
+// kGuard padding cells separate it from the previous row), predecessor
+// offsets, the relaxation count, and what the host needs of them, written
+// straight to its pinned buffer (the status, sizes, widths and both offset
+// arrays at the byte offsets of o).
+struct ShapeOut {
+  char* host;
+  int64_t o_st, o_size, o_w, o_off, o_pp;
+};
+
+__global__ __launch_bounds__(kScanThreads) void k_shape(int64_t F, const int32_t* size,
+                                                        const int32_t* w, const int64_t* counts,
+                                                        const int64_t* walg, int64_t* row_off,
+                                                        int64_t* pred_ptr, DevStatus* st,
+                                                        ShapeOut o) {
+  __shared__ int64_t s_part[kScanThreads / kWave];
+  int32_t* h_size = reinterpret_cast<int32_t*>(o.host + o.o_size);
+  int32_t* h_w = reinterpret_cast<int32_t*>(o.host + o.o_w);
+  int64_t* h_off = reinterpret_cast<int64_t*>(o.host + o.o_off);
+  int64_t* h_pp = reinterpret_cast<int64_t*>(o.host + o.o_pp);
+  int64_t cells = 0, pairs = 0, relax = 0;
+  for (int64_t b = 0; b < F; b += kScanThreads) {
+    const int64_t i = b + threadIdx.x;
+    const int32_t wi = i < F ? w[i] : 0;
+    const int64_t slot = i < F ? row_slot(wi) : 0;
+    int64_t total;
+    const int64_t off = cells + block_scan(slot, s_part, &total) + slot - wi;
+    cells += total;
+    const int64_t pp = pairs + block_scan(i < F ? counts[i] : 0, s_part, &total);
+    pairs += total;
+    block_scan(i < F ? walg[i] : 0, s_part, &total);
+    relax += total;
+    if (i < F) {
+      row_off[i] = off;
+      pred_ptr[i] = pp;
+      h_off[i] = off;
+      h_pp[i] = pp;
+      h_size[i] = size[i];
+      h_w[i] = wi;
+    }
+  }
+  if (threadIdx.x == 0) {
+    row_off[F] = cells;
+    pred_ptr[F] = pairs;
+    h_off[F] = cells;
+    h_pp[F] = pairs;
+    st->walg = relax;
+    DevStatus x = *st;
+    x.walg = relax;
+    *reinterpret_cast<DevStatus*>(o.host + o.o_st) = x;
+  }
 }
 
 }  // namespace
@@ -809,33 +1000,39 @@ hipError_t launch_ancestors(rc_graph g, uint64_t* anc, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_pruned_candidates(rc_graph g, const uint64_t* anc, uint64_t* cand,
-                                    hipStream_t s) {
-  hipLaunchKernelGGL(k_pruned_candidates, dim3(32), dim3(256), 0, s, g->n, g->words, anc, cand);
+// Sets of the exact family, grouped by size; stop (host memory, 3 words): the
+// first level not expanded, the number of sets, overflow.  first: level to
+// start from (0, or stop[0] of the call before).
+hipError_t launch_enum_exact(rc_graph g, int32_t first, uint64_t* cand, uint64_t* top, int64_t cap,
+                             int32_t* lvl, int32_t* cnt, DevStatus* st, int32_t* stop,
+                             hipStream_t s) {
+  if (first == 0 && g->words <= kMaxWords / 8 && (int64_t)g->n * g->words <= kEnumMasks) {
+    hipLaunchKernelGGL(k_enum_block, dim3(1), dim3(kEnumThreads), 0, s, g->n, g->words, g->dPred,
+                       cand, top, cap, lvl, cnt, st, stop);
+    return hipGetLastError();
+  }
+  if (first == 0)
+    hipLaunchKernelGGL(k_enum_start, dim3(1), dim3(64), 0, s, g->n, g->words, cand, top, lvl, cnt,
+                       st);
+  for (int lev = first; lev < g->n; lev++)
+    hipLaunchKernelGGL(k_enum_level, dim3(512), dim3(256), 0, s, g->n, g->words, lev, g->dPred,
+                       cand, top, cap, lvl, cnt, st);
+  hipLaunchKernelGGL(k_enum_end, dim3(1), dim3(1), 0, s, g->n, lvl, cnt, st, stop);
   return hipGetLastError();
 }
 
-hipError_t launch_enum_exact(rc_graph g, uint64_t* cand, int64_t cap, int32_t* lvl,
-                             DevStatus* st, hipStream_t s) {
-  hipLaunchKernelGGL(k_enum_start, dim3(1), dim3(64), 0, s, g->words, cand, lvl, st);
-  for (int lev = 0; lev < g->n; lev++) {
-    hipLaunchKernelGGL(k_enum_level, dim3(512), dim3(256), 0, s, g->n, g->words, lev, g->dSucc,
-                       g->dPred, cand, cap, lvl, st);
-    hipLaunchKernelGGL(k_enum_close, dim3(1), dim3(1), 0, s, lev, cap, lvl, st);
-  }
+hipError_t launch_rank_exact(rc_family f, const uint64_t* cand, const int32_t* lvl,
+                             const int32_t* cnt, hipStream_t s) {
+  const int per_block = 256 / kWave;
+  hipLaunchKernelGGL(k_rank, dim3((unsigned)((f->F + per_block - 1) / per_block)), dim3(256), 0, s,
+                     f->g->words, f->F, cand, lvl, cnt, f->bits, f->fstride, f->status);
   return hipGetLastError();
 }
 
-hipError_t launch_rank(rc_graph g, int32_t mode, const uint64_t* cand, int64_t ncand_max,
-                       const int32_t* lvl, uint64_t* bits, int64_t fstride, DevStatus* st,
-                       hipStream_t s) {
-  if (mode == RC_FAMILY_PRUNED) {
-    hipLaunchKernelGGL(k_rank_pruned, dim3(1), dim3(1024), 0, s, g->words, g->n, cand, bits,
-                       fstride, st);
-  } else {
-    hipLaunchKernelGGL(k_rank, dim3((unsigned)((ncand_max + 255) / 256)), dim3(256), 0, s,
-                       g->words, g->n, cand, lvl, bits, fstride, st);
-  }
+hipError_t launch_rank_pruned(rc_family f, hipStream_t s) {
+  rc_graph g = f->g;
+  hipLaunchKernelGGL(k_rank_pruned, dim3(1), dim3(1024), 0, s, g->words, g->n, g->dAnc, f->bits,
+                     f->fstride, f->status);
   return hipGetLastError();
 }
 
@@ -866,40 +1063,41 @@ hipError_t launch_set_quantities(rc_family f, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_row_widths(rc_family f, int64_t* padded, hipStream_t s) {
-  hipLaunchKernelGGL(k_row_widths, dim3((unsigned)((f->F + 255) / 256)), dim3(256), 0, s, f->F,
-                     f->w, padded);
-  return hipGetLastError();
-}
+// 64-bit words of the pair bits of one target; 0: they are not kept.
+int64_t pair_mask_words(rc_family f) { return f->F <= kMaskSets ? (f->F + kWave - 1) / kWave : 0; }
 
-hipError_t launch_row_align(rc_family f, hipStream_t s) {
-  hipLaunchKernelGGL(k_row_align, dim3((unsigned)((f->F + 255) / 256)), dim3(256), 0, s, f->F,
-                     f->w, f->row_off);
-  return hipGetLastError();
-}
-
-hipError_t launch_pair_count(rc_family f, int64_t* counts, hipStream_t s) {
+hipError_t launch_pair_count(rc_family f, int64_t* counts, int64_t* walg, uint64_t* mask,
+                             hipStream_t s) {
   hipLaunchKernelGGL(k_pair_count, dim3((unsigned)f->F), dim3(256), 0, s, f->F, f->g->words,
-                     f->fstride, f->bits, f->size, counts);
+                     f->fstride, f->bits, f->size, f->w, counts, walg, mask, pair_mask_words(f));
   return hipGetLastError();
 }
 
-hipError_t launch_scan(const int64_t* in, int64_t* out, int64_t count, int64_t, hipStream_t s) {
-  hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, in, out, count);
+hipError_t launch_shape(rc_family f, const int64_t* counts, const int64_t* walg, char* host,
+                        const int64_t (&o)[5], hipStream_t s) {
+  hipLaunchKernelGGL(k_shape, dim3(1), dim3(kScanThreads), 0, s, f->F, f->size, f->w, counts, walg,
+                     f->row_off, f->pred_ptr, f->status,
+                     ShapeOut{host, o[0], o[1], o[2], o[3], o[4]});
   return hipGetLastError();
 }
 
-hipError_t launch_pair_write(rc_family f, int64_t* walg_per_target, hipStream_t s) {
+hipError_t launch_scan(const int64_t* in, int64_t* out, int64_t count, hipStream_t s) {
+  hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanThreads), 0, s, in, out, count);
+  return hipGetLastError();
+}
+
+hipError_t launch_pair_write(rc_family f, const uint64_t* mask, hipStream_t s) {
   rc_graph g = f->g;
-  hipLaunchKernelGGL(k_pair_write, dim3((unsigned)f->F), dim3(256), 0, s, f->F, g->words,
-                     f->fstride, f->bits, f->bd, f->size, f->Tsum, f->Msum, f->Tbd, f->Mbd, f->A,
-                     f->w, g->dT, g->dM, f->pred_ptr, f->pidx, f->pdt, f->pdm, f->pc,
-                     walg_per_target);
-  return hipGetLastError();
-}
-
-hipError_t launch_sum(const int64_t* in, int64_t count, int64_t* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_sum, dim3(1), dim3(1024), 0, s, in, count, out);
+  const int64_t mw = pair_mask_words(f);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)f->F), dim3(256), 0, s, f->F, g->words, f->fstride,
+                       f->bits, f->bd, f->size, f->Tsum, f->Msum, f->Tbd, f->Mbd, f->A, g->dT,
+                       g->dM, f->pred_ptr, mask, mw, f->pidx, f->pdt, f->pdm, f->pc);
+  };
+  if (mask)
+    go(k_pair_write<true>);
+  else
+    go(k_pair_write<false>);
   return hipGetLastError();
 }
 

@@ -75,7 +75,7 @@ Staging::Staging(size_t bytes) {
   size_t n = (size_t)64 << 10;
   while (n < bytes) n <<= 1;
   void* p = nullptr;
-  if (hipHostMalloc(&p, n, hipHostMallocDefault) != hipSuccess) return;
+  if (hipHostMalloc(&p, n, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) return;
   p_ = static_cast<char*>(p);
   n_ = n;
 }
@@ -363,12 +363,14 @@ void rc_graph_free(rc_graph g) {
 
 // Which blocks the family's wavefront records use.  RCDP_FILL=wavefront
 // forces the row-push fill's fixed blocks and RCDP_FILL=ghost the ghost-zone
-// blocks (families of at most kGhostMaxSets sets).  Otherwise: fixed blocks
-// for families beyond that size, for families of kWideMinSets sets and more
-// and for tables with rows of 2^16 cells and more (where the split-panel
-// fill measured fastest), ghost-zone blocks for the rest.
-// shape_known: max_row and the levels are set (after the host copies).
-static int32_t family_block_kind(rc_family f, bool shape_known) {
+// blocks (families of at most kGhostMaxSets sets).  Otherwise: fixed blocks,
+// so that the split-panel fill can take the family, for families beyond that
+// size, for rows of 2^16 cells and more and for families of kWideMinSets sets
+// and more (measured faster than the ghost-zone fill on every such shape
+// here, resnet50_t10's 175 sets included: the ghost blocks hold fewer rows,
+// so that each staged window serves fewer targets); ghost-zone blocks for
+// the smaller families.
+static int32_t family_block_kind(rc_family f) {
   const int64_t F = f->F;
   if (F < 2) return 0;
   const char* env = std::getenv("RCDP_FILL");
@@ -376,13 +378,6 @@ static int32_t family_block_kind(rc_family f, bool shape_known) {
       (env && (std::strcmp(env, "wavefront") == 0 || std::strcmp(env, "wide") == 0)))
     return kBlocksFixed;
   if (env && std::strcmp(env, "ghost") == 0) return kBlocksGhost;
-  if (!shape_known) return -1;                 // decided once the table's shape is known
-  // fixed blocks, so that the split-panel fill can take the family, for
-  // rows of 2^16 cells and more and for families of kWideMinSets sets and
-  // more (measured faster than the ghost-zone fill on every such shape
-  // here, resnet50_t10's 175 sets included: the ghost blocks hold fewer
-  // rows, so that each staged window serves fewer targets); ghost-zone
-  // blocks for the smaller families
   return f->max_row >= 65536 || F >= kWideMinSets ? kBlocksFixed : kBlocksGhost;
 }
 
@@ -419,7 +414,7 @@ static int upload_blocks(rc_family f, int64_t* counts, std::unique_ptr<Staging>&
   stage->in_flight();
   if (hipMemcpyAsync(f->bstart, stage->data(), bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
       launch_blk_count(f, f->nblk, counts, s) != hipSuccess ||
-      launch_scan(counts, f->rec_ptr, f->nblk, 1, s) != hipSuccess)
+      launch_scan(counts, f->rec_ptr, f->nblk, s) != hipSuccess)
     return RC_E_DEVICE;
   return RC_OK;
 }
@@ -447,6 +442,18 @@ static int pack_to_host(const PackList& L, void* dev, size_t bytes, Staging& st,
 // (every record holds at least one pair) without waiting for their count.
 constexpr int64_t kRecordBound = (int64_t)1 << 18;
 
+static int sync_landed(Staging& st, hipStream_t s) {
+  if (hipStreamSynchronize(s) != hipSuccess) {
+    set_last_error_msg("stream synchronisation failed");
+    return RC_E_DEVICE;
+  }
+  st.landed();
+  return RC_OK;
+}
+
+static int ensure_records(rc_family f, hipStream_t s);
+static bool level_is_default(rc_family f);
+
 static int build_family_impl(rc_family f, int64_t max_sets, hipStream_t s) {
   rc_graph g = f->g;
   const int n = g->n, words = g->words;
@@ -455,7 +462,6 @@ static int build_family_impl(rc_family f, int64_t max_sets, hipStream_t s) {
   tmp.alloc = A.alloc;
   tmp.free_fn = A.free_fn;
   tmp.user = A.user;
-  std::unique_ptr<Staging> up_stage;  // host -> device block starts
   struct TmpGuard {
     Arena& a;
     hipStream_t s;
@@ -464,51 +470,47 @@ static int build_family_impl(rc_family f, int64_t max_sets, hipStream_t s) {
       a.release_all();
     }
   } guard{tmp, s};
-  // Host -> device and device -> host copies go through pinned buffers; a
-  // build waits for the stream once for the family's size (exact family
-  // only), once for its shape and pair count, once more for the near shifts
-  // of a ghost-zone family, and once at the end.
-  auto sync_landed = [&](Staging& st) -> int {
-    if (hipStreamSynchronize(s) != hipSuccess) {
-      set_last_error_msg("family build: stream synchronisation failed");
-      return RC_E_DEVICE;
-    }
-    st.landed();
-    return RC_OK;
-  };
+  // Kernels write what the host reads into pinned buffers; a build waits for
+  // the stream for the family's size (exact family only, once more for a
+  // level too large for one workgroup), for its shape, and at the end.
 
   f->status = A.get_n<DevStatus>(1);
   if (!f->status) return RC_E_NOMEM;
-  RC_HIP(launch_zero(f->status, sizeof(DevStatus), s));
 
   // ---- a2: the family as bitmasks, in canonical order
   const bool pruned = f->mode == RC_FAMILY_PRUNED;
-  const int64_t cap = pruned ? (int64_t)n + 2 : max_sets;
-  f->fstride = cap;
-  uint64_t* cand = tmp.get_n<uint64_t>(cap * words);
-  int32_t* lvl = tmp.get_n<int32_t>(n + 3);
-  f->bits = A.get_n<uint64_t>(cap * words);
-  if (!cand || !lvl || !f->bits) return RC_E_NOMEM;
-  if (pruned) {
-    RC_HIP(launch_pruned_candidates(g, g->dAnc, cand, s));
-  } else {
-    RC_HIP(launch_enum_exact(g, cand, cap, lvl, f->status, s));
-  }
-  RC_HIP(launch_rank(g, f->mode, cand, cap, lvl, f->bits, f->fstride, f->status, s));
   int64_t F = 0;
   if (pruned) {
     F = pruned_family_size(g);          // checked against the device's count below
+    f->fstride = (int64_t)n + 2;
+    f->bits = A.get_n<uint64_t>(f->fstride * words);
+    if (!f->bits) return RC_E_NOMEM;
+    RC_HIP(launch_rank_pruned(f, s));
   } else {
-    Staging st0(sizeof(DevStatus));
-    if (!st0.data()) return RC_E_NOMEM;
-    st0.in_flight();
-    RC_HIP(hipMemcpyAsync(st0.data(), f->status, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
-    const int ss = sync_landed(st0);
-    if (ss != RC_OK) return ss;
-    const DevStatus& h0 = *st0.at<DevStatus>(0);
-    if (h0.overflow) return RC_E_TOO_MANY_SETS;
-    if (h0.error) return RC_E_DEVICE;
-    F = h0.count;
+    const int64_t cap = max_sets;
+    uint64_t* cand = tmp.get_n<uint64_t>(cap * words);
+    uint64_t* top = tmp.get_n<uint64_t>(cap * words);
+    int32_t* lvl = tmp.get_n<int32_t>(n + 3);
+    int32_t* cnt = tmp.get_n<int32_t>(n + 3);
+    Staging st0(3 * sizeof(int32_t));
+    if (!cand || !top || !lvl || !cnt || !st0.data()) return RC_E_NOMEM;
+    int32_t* stop = st0.at<int32_t>(0);
+    for (int32_t first = 0;;) {
+      st0.in_flight();
+      RC_HIP(launch_enum_exact(g, first, cand, top, cap, lvl, cnt, f->status, stop, s));
+      const int ss = sync_landed(st0, s);
+      if (ss != RC_OK) return ss;
+      if (stop[2]) return RC_E_TOO_MANY_SETS;
+      first = stop[0];
+      if (first >= n) break;
+    }
+    F = stop[1];
+    if (F < 1 || F > max_sets) return RC_E_TOO_MANY_SETS;
+    f->F = F;
+    f->fstride = F;
+    f->bits = A.get_n<uint64_t>(F * words);
+    if (!f->bits) return RC_E_NOMEM;
+    RC_HIP(launch_rank_exact(f, cand, lvl, cnt, s));
   }
   if (F < 1 || F > max_sets) return RC_E_TOO_MANY_SETS;
   f->F = F;
@@ -524,47 +526,36 @@ static int build_family_impl(rc_family f, int64_t max_sets, hipStream_t s) {
   f->bd = A.get_n<uint64_t>(f->fstride * words);
   f->row_off = A.get_n<int64_t>(F + 1);
   f->pred_ptr = A.get_n<int64_t>(F + 1);
-  int64_t* counts = tmp.get_n<int64_t>(F + 1);
-  int64_t* padded = tmp.get_n<int64_t>(F + 1);
-  int64_t* walg_t = tmp.get_n<int64_t>(F + 1);
+  int64_t* counts = tmp.get_n<int64_t>(F);
+  int64_t* walg = tmp.get_n<int64_t>(F);
+  const int64_t mw = pair_mask_words(f);
+  uint64_t* mask = mw > 0 ? tmp.get_n<uint64_t>(F * mw) : nullptr;
   if (!f->size || !f->Tsum || !f->Msum || !f->Tbd || !f->Mbd || !f->A || !f->w || !f->bd ||
-      !f->row_off || !f->pred_ptr || !counts || !padded || !walg_t)
+      !f->row_off || !f->pred_ptr || !counts || !walg || (mw > 0 && !mask))
     return RC_E_NOMEM;
   RC_HIP(launch_set_quantities(f, s));
-  // row offsets: rows padded to kRowAlign cells
-  RC_HIP(launch_row_widths(f, padded, s));
-  RC_HIP(launch_scan(padded, f->row_off, F, 1, s));
-  RC_HIP(launch_row_align(f, s));
-  // ---- a4: predecessor pairs, counted per target
-  RC_HIP(launch_pair_count(f, counts, s));
-  RC_HIP(launch_scan(counts, f->pred_ptr, F, 1, s));
-
-  // ---- the family's shape to the host: sizes, widths, row offsets, pairs
+  // ---- a4: predecessor pairs, counted per target; row and pair offsets
+  RC_HIP(launch_pair_count(f, counts, walg, mask, s));
   StageLayout L1;
   const size_t o_st = L1.add<DevStatus>(1), o_size = L1.add<int32_t>(F),
                o_w = L1.add<int32_t>(F), o_off = L1.add<int64_t>(F + 1),
                o_pp = L1.add<int64_t>(F + 1);
   {
     Staging st1(L1.bytes);
-    void* pk1 = tmp.get(L1.bytes);
-    if (!st1.data() || !pk1) return RC_E_NOMEM;
-    PackList P1;
-    P1.add(f->status, sizeof(DevStatus), (int64_t)o_st);
-    P1.add(f->size, sizeof(int32_t) * F, (int64_t)o_size);
-    P1.add(f->w, sizeof(int32_t) * F, (int64_t)o_w);
-    P1.add(f->row_off, sizeof(int64_t) * (F + 1), (int64_t)o_off);
-    P1.add(f->pred_ptr, sizeof(int64_t) * (F + 1), (int64_t)o_pp);
-    const int pc1 = pack_to_host(P1, pk1, L1.bytes, st1, s);
-    if (pc1 != RC_OK) return pc1;
-    const int ss = sync_landed(st1);
+    if (!st1.data()) return RC_E_NOMEM;
+    const int64_t o[5] = {(int64_t)o_st, (int64_t)o_size, (int64_t)o_w, (int64_t)o_off,
+                          (int64_t)o_pp};
+    st1.in_flight();
+    RC_HIP(launch_shape(f, counts, walg, st1.data(), o, s));
+    const int ss = sync_landed(st1, s);
     if (ss != RC_OK) return ss;
     const DevStatus& h1 = *st1.at<DevStatus>(o_st);
-    if (h1.overflow) return RC_E_TOO_MANY_SETS;
     if (h1.error) return RC_E_DEVICE;
     if (h1.count != F) {
       set_last_error_msg("family build: the device counted another family size");
       return RC_E_DEVICE;
     }
+    f->relax = h1.walg;
     const int32_t* size_h = st1.at<int32_t>(o_size);
     const int32_t* w_h = st1.at<int32_t>(o_w);
     const int64_t* off_h = st1.at<int64_t>(o_off);
@@ -597,61 +588,61 @@ static int build_family_impl(rc_family f, int64_t max_sets, hipStream_t s) {
         most = std::max(most, pp_h[j + 1] - pp_h[j]);
       f->level_pairs.push_back(most);
     }
+    f->block_pairs = 0;
+    for (int64_t j = 1; j < F; j += kJB)
+      f->block_pairs = std::max(f->block_pairs, pp_h[std::min<int64_t>(j + kJB, F)] - pp_h[j]);
   }
 
-  // ---- a4: the pairs themselves and the relaxation count
+  // ---- a4: the pairs themselves
   const int64_t P = f->P;
   f->pidx = A.get_n<int32_t>(P);
   f->pdt = A.get_n<int32_t>(P);
   f->pdm = A.get_n<int32_t>(P);
   f->pc = A.get_n<int32_t>(P);
   if (!f->pidx || !f->pdt || !f->pdm || !f->pc) return RC_E_NOMEM;
-  RC_HIP(launch_pair_write(f, walg_t, s));
-  RC_HIP(launch_sum(walg_t, F, &f->status->walg, s));
+  RC_HIP(launch_pair_write(f, mask, s));
 
-  // ---- blocks of the wavefront fills: kJB targets each for the row-push
-  // fill; for the ghost-zone fill cut on the host from the shifts of near
-  // pairs
-  f->blk_kind = family_block_kind(f, true);
-  if (f->blk_kind == kBlocksGhost) {
-    int32_t* near_d = tmp.get_n<int32_t>(F * kNear);
-    if (!near_d) return RC_E_NOMEM;
-    RC_HIP(launch_near_shifts(f, near_d, s));
-    Staging st2(sizeof(int32_t) * (size_t)(F * kNear));
-    if (!st2.data()) return RC_E_NOMEM;
-    st2.in_flight();
-    RC_HIP(hipMemcpyAsync(st2.data(), near_d, sizeof(int32_t) * (size_t)(F * kNear),
-                          hipMemcpyDeviceToHost, s));
-    const int ss = sync_landed(st2);
-    if (ss != RC_OK) return ss;
-    const int32_t* nh = st2.at<int32_t>(0);
-    cut_blocks(f, std::vector<int32_t>(nh, nh + F * kNear));
-  } else if (f->blk_kind == kBlocksFixed) {
-    cut_blocks(f, std::vector<int32_t>());
+  // ---- the records of the wavefront fills, unless the level launches are
+  // this family's fill or most budgets take 32-bit cells (then the first
+  // solve that needs them builds them)
+  f->blk_kind = family_block_kind(f);
+  if (f->blk_kind != 0 && 2 * g->M_total <= kMaxBudget && !level_is_default(f)) {
+    const int er = ensure_records(f, s);
+    if (er != RC_OK) return er;
   }
-  if (f->blk_kind != 0) {
-    const int ub = upload_blocks(f, counts, up_stage, s);
-    if (ub != RC_OK) return ub;
+  if (hipStreamSynchronize(s) != hipSuccess) {
+    set_last_error_msg("family build: stream synchronisation failed");
+    return RC_E_DEVICE;
   }
+  return RC_OK;
+}
 
-  // ---- panel records: buffers sized from the bound P when it is small,
-  // else from the count (one more wait)
-  f->rec_total = 0;
-  int64_t rec_cap = std::min<int64_t>(P, f->nblk * F);
-  if (f->nblk > 0 && rec_cap > kRecordBound) {
-    Staging st3(sizeof(int64_t));
-    if (!st3.data()) return RC_E_NOMEM;
-    st3.in_flight();
-    RC_HIP(hipMemcpyAsync(st3.data(), f->rec_ptr + f->nblk, sizeof(int64_t),
-                          hipMemcpyDeviceToHost, s));
-    const int ss = sync_landed(st3);
-    if (ss != RC_OK) return ss;
-    rec_cap = *st3.at<int64_t>(0);
-  }
-  const bool records = f->nblk > 0 && rec_cap <= kMaxRecords;
-  if (records) {
+// The block records of the wavefront fills: those of the family's block
+// kind, on first use.  Sets has_records and has_wide (false where the family
+// is too large for them).  Waits for the stream only where the size of a
+// buffer has to be counted: dense records and a bound on the split-panel
+// ones need no count.
+static int ensure_records(rc_family f, hipStream_t s) {
+  if (f->tried_records) return RC_OK;
+  Arena& A = f->arena;
+  Arena tmp;                       // scratch released on return
+  tmp.alloc = A.alloc;
+  tmp.free_fn = A.free_fn;
+  tmp.user = A.user;
+  struct TmpGuard {
+    Arena& a;
+    hipStream_t s;
+    ~TmpGuard() {
+      if (a.ptrs.empty()) return;
+      (void)hipStreamSynchronize(s);
+      a.release_all();
+    }
+  } guard{tmp, s};
+  std::unique_ptr<Staging> up_stage;  // host -> device block starts
+  const int64_t F = f->F, P = f->P;
+  auto records = [&](int64_t Rn) -> int {
     BlockRecords& R = f->rec;
-    const int64_t Rn = rec_cap, T3 = f->nblk * kJB * kJB;
+    const int64_t T3 = f->nblk * kJB * kJB;
     R.src = A.get_n<int32_t>(Rn);
     R.e = A.get_n<int32_t>(Rn * kJB);
     R.kadd = A.get_n<uint32_t>(Rn * kJB);
@@ -659,60 +650,116 @@ static int build_family_impl(rc_family f, int64_t max_sets, hipStream_t s) {
     R.tri_e = A.get_n<int32_t>(T3);
     R.tri_kadd = A.get_n<uint32_t>(T3);
     R.tri_c = A.get_n<int32_t>(T3);
-    if (!R.src || !R.e || !R.kadd || !R.c || !R.tri_e || !R.tri_kadd || !R.tri_c)
-      return RC_E_NOMEM;
-    RC_HIP(launch_blk_fill(f, f->nblk, s));
-    f->clu_ptr = A.get_n<int64_t>(f->nblk + 1);
-    if (!f->clu_ptr) return RC_E_NOMEM;
-    RC_HIP(launch_blk_clusters(f, counts, s));
-    RC_HIP(launch_scan(counts, f->clu_ptr, f->nblk, 1, s));
-  }
-  // the split-panel fill: one record per (block, source, shift), a block's
-  // records sorted in LDS, byte offsets of the table in 31 bits
-  int64_t* wcounts = nullptr;
-  if (records && f->blk_kind == kBlocksFixed) {
+    return R.src && R.e && R.kadd && R.c && R.tri_e && R.tri_kadd && R.tri_c ? RC_OK : RC_E_NOMEM;
+  };
+  auto read_back = [&](const int64_t* dev, int64_t count, Staging& st) -> int {
+    if (!st.data()) return RC_E_NOMEM;
+    st.in_flight();
+    RC_HIP(hipMemcpyAsync(st.data(), dev, sizeof(int64_t) * (size_t)count, hipMemcpyDeviceToHost,
+                          s));
+    return sync_landed(st, s);
+  };
+
+  if (f->blk_kind == kBlocksFixed && dense_records((F - 1 + kJB - 1) / kJB) <= kMaxRecords) {
+    f->nblk = (F - 1 + kJB - 1) / kJB;
+    f->bstart = A.get_n<int32_t>(f->nblk + 1);
+    f->rec_ptr = A.get_n<int64_t>(f->nblk + 1);
     f->wrec_ptr = A.get_n<int64_t>(f->nblk + 1);
-    wcounts = tmp.get_n<int64_t>(f->nblk + 1);
-    if (!f->wrec_ptr || !wcounts) return RC_E_NOMEM;
-    RC_HIP(launch_wide_count(f, wcounts, s));
-    RC_HIP(launch_scan(wcounts, f->wrec_ptr, f->nblk, 1, s));
+    if (!f->bstart || !f->rec_ptr || !f->wrec_ptr) return RC_E_NOMEM;
+    const int ra = records(dense_records(f->nblk));
+    if (ra != RC_OK) return ra;
+    RC_HIP(launch_blk_dense(f, s));
+    f->has_records = true;
+    f->wrec_total = P;
+  } else {
+    std::vector<int32_t> near_h;
+    if (f->blk_kind == kBlocksGhost) {
+      int32_t* near_d = tmp.get_n<int32_t>(F * kNear);
+      Staging st2(sizeof(int32_t) * (size_t)(F * kNear));
+      if (!near_d || !st2.data()) return RC_E_NOMEM;
+      RC_HIP(launch_near_shifts(f, near_d, s));
+      st2.in_flight();
+      RC_HIP(hipMemcpyAsync(st2.data(), near_d, sizeof(int32_t) * (size_t)(F * kNear),
+                            hipMemcpyDeviceToHost, s));
+      const int ss = sync_landed(st2, s);
+      if (ss != RC_OK) return ss;
+      near_h.assign(st2.at<int32_t>(0), st2.at<int32_t>(0) + F * kNear);
+    }
+    cut_blocks(f, near_h);
+    int64_t* counts = tmp.get_n<int64_t>(F + 1);
+    if (!counts) return RC_E_NOMEM;
+    const int ub = upload_blocks(f, counts, up_stage, s);
+    if (ub != RC_OK) return ub;
+    // buffers sized from the bound P when it is small, else from the count
+    int64_t rec_cap = std::min<int64_t>(P, f->nblk * F);
+    if (f->nblk > 0 && rec_cap > kRecordBound) {
+      Staging st3(sizeof(int64_t));
+      const int ss = read_back(f->rec_ptr + f->nblk, 1, st3);
+      if (ss != RC_OK) return ss;
+      rec_cap = *st3.at<int64_t>(0);
+    }
+    f->has_records = f->nblk > 0 && rec_cap <= kMaxRecords;
+    if (f->has_records) {
+      const int ra = records(rec_cap);
+      if (ra != RC_OK) return ra;
+      RC_HIP(launch_blk_fill(f, f->nblk, s));
+    }
   }
 
-  // ---- the counts to the host: status (relaxations, errors), records
-  StageLayout L4;
-  const size_t q_st = L4.add<DevStatus>(1), q_rec = L4.add<int64_t>(1),
-               q_clu = L4.add<int64_t>(1), q_wrec = L4.add<int64_t>(1),
-               q_wc = L4.add<int64_t>(wcounts ? f->nblk : 0);
-  Staging st4(L4.bytes);
-  void* pk4 = tmp.get(L4.bytes);
-  if (!st4.data() || !pk4) return RC_E_NOMEM;
-  PackList P4;
-  P4.add(f->status, sizeof(DevStatus), (int64_t)q_st);
-  if (f->nblk > 0) P4.add(f->rec_ptr + f->nblk, sizeof(int64_t), (int64_t)q_rec);
-  if (records) P4.add(f->clu_ptr + f->nblk, sizeof(int64_t), (int64_t)q_clu);
-  if (wcounts) {
-    P4.add(f->wrec_ptr + f->nblk, sizeof(int64_t), (int64_t)q_wrec);
-    P4.add(wcounts, sizeof(int64_t) * f->nblk, (int64_t)q_wc);
+  // the split-panel fill: one record per (block, source, shift), a block's
+  // records sorted in LDS, byte offsets of the table in 31 bits
+  if (f->has_records && f->blk_kind == kBlocksFixed) {
+    f->has_wide = 2 * f->cells_alloc < INT32_MAX;
+    if (!f->wrec_ptr || f->block_pairs > kWMaxRec || P >= ((int64_t)1 << 26)) {
+      int64_t* wcounts = tmp.get_n<int64_t>(f->nblk + 1);
+      if (!f->wrec_ptr) f->wrec_ptr = A.get_n<int64_t>(f->nblk + 1);
+      if (!f->wrec_ptr || !wcounts) return RC_E_NOMEM;
+      RC_HIP(launch_wide_count(f, wcounts, s));
+      RC_HIP(launch_scan(wcounts, f->wrec_ptr, f->nblk, s));
+      Staging st4(sizeof(int64_t) * (size_t)f->nblk);
+      const int ss = read_back(wcounts, f->nblk, st4);
+      if (ss != RC_OK) return ss;
+      f->wrec_total = 0;
+      for (int64_t b = 0; b < f->nblk; b++) {
+        const int64_t c = st4.at<int64_t>(0)[b];
+        f->wrec_total += c;
+        f->has_wide = f->has_wide && c <= kWMaxRec;
+      }
+      f->has_wide = f->has_wide && f->wrec_total < ((int64_t)1 << 26);
+    }
   }
-  const int pc4 = pack_to_host(P4, pk4, L4.bytes, st4, s);
-  if (pc4 != RC_OK) return pc4;
-  const int ss = sync_landed(st4);
-  if (ss != RC_OK) return ss;
-  if (up_stage) up_stage->landed();
-  const DevStatus& h4 = *st4.at<DevStatus>(q_st);
-  if (h4.error) return RC_E_DEVICE;
-  f->relax = h4.walg;
-  f->rec_total = f->nblk > 0 ? *st4.at<int64_t>(q_rec) : 0;
-  if (f->rec_total > rec_cap) {
-    set_last_error_msg("family build: more panel records than pairs");
+  if (up_stage) {
+    RC_HIP(hipStreamSynchronize(s));
+    up_stage->landed();
+  }
+  f->tried_records = true;
+  return RC_OK;
+}
+
+// The shift clusters of the row-push and ghost-zone fills (clu_ptr and their
+// number, or a bound on it), on first use.
+static int ensure_clusters(rc_family f, hipStream_t s) {
+  if (f->clu_ptr) return RC_OK;
+  int64_t* counts = f->arena.get_n<int64_t>(f->nblk);
+  int64_t* ptr = f->arena.get_n<int64_t>(f->nblk + 1);
+  if (!counts || !ptr) return RC_E_NOMEM;
+  f->clu_ptr = ptr;
+  if (launch_blk_clusters(f, counts, s) != hipSuccess ||
+      launch_scan(counts, ptr, f->nblk, s) != hipSuccess) {
+    f->clu_ptr = nullptr;
     return RC_E_DEVICE;
   }
-  f->has_records = records;
-  f->clu_total = records ? *st4.at<int64_t>(q_clu) : 0;
-  f->wrec_total = wcounts ? *st4.at<int64_t>(q_wrec) : 0;
-  f->has_wide = wcounts && 2 * f->cells_alloc < INT32_MAX && f->wrec_total < ((int64_t)1 << 26);
-  for (int64_t b = 0; wcounts && b < f->nblk; b++)
-    f->has_wide = f->has_wide && st4.at<int64_t>(q_wc)[b] <= kWMaxRec;
+  f->clu_total = f->P;                   // every cluster holds a pair
+  if (f->P > (int64_t)1 << 14) {
+    Staging st(sizeof(int64_t));
+    const int e = st.data() ? RC_OK : RC_E_NOMEM;
+    if (e != RC_OK) return e;
+    st.in_flight();
+    RC_HIP(hipMemcpyAsync(st.data(), ptr + f->nblk, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    const int ss = sync_landed(st, s);
+    if (ss != RC_OK) return ss;
+    f->clu_total = *st.at<int64_t>(0);
+  }
   return RC_OK;
 }
 
@@ -834,9 +881,6 @@ void rc_family_free(rc_family f) {
 
 // ------------------------------------------------------------------ solve
 
-// Level launches suit narrow tables (few columns, many targets per level);
-// the persistent wavefront suits wide ones.  RCDP_FILL=level|wavefront
-// overrides the choice.
 static void destroy_events(rc_solution sol) {
   for (hipEvent_t* e : {&sol->ev0, &sol->ev1, &sol->evk0, &sol->evk1})
     if (*e) {
@@ -845,37 +889,62 @@ static void destroy_events(rc_solution sol) {
     }
 }
 
-static int choose_fill_path(rc_family f) {
-  if (!f->has_records || f->F < 2) return 0;
+// The level launches against the family's wavefront, by their measured costs
+// on this GPU.  The wavefront runs its 256-cell columns at most three (the
+// split-panel fill: four) per compute unit at a time, each through every row
+// of the table at about 2.5 us per row.  A level launch costs about 4 us,
+// plus the source reads of its pairs (2 bytes per relaxation) at about
+// 6 TB/s, partly beside each other.  Few levels of many sets or of very long
+// rows take the level launches (ms, level against wavefront: ladder40
+// 0.17 / 0.49, layered36 1.7, U-Net 0.44 / 1.05), many levels the wavefront
+// (ResNet-50 0.85 / 0.61).
+static bool level_is_cheaper(rc_family f) {
+  const int64_t levels = (int64_t)f->level_ptr.size() - 1;
+  const int64_t slots = (f->blk_kind == kBlocksGhost ? 3 : wide_slots_per_cu(3)) *
+                        (int64_t)num_cus();
+  const int64_t col_rounds = ((f->max_row + kWC - 1) / kWC + slots - 1) / slots;
+  const double wave_us = 2.5 * (double)f->F * (double)col_rounds;
+  const double level_us = 4.0 * (double)levels + 2.0 * (double)f->relax / 6.0e6;
+  return level_us < wave_us;
+}
+
+static bool forces_wavefront(const char* env) {
+  return env && (std::strcmp(env, "wavefront") == 0 || std::strcmp(env, "wide") == 0 ||
+                 std::strcmp(env, "ghost") == 0);
+}
+
+static bool level_is_default(rc_family f) {
+  const char* env = std::getenv("RCDP_FILL");
+  if (env && std::strcmp(env, "level") == 0) return true;
+  return !forces_wavefront(env) && level_is_cheaper(f);
+}
+
+// The fill of a solve (rc_solution_fill_path's numbers), with the records it
+// reads built.
+static int choose_fill_path(rc_family f, hipStream_t s, int32_t* path) {
+  *path = 0;
+  if (f->blk_kind == 0 || level_is_default(f)) return RC_OK;
+  const int er = ensure_records(f, s);
+  if (er != RC_OK) return er;
+  if (!f->has_records) return RC_OK;
   // the family's wavefront fill: ghost-zone blocks, or fixed blocks of kJB
   // with the split-panel fill when it can take the family
   const int wave = f->blk_kind == kBlocksGhost ? 2 : (f->has_wide ? 3 : 1);
   const char* env = std::getenv("RCDP_FILL");
-  if (env && std::strcmp(env, "level") == 0) return 0;
-  if (env && std::strcmp(env, "wavefront") == 0 && f->blk_kind == kBlocksFixed) return 1;
-  if (env && (std::strcmp(env, "wide") == 0 || std::strcmp(env, "ghost") == 0)) return wave;
-  if (wave == 1) return 0;
-  // The wavefront against the level launches, by their measured costs on
-  // this GPU.  The wavefront runs its 256-cell columns at most three (the
-  // split-panel fill: four) per compute unit at a time, each through every
-  // row of the table at about 2.5 us per row.  A level launch costs about
-  // 4 us, plus the source reads of its pairs (2 bytes per relaxation) at
-  // about 6 TB/s, partly beside each other.  Few levels of many sets or of
-  // very long rows take the level launches (ms, level against wavefront:
-  // ladder40 0.17 / 0.49, layered36 1.7, U-Net 0.44 / 1.05), many levels the
-  // wavefront (ResNet-50 0.85 / 0.61).
-  const int64_t levels = (int64_t)f->level_ptr.size() - 1;
-  const int64_t slots = (wave == 3 ? wide_slots_per_cu(3) : 3) * (int64_t)num_cus();
-  const int64_t col_rounds = ((f->max_row + kWC - 1) / kWC + slots - 1) / slots;
-  const double wave_us = 2.5 * (double)f->F * (double)col_rounds;
-  const double level_us = 4.0 * (double)levels + 2.0 * (double)f->relax / 6.0e6;
-  return level_us < wave_us ? 0 : wave;
+  if (env && std::strcmp(env, "wavefront") == 0 && f->blk_kind == kBlocksFixed)
+    *path = 1;
+  else if (env && (std::strcmp(env, "wide") == 0 || std::strcmp(env, "ghost") == 0))
+    *path = wave;
+  else
+    *path = wave == 1 || level_is_cheaper(f) ? 0 : wave;
+  return *path == 1 || *path == 2 ? ensure_clusters(f, s) : RC_OK;
 }
 
 }  // extern "C"
 
 // A solution handle with its buffers and events; nothing enqueued yet.
-static int new_solution(rc_family f, int64_t B, int32_t objective, rc_solution* out) {
+static int new_solution(rc_family f, int64_t B, int32_t objective, hipStream_t s,
+                        rc_solution* out) {
   if (!f || B < 0) return RC_E_ARG;
   if (objective != RC_TIME_CENTRIC && objective != RC_MEMORY_CENTRIC) return RC_E_ARG;
   const int64_t Beff = std::min<int64_t>(B, 2 * f->g->M_total);
@@ -910,7 +979,10 @@ static int new_solution(rc_family f, int64_t B, int32_t objective, rc_solution* 
     return fail(RC_E_NOMEM);
   if (hipEventCreate(&sol->ev0) != hipSuccess || hipEventCreate(&sol->ev1) != hipSuccess)
     return fail(RC_E_DEVICE);
-  sol->fill_path = cell32 ? 0 : choose_fill_path(f);
+  if (!cell32) {
+    const int cp = choose_fill_path(f, s, &sol->fill_path);
+    if (cp != RC_OK) return fail(cp);
+  }
   if (sol->fill_path != 0 &&
       (hipEventCreate(&sol->evk0) != hipSuccess || hipEventCreate(&sol->evk1) != hipSuccess))
     return fail(RC_E_DEVICE);
@@ -989,7 +1061,7 @@ static int solve_one(rc_family f, int64_t B, int32_t objective, void* stream, rc
   if (!f || !out) return RC_E_ARG;
   hipStream_t s = as_stream(stream);
   rc_solution sol = nullptr;
-  const int st0 = new_solution(f, B, objective, &sol);
+  const int st0 = new_solution(f, B, objective, s, &sol);
   if (st0 != RC_OK) return st0;
   if (dominance && sol->cell32) {      // the weak-front kernels take 16-bit cells only
     drop_solution(sol);
@@ -1060,7 +1132,7 @@ int rc_solve_batch(rc_family f, const int64_t* B_host, int32_t nb, int32_t objec
   };
   for (int32_t b = 0; b < nb; b++) {
     rc_solution x = nullptr;
-    const int st = new_solution(f, B_host[b], objective, &x);
+    const int st = new_solution(f, B_host[b], objective, s, &x);
     if (st != RC_OK) return fail(st);
     sols.push_back(x);
   }

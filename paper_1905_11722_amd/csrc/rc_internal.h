@@ -69,6 +69,10 @@ __host__ __device__ inline int64_t row_slot(int64_t w) {
   return (w + kRowAlign - 1) / kRowAlign * kRowAlign + kGuard;
 }
 
+// Records before block b when every block of kJB targets has one for each
+// source before it (block b: 1 + kJB b of them).
+__host__ __device__ inline int64_t dense_records(int64_t b) { return b + kJB / 2 * b * (b - 1); }
+
 // Device allocator with ownership tracking.
 struct Arena {
   rc_alloc_fn alloc = nullptr;
@@ -168,11 +172,11 @@ struct rc_family_s {
   int64_t nblk = 0;
   int32_t* bstart = nullptr;      // [nblk+1] first target of each block
   std::vector<int32_t> bstart_host;
-  int64_t rec_total = 0;
+  bool tried_records = false;     // ensure_records has run (its results below)
   bool has_records = false;
   int64_t* rec_ptr = nullptr;     // [nblk+1]
   int64_t* clu_ptr = nullptr;     // [nblk+1] compact records (shift clusters) per block
-  int64_t clu_total = 0;
+  int64_t clu_total = 0;          // ... of all blocks, or a bound on them
   int64_t* wrec_ptr = nullptr;    // [nblk+1] split-panel records per block (upper bound)
   int64_t wrec_total = 0;
   bool has_wide = false;          // the split-panel fill can take this family
@@ -182,6 +186,7 @@ struct rc_family_s {
   // host copies used for launches
   std::vector<int64_t> level_ptr; // family index ranges of equal set size
   std::vector<int64_t> level_pairs; // the most pairs of a target in each level
+  int64_t block_pairs = 0;        // the most pairs of the targets of a fixed block
   std::vector<int32_t> level_maxw;
   std::vector<int32_t> w_host;
   std::vector<int64_t> row_off_host;
@@ -308,20 +313,20 @@ hipError_t launch_graph_masks(rc_graph g, const int32_t* d_row_ptr, const int32_
 
 // ---- family kernels (family.hip)
 hipError_t launch_ancestors(rc_graph g, uint64_t* anc, hipStream_t s);
-hipError_t launch_pruned_candidates(rc_graph g, const uint64_t* anc, uint64_t* cand,
-                                    hipStream_t s);
-hipError_t launch_enum_exact(rc_graph g, uint64_t* cand, int64_t cap, int32_t* lvl,
-                             DevStatus* st, hipStream_t s);
-hipError_t launch_rank(rc_graph g, int32_t mode, const uint64_t* cand, int64_t ncand_max,
-                       const int32_t* lvl, uint64_t* bits, int64_t fstride, DevStatus* st,
-                       hipStream_t s);
+hipError_t launch_enum_exact(rc_graph g, int32_t first, uint64_t* cand, uint64_t* top, int64_t cap,
+                             int32_t* lvl, int32_t* cnt, DevStatus* st, int32_t* stop,
+                             hipStream_t s);
+hipError_t launch_rank_exact(rc_family f, const uint64_t* cand, const int32_t* lvl,
+                             const int32_t* cnt, hipStream_t s);
+hipError_t launch_rank_pruned(rc_family f, hipStream_t s);
 hipError_t launch_set_quantities(rc_family f, hipStream_t s);
-hipError_t launch_pair_count(rc_family f, int64_t* counts, hipStream_t s);
-hipError_t launch_scan(const int64_t* in, int64_t* out, int64_t count, int64_t align,
-                       hipStream_t s);
-hipError_t launch_pair_write(rc_family f, int64_t* walg_per_target, hipStream_t s);
-hipError_t launch_row_widths(rc_family f, int64_t* padded, hipStream_t s);
-hipError_t launch_sum(const int64_t* in, int64_t count, int64_t* out, hipStream_t s);
+int64_t pair_mask_words(rc_family f);
+hipError_t launch_pair_count(rc_family f, int64_t* counts, int64_t* walg, uint64_t* mask,
+                             hipStream_t s);
+hipError_t launch_shape(rc_family f, const int64_t* counts, const int64_t* walg, char* host,
+                        const int64_t (&o)[5], hipStream_t s);
+hipError_t launch_scan(const int64_t* in, int64_t* out, int64_t count, hipStream_t s);
+hipError_t launch_pair_write(rc_family f, const uint64_t* mask, hipStream_t s);
 
 // ---- DP kernels (fill.hip)
 hipError_t launch_solve_init(rc_solution sol, hipStream_t s);
@@ -334,7 +339,7 @@ hipError_t launch_arg_all(rc_solution sol, hipStream_t s);
 hipError_t launch_fronts(rc_solution sol, hipStream_t s);
 
 // ---- blocked fill (blocks.hip, blocked.hip)
-hipError_t launch_row_align(rc_family f, hipStream_t s);
+hipError_t launch_blk_dense(rc_family f, hipStream_t s);
 hipError_t launch_blk_count(rc_family f, int64_t nblk, int64_t* count, hipStream_t s);
 hipError_t launch_blk_fill(rc_family f, int64_t nblk, hipStream_t s);
 hipError_t launch_blk_clusters(rc_family f, int64_t* count, hipStream_t s);

@@ -84,3 +84,42 @@ def test_level_fill_wide_levels(rc, oracle_mod, monkeypatch, seed, scale):
     g.M = [m * scale for m in g.M]
     for share in (1.2, 1.6, 2.0):
         compare(rc, oracle_mod, g, "exact", int(share * sum(g.M)))
+
+
+@pytest.mark.parametrize("graph", [W.chain(63), W.chain(64), W.chain(65), W.chain(130),
+                                   W.chain(440), W.antichain(10), W.antichain(11),
+                                   W.ladder(24)],
+                         ids=["chain63", "chain64", "chain65", "chain130", "chain440",
+                              "antichain10", "antichain11", "ladder24"])
+def test_exact_enumeration(rc, oracle_mod, graph):
+    """The exact family where it ends in one workgroup, where a level (462 or
+    fewer sets, several words each) or the graph is too large for that, and
+    at caps that just hold it and just do not."""
+    ref = oracle_mod.family(graph, "exact")
+    g = rc.Graph.create(graph)
+    fam = g.build_family("exact", max_sets=ref.num_sets)
+    assert fam.info["num_sets"] == ref.num_sets
+    assert (fam.sets() == ref.sets()).all()
+    for cap in (1, ref.num_sets - 1):
+        with pytest.raises(rc.RcError) as err:
+            g.build_family("exact", max_sets=cap)
+        assert err.value.status == rc.E_TOO_MANY_SETS
+
+
+@pytest.mark.parametrize("name", ["chain16", "ladder40", "resnet50_t10"])
+def test_fill_switched_after_the_build(rc, oracle_mod, monkeypatch, name):
+    """Records that the family's own fill does not need are built by the
+    first solve that does; every fill then gives the same table."""
+    c = W.case(name)
+    fam = rc.Graph.create(c.graph).build_family(c.mode)
+    ref = oracle_mod.solve(c.graph, c.mode, c.B, "tc").table()
+    for path in ("wide", "wavefront", "ghost", "level", None):
+        if path:
+            monkeypatch.setenv("RCDP_FILL", path)
+        else:
+            monkeypatch.delenv("RCDP_FILL")
+        for _ in range(2):
+            sol = fam.solve(c.B, "tc")
+            for got, want in zip(sol.table(), ref):
+                assert (got == want).all(), path
+            sol.free()
