@@ -654,9 +654,7 @@ hipError_t prepare_table(rc_solution sol, int32_t C, int32_t K, int32_t* ticket,
   rc_family f = sol->f;
   hipLaunchKernelGGL(k_blocked_init, dim3((K + 255) / 256), dim3(256), 0, s, sol->progress, K,
                      ticket);
-  hipError_t pe = launch_fill_pending(sol, s);
-  if (pe == hipSuccess) pe = launch_pad_init(sol, s);
-  if (pe == hipSuccess) pe = launch_rec_prepare(sol, s);
+  hipError_t pe = launch_rec_prepare(sol, s);
   if (pe == hipSuccess) pe = launch_rec_sort(sol, C, 0, s);
   if (pe == hipSuccess) pe = launch_push_prepare(sol, C, s);
   if (pe != hipSuccess) return pe;

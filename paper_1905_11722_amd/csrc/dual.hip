@@ -91,8 +91,10 @@ __global__ __launch_bounds__(kDualThreads) void k_dual_level(
 }
 
 // t of the objective over row V and the least m that attains it.
+// host (pinned; null: none) receives the status.
 __global__ __launch_bounds__(kDualThreads) void k_dual_select(const uint32_t* __restrict__ row,
-                                                              int32_t W, int tc, DevStatus* st) {
+                                                              int32_t W, int tc, DevStatus* st,
+                                                              DevStatus* host) {
   __shared__ unsigned long long s_best;             // TC: t; MC: t + 1 (0: none)
   __shared__ int32_t s_m;
   if (threadIdx.x == 0) {
@@ -121,10 +123,12 @@ __global__ __launch_bounds__(kDualThreads) void k_dual_select(const uint32_t* __
       }
   }
   __syncthreads();
-  if (threadIdx.x == 0 && found) {
-    st->t_sel = (int32_t)(tc ? s_best : s_best - 1);
-    st->m_sel = s_m;
-  }
+  if (threadIdx.x != 0) return;
+  DevStatus r = *st;
+  r.t_sel = found ? (int32_t)(tc ? s_best : s_best - 1) : -1;
+  r.m_sel = found ? s_m : -1;
+  *st = r;
+  if (host) *host = r;
 }
 
 // Traceback through the table (Section 4.2's, read on cells (L, m)): from
@@ -144,8 +148,8 @@ __global__ __launch_bounds__(kDualTraceThreads) void k_dual_trace(
     const int32_t* __restrict__ M, const int64_t* __restrict__ pred_ptr,
     const int32_t* __restrict__ pidx, const int32_t* __restrict__ pdt,
     const int32_t* __restrict__ pdm, const int32_t* __restrict__ pc, int32_t B, int32_t W,
-    const uint32_t* __restrict__ D, int64_t T_total, DevStatus* st, int32_t* chain, int32_t* seg,
-    uint8_t* cached) {
+    const uint32_t* __restrict__ D, int64_t T_total, DevStatus* st, int32_t* chain,
+    ScheduleOut out) {
   constexpr int kWaves = kDualTraceThreads / 64;
   __shared__ int32_t s_first[2][kWaves];
   __shared__ int32_t s_src[2][kDualTraceThreads];
@@ -206,39 +210,30 @@ __global__ __launch_bounds__(kDualTraceThreads) void k_dual_trace(
   }
   if (t != 0 || m != 0) bad = true;                  // the walk must end at (empty set, 0, 0)
   __syncthreads();
-  if (bad) {
-    if (tid == 0) {
-      st->error = 2;
-      st->k = -1;
-    }
-    return;
-  }
-  finish_schedule<kDualTraceThreads>(k, n, words, fstride, bits, bd, A, T, M, T_total, st, chain,
-                                     seg, cached, s_chain, s_M);
+  finish_schedule<kDualTraceThreads>(bad ? -1 : k, n, words, fstride, bits, bd, A, T, M, T_total, chain, out,
+                      s_chain, s_M);
 }
 
 }  // namespace
 
 hipError_t launch_dual_trace(rc_family f, int32_t B, int32_t W, int objective, const uint32_t* D,
-                             DevStatus* st, int32_t* chain, int32_t* seg, uint8_t* cached,
+                             DevStatus* st, int32_t* chain, const ScheduleOut& out,
                              hipStream_t s) {
   rc_graph g = f->g;
   if (objective == RC_TIME_CENTRIC)
     hipLaunchKernelGGL(k_dual_trace<true>, dim3(1), dim3(kDualTraceThreads), 0, s, f->F, g->n,
                        g->words, f->fstride, f->bits, f->bd, f->A, g->dT, g->dM, f->pred_ptr,
-                       f->pidx, f->pdt, f->pdm, f->pc, B, W, D, g->T_total, st, chain, seg,
-                       cached);
+                       f->pidx, f->pdt, f->pdm, f->pc, B, W, D, g->T_total, st, chain, out);
   else
     hipLaunchKernelGGL(k_dual_trace<false>, dim3(1), dim3(kDualTraceThreads), 0, s, f->F, g->n,
                        g->words, f->fstride, f->bits, f->bd, f->A, g->dT, g->dM, f->pred_ptr,
-                       f->pidx, f->pdt, f->pdm, f->pc, B, W, D, g->T_total, st, chain, seg,
-                       cached);
+                       f->pidx, f->pdt, f->pdm, f->pc, B, W, D, g->T_total, st, chain, out);
   return hipGetLastError();
 }
 
 hipError_t launch_dual(rc_family f, const std::vector<int64_t>& level_pairs, int32_t B, int32_t W,
-                       int objective, uint32_t* D, DevStatus* st, hipEvent_t e0, hipEvent_t e1,
-                       hipStream_t s) {
+                       int objective, uint32_t* D, DevStatus* st, DevStatus* host, hipEvent_t e0,
+                       hipEvent_t e1, hipStream_t s) {
   const int64_t cells = f->F * (int64_t)W;
   const unsigned grid0 = (unsigned)std::min<int64_t>((cells + 255) / 256, 4096);
   const bool tc = objective == RC_TIME_CENTRIC;
@@ -261,7 +256,7 @@ hipError_t launch_dual(rc_family f, const std::vector<int64_t>& level_pairs, int
   }
   if (e1 && hipEventRecord(e1, s) != hipSuccess) return hipErrorUnknown;
   hipLaunchKernelGGL(k_dual_select, dim3(1), dim3(kDualThreads), 0, s,
-                     D + (f->F - 1) * (int64_t)W, W, tc ? 1 : 0, st);
+                     D + (f->F - 1) * (int64_t)W, W, tc ? 1 : 0, st, host);
   return hipGetLastError();
 }
 

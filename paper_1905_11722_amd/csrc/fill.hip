@@ -60,23 +60,69 @@ __device__ __forceinline__ int64_t word_cost(uint64_t bits, int word, const int3
   return s;
 }
 
+// Tables of one launch (z, or y of the selection).
+constexpr int kTables = 64;
+struct InitTables {
+  void* m[kTables];
+  DevStatus* st[kTables];
+  uint16_t* sentinel[kTables];
+};
+struct SelectTables {
+  const void* m[kTables];
+  DevStatus* st[kTables];
+  DevStatus* host;
+};
+
 // opt[empty, 0] = 0 (Algorithm 1's initial condition), the selection state,
-// and infinity in the padding: the cells of every row's slot before the row
-// (at least kGuard) and the kGuard cells after the last row, so that a
-// window that overlaps a row reads infinity outside it.  A workgroup per row.
+// infinity in the padding (the cells of every row's slot before the row, at
+// least kGuard, the kGuard cells after the last row and an 8-cell sentinel,
+// so that a window that overlaps a row reads infinity outside it) and, with
+// pend, kPendM ("not written yet") in every cell after row 0.  Block (x, y):
+// kInitChunk cells of row lb + y's slot, 16 bytes per store.
+constexpr int kInitChunk = 16384;
+
 template <class T>
-__global__ __launch_bounds__(kFillThreads) void k_solve_init(T* m, int64_t F,
+__global__ __launch_bounds__(kFillThreads) void k_solve_init(InitTables tabs, int64_t lb,
+                                                             int64_t F,
                                                              const int32_t* __restrict__ w,
                                                              const int64_t* __restrict__ row_off,
                                                              int64_t cells, int objective,
-                                                             DevStatus* st) {
-  for (int64_t s = blockIdx.x; s <= F; s += gridDim.x) {
-    const int64_t start = s < F ? row_off[s] + w[s] - row_slot(w[s]) : cells;
-    const int64_t end = s < F ? row_off[s] : cells + kGuard;
-    for (int64_t x = start + threadIdx.x; x < end; x += blockDim.x) m[x] = (T)cell_inf<T>();
+                                                             int pend) {
+  constexpr int kVec = 16 / (int)sizeof(T);
+  T* const m = static_cast<T*>(tabs.m[blockIdx.z]);
+  const int64_t s = lb + blockIdx.y;
+  const int32_t ws = w[s];
+  const int64_t off = row_off[s];
+  const int64_t slot = row_slot(ws);
+  const int64_t pad = slot - ws;                    // padding cells of the slot
+  const int64_t end = pend && s > 0 ? slot : pad;   // cells of the slot to write
+  T* const p = m + off - pad;                       // 128-byte aligned
+  for (int64_t x = (int64_t)blockIdx.x * kInitChunk + kVec * threadIdx.x;
+       x < min(end, ((int64_t)blockIdx.x + 1) * kInitChunk); x += kVec * kFillThreads) {
+    union {
+      uint4 q;
+      T c[kVec];
+    } v;
+#pragma unroll
+    for (int k = 0; k < kVec; k++) v.c[k] = x + k < pad ? (T)cell_inf<T>() : (T)kPendM;
+    if (x + kVec <= end) {
+      *reinterpret_cast<uint4*>(p + x) = v.q;
+    } else {
+#pragma unroll
+      for (int k = 0; k < kVec; k++)
+        if (x + k < end) p[x + k] = v.c[k];
+    }
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    m[row_off[0]] = 0;
+  if (blockIdx.x != 0) return;
+  if (s == F - 1)
+    for (int64_t x = cells + threadIdx.x; x < cells + kGuard; x += kFillThreads)
+      m[x] = (T)cell_inf<T>();
+  if (s != 0) return;
+  if (threadIdx.x < 8 && tabs.sentinel[blockIdx.z])
+    tabs.sentinel[blockIdx.z][threadIdx.x] = (uint16_t)kInfM;
+  if (threadIdx.x == 0) {
+    DevStatus* const st = tabs.st[blockIdx.z];
+    m[off] = 0;
     st->error = 0;
     st->t_sel = objective == RC_TIME_CENTRIC ? INT32_MAX : -1;
     st->m_sel = -1;
@@ -460,7 +506,8 @@ __global__ __launch_bounds__(kFillThreads) void k_arg_all(
 // t* = min (time-centric) or max (memory-centric) finite t of row V, and
 // opt[V, t*].  A lane reads 16 bytes of the row at a time, counted from the
 // row's end (aligned to kRowAlign cells); a workgroup reduces to one atomic,
-// and the last workgroup to finish (st->done) reads the result back.  Bound
+// and the last workgroup to finish (st->done) reads the result back and
+// writes the status to the host's pinned buffer.  Table y of tabs.  Bound
 // by its loads in flight: U-Net's 2.4 M cells take 10 us (13 with 512
 // workgroups, whose atomics meet on one address), against 48 us with one
 // cell per load and 64 workgroups and 5 more in a second launch.
@@ -468,10 +515,12 @@ constexpr int kSelectThreads = 256;
 constexpr int kSelectBlocks = 128;
 
 template <class T>
-__global__ __launch_bounds__(kSelectThreads) void k_select(const T* m, const int64_t* row_off,
-                                                          int64_t v, const int32_t* w,
-                                                          int objective, DevStatus* st) {
+__global__ __launch_bounds__(kSelectThreads) void k_select(SelectTables tabs,
+                                                          const int64_t* row_off, int64_t v,
+                                                          const int32_t* w, int objective) {
   constexpr int kVec = 16 / (int)sizeof(T);
+  const T* const m = static_cast<const T*>(tabs.m[blockIdx.y]);
+  DevStatus* const st = tabs.st[blockIdx.y];
   __shared__ int32_t s_best[kSelectThreads / kWave];
   const int64_t off = row_off[v];
   const int32_t wv = w[v];
@@ -511,8 +560,12 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(const T* m, const int
   __threadfence();
   int32_t t = __hip_atomic_load(&st->t_sel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (t == INT32_MAX) t = -1;
-  st->t_sel = t;
-  st->m_sel = t >= 0 ? (int32_t)m[off + t] : -1;
+  DevStatus r = *st;
+  r.t_sel = t;
+  r.m_sel = t >= 0 ? (int32_t)m[off + t] : -1;
+  st->t_sel = r.t_sel;
+  st->m_sel = r.m_sel;
+  tabs.host[blockIdx.y] = r;
 }
 
 // Traceback from (V, t*) (Section 4.2), then Eq. 1 and Eq. 2 of the chain
@@ -533,8 +586,8 @@ __global__ __launch_bounds__(kTraceThreads) void k_trace(
     const int64_t* __restrict__ row_off, const int64_t* __restrict__ pred_ptr,
     const int32_t* __restrict__ pidx, const int32_t* __restrict__ pdt,
     const int32_t* __restrict__ pdm, const int32_t* __restrict__ pc, int32_t Beff,
-    const Cell* __restrict__ m, int64_t T_total, DevStatus* st, int32_t* chain, int32_t* seg,
-    uint8_t* cached) {
+    const Cell* __restrict__ m, int64_t T_total, DevStatus* st, int32_t* chain,
+    ScheduleOut out) {
   // per-set arrays of small families live in LDS for the whole walk
   __shared__ int32_t s_w[kTraceLds];
   __shared__ int64_t s_off[kTraceLds];
@@ -624,15 +677,8 @@ __global__ __launch_bounds__(kTraceThreads) void k_trace(
   }
   if (t != 0) bad = true;                            // the walk must end at (empty, 0)
   __syncthreads();
-  if (bad) {
-    if (tid == 0) {
-      st->error = 2;
-      st->k = -1;
-    }
-    return;
-  }
-  finish_schedule<kTraceThreads>(k, n, words, fstride, bits, bd, A, T, M, T_total, st, chain, seg,
-                                  cached, s_chain, s_M);
+  finish_schedule<kTraceThreads>(bad ? -1 : k, n, words, fstride, bits, bd, A, T, M, T_total, chain, out,
+                      s_chain, s_M);
 }
 
 // The traceback through an optarg slice.  When t* is small, every step of
@@ -772,7 +818,8 @@ __global__ __launch_bounds__(kTraceThreads) void k_trace_follow(
     int64_t F, int n, int words, int64_t fstride, const uint64_t* __restrict__ bits,
     const uint64_t* __restrict__ bd, const int32_t* __restrict__ A, const int32_t* __restrict__ T,
     const int32_t* __restrict__ M, int32_t S, const uint32_t* __restrict__ nxt, int64_t T_total,
-    DevStatus* st, int32_t* chain, int32_t* seg, uint8_t* cached) {
+    DevStatus* st, int32_t* chain,
+    ScheduleOut out) {
   __shared__ int32_t s_chain[kMaxNodes + 1];
   __shared__ int32_t s_M[kMaxNodes];
   __shared__ int32_t s_k;
@@ -818,29 +865,74 @@ __global__ __launch_bounds__(kTraceThreads) void k_trace_follow(
     s_k = bad ? -1 : k;
   }
   __syncthreads();
-  const int32_t k = s_k;
-  if (k < 0) {
-    if (tid == 0) {
-      st->error = 2;
-      st->k = -1;
-    }
-    return;
-  }
-  finish_schedule<kTraceThreads>(k, n, words, fstride, bits, bd, A, T, M, T_total, st, chain, seg,
-                                  cached, s_chain, s_M);
+  finish_schedule<kTraceThreads>(s_k, n, words, fstride, bits, bd, A, T, M, T_total, chain, out, s_chain,
+                      s_M);
 }
 
 }  // namespace
 
-hipError_t launch_solve_init(rc_solution sol, hipStream_t s) {
-  rc_family f = sol->f;
-  const dim3 grid((unsigned)std::min<int64_t>(f->F + 1, 4096));
-  if (sol->cell32)
-    hipLaunchKernelGGL(k_solve_init<uint32_t>, grid, dim3(kFillThreads), 0, s, sol->m32, f->F,
-                       f->w, f->row_off, f->cells, sol->objective, sol->status);
-  else
-    hipLaunchKernelGGL(k_solve_init<uint16_t>, grid, dim3(kFillThreads), 0, s, sol->m, f->F, f->w,
-                       f->row_off, f->cells, sol->objective, sol->status);
+// Launches over all rows, `per` cells of a row to a workgroup, as
+// launch(first row, grid): one launch for consecutive levels while their
+// longest row leaves at most half of the grid's workgroups without cells.
+template <class Launch>
+static void for_row_groups(rc_family f, int64_t per, Launch launch) {
+  const int64_t L = (int64_t)f->level_ptr.size() - 1;
+  for (int64_t l = 0; l < L;) {
+    const int64_t first = f->level_ptr[l];
+    int64_t most = 0, used = 0, end = l;
+    for (; end < L; end++) {
+      const int64_t tiles = (f->level_maxw[end] + per - 1) / per;
+      const int64_t rows = f->level_ptr[end + 1] - first;
+      const int64_t now = used + tiles * (f->level_ptr[end + 1] - f->level_ptr[end]);
+      const int64_t wide = std::max(most, tiles);
+      if (end > l && wide * rows > 2 * now + 65536) break;
+      most = wide;
+      used = now;
+    }
+    launch(first, dim3((unsigned)most, (unsigned)(f->level_ptr[end] - first)));
+    l = end;
+  }
+}
+
+// nb solutions of one family, which agree in cell width and fill.
+template <class T>
+static void solve_init_t(const rc_solution* sols, int32_t nb, hipStream_t s) {
+  rc_family f = sols[0]->f;
+  // the row-push and split-panel fills poll cells until they are written
+  const int pend = sols[0]->fill_path == 1 || sols[0]->fill_path == 3;
+  for (int32_t t0 = 0; t0 < nb; t0 += kTables) {
+    InitTables tabs{};
+    const int32_t n = std::min<int32_t>(kTables, nb - t0);
+    for (int32_t t = 0; t < n; t++) {
+      tabs.m[t] = sizeof(T) == 4 ? (void*)sols[t0 + t]->m32 : (void*)sols[t0 + t]->m;
+      tabs.st[t] = sols[t0 + t]->status;
+      tabs.sentinel[t] = sols[t0 + t]->sentinel;
+    }
+    auto launch = [&](int64_t lb, dim3 grid) {
+      grid.z = (unsigned)n;
+      hipLaunchKernelGGL(k_solve_init<T>, grid, dim3(kFillThreads), 0, s, tabs, lb, f->F, f->w,
+                         f->row_off, f->cells, sols[0]->objective, pend);
+    };
+    if (pend)
+      for_row_groups(f, kInitChunk, [&](int64_t lb, dim3 grid) {
+        grid.x += 1;                                 // a slot is up to kGuard + 63 cells longer
+        launch(lb, grid);
+      });
+    else
+      launch(0, dim3(1, (unsigned)f->F));
+  }
+}
+
+hipError_t launch_solve_init(const rc_solution* sols, int32_t nb, hipStream_t s) {
+  for (int32_t a = 0, b; a < nb; a = b) {
+    for (b = a + 1; b < nb && sols[b]->cell32 == sols[a]->cell32 &&
+                    sols[b]->fill_path == sols[a]->fill_path;)
+      b++;
+    if (sols[a]->cell32)
+      solve_init_t<uint32_t>(sols + a, b - a, s);
+    else
+      solve_init_t<uint16_t>(sols + a, b - a, s);
+  }
   return hipGetLastError();
 }
 
@@ -922,29 +1014,6 @@ hipError_t launch_fill(rc_solution sol, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Launches over all rows, `per` cells of a row to a workgroup, as
-// launch(first row, grid): one launch for consecutive levels while their
-// longest row leaves at most half of the grid's workgroups without cells.
-template <class Launch>
-static void for_row_groups(rc_family f, int64_t per, Launch launch) {
-  const int64_t L = (int64_t)f->level_ptr.size() - 1;
-  for (int64_t l = 0; l < L;) {
-    const int64_t first = f->level_ptr[l];
-    int64_t most = 0, used = 0, end = l;
-    for (; end < L; end++) {
-      const int64_t tiles = (f->level_maxw[end] + per - 1) / per;
-      const int64_t rows = f->level_ptr[end + 1] - first;
-      const int64_t now = used + tiles * (f->level_ptr[end + 1] - f->level_ptr[end]);
-      const int64_t wide = std::max(most, tiles);
-      if (end > l && wide * rows > 2 * now + 65536) break;
-      most = wide;
-      used = now;
-    }
-    launch(first, dim3((unsigned)most, (unsigned)(f->level_ptr[end] - first)));
-    l = end;
-  }
-}
-
 hipError_t launch_fronts(rc_solution sol, hipStream_t s) {
   rc_family f = sol->f;
   uint16_t* segmin = sol->arena.get_n<uint16_t>((f->cells >> kSegShift) + f->F + 1);
@@ -967,21 +1036,33 @@ hipError_t launch_fronts(rc_solution sol, hipStream_t s) {
 }
 
 template <class T>
-static void select_t(rc_solution sol, const T* m, hipStream_t s) {
-  rc_family f = sol->f;
+static void select_t(const rc_solution* sols, int32_t nb, DevStatus* host, hipStream_t s) {
+  rc_family f = sols[0]->f;
   const int64_t v = f->F - 1;
   const int64_t groups = (f->w_host[v] * (int64_t)sizeof(T) + 15) / 16;
   const unsigned blocks = (unsigned)std::max<int64_t>(
       1, std::min<int64_t>((groups + kSelectThreads - 1) / kSelectThreads, kSelectBlocks));
-  hipLaunchKernelGGL(k_select<T>, dim3(blocks), dim3(kSelectThreads), 0, s, m, f->row_off, v,
-                     f->w, sol->objective, sol->status);
+  for (int32_t t0 = 0; t0 < nb; t0 += kTables) {
+    SelectTables tabs{};
+    const int32_t n = std::min<int32_t>(kTables, nb - t0);
+    for (int32_t t = 0; t < n; t++) {
+      tabs.m[t] = sizeof(T) == 4 ? (const void*)sols[t0 + t]->m32 : (const void*)sols[t0 + t]->m;
+      tabs.st[t] = sols[t0 + t]->status;
+    }
+    tabs.host = host + t0;
+    hipLaunchKernelGGL(k_select<T>, dim3(blocks, (unsigned)n), dim3(kSelectThreads), 0, s, tabs,
+                       f->row_off, v, f->w, sols[0]->objective);
+  }
 }
 
-hipError_t launch_select(rc_solution sol, hipStream_t s) {
-  if (sol->cell32)
-    select_t<uint32_t>(sol, sol->m32, s);
-  else
-    select_t<uint16_t>(sol, sol->m, s);
+hipError_t launch_select(const rc_solution* sols, int32_t nb, DevStatus* host, hipStream_t s) {
+  for (int32_t a = 0, b; a < nb; a = b) {
+    for (b = a + 1; b < nb && sols[b]->cell32 == sols[a]->cell32;) b++;
+    if (sols[a]->cell32)
+      select_t<uint32_t>(sols + a, b - a, host + a, s);
+    else
+      select_t<uint16_t>(sols + a, b - a, host + a, s);
+  }
   return hipGetLastError();
 }
 
@@ -1008,7 +1089,7 @@ static bool use_slice(rc_solution sol) {
 }
 
 template <class T>
-static hipError_t trace_t(rc_solution sol, const T* m, hipStream_t s) {
+static hipError_t trace_t(rc_solution sol, const T* m, const ScheduleOut& out, hipStream_t s) {
   rc_family f = sol->f;
   rc_graph g = f->g;
   sol->trace_path = use_slice(sol) ? 1 : 0;
@@ -1025,24 +1106,24 @@ static hipError_t trace_t(rc_solution sol, const T* m, hipStream_t s) {
                        f->pdt, f->pdm, f->pc, (int32_t)sol->Beff, m, sol->nxt);
     hipLaunchKernelGGL(k_trace_follow, dim3(1), dim3(kTraceThreads), 0, s, f->F, g->n, g->words,
                        f->fstride, f->bits, f->bd, f->A, g->dT, g->dM, S, sol->nxt, g->T_total,
-                       sol->status, sol->chain, sol->seg, sol->cached);
+                       sol->status, sol->chain, out);
   } else if (f->F <= kTraceLds) {
     hipLaunchKernelGGL((k_trace<true, T>), dim3(1), dim3(kTraceThreads), 0, s, f->F, g->n, g->words,
                        f->fstride, f->bits, f->bd, f->A, g->dT, g->dM, f->w, f->row_off,
                        f->pred_ptr, f->pidx, f->pdt, f->pdm, f->pc, (int32_t)sol->Beff, m,
-                       g->T_total, sol->status, sol->chain, sol->seg, sol->cached);
+                       g->T_total, sol->status, sol->chain, out);
   } else {
     hipLaunchKernelGGL((k_trace<false, T>), dim3(1), dim3(kTraceThreads), 0, s, f->F, g->n,
                        g->words, f->fstride, f->bits, f->bd, f->A, g->dT, g->dM, f->w,
                        f->row_off, f->pred_ptr, f->pidx, f->pdt, f->pdm, f->pc,
-                       (int32_t)sol->Beff, m, g->T_total, sol->status, sol->chain, sol->seg,
-                       sol->cached);
+                       (int32_t)sol->Beff, m, g->T_total, sol->status, sol->chain, out);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_trace(rc_solution sol, hipStream_t s) {
-  return sol->cell32 ? trace_t<uint32_t>(sol, sol->m32, s) : trace_t<uint16_t>(sol, sol->m, s);
+hipError_t launch_trace(rc_solution sol, const ScheduleOut& out, hipStream_t s) {
+  return sol->cell32 ? trace_t<uint32_t>(sol, sol->m32, out, s)
+                     : trace_t<uint16_t>(sol, sol->m, out, s);
 }
 
 // optarg of the whole table in as few launches as the rows' lengths allow: no cell's optarg depends on

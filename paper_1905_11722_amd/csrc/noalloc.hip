@@ -83,6 +83,7 @@ extern "C" int rc_solve_dual_noalloc(rc_family f, int64_t B, int32_t objective, 
   unsigned char* p = static_cast<unsigned char*>(base);
   b.st = reinterpret_cast<DevStatus*>(p + o_st);
   b.chain = reinterpret_cast<int32_t*>(p + o_chain);
+  b.out_chain = b.chain;                  // read into LDS before it is rewritten
   b.seg = reinterpret_cast<int32_t*>(p + o_seg);
   b.cached = p + o_cached;
   b.D = reinterpret_cast<uint32_t*>(p + o_D);

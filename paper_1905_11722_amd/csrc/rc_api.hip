@@ -15,6 +15,7 @@
 
 #include "rc_internal.h"
 #include "dual.h"
+#include "schedule.h"
 
 using namespace rcdp;
 
@@ -115,45 +116,55 @@ int dual_solve(rc_family f, int32_t objective, const DualBuffers& b, hipEvent_t 
                hipEvent_t e1, hipStream_t s, int64_t* t_opt, int64_t* m_opt, int32_t* k,
                int32_t* chain_host, int32_t* seg_host, uint8_t* cached_host, int64_t* overhead,
                int64_t* peak, int64_t* cache_mem) {
+  const bool pinned = b.host != nullptr;
+  if (pinned) b.host->in_flight();
   const hipError_t le = launch_dual(f, f->level_pairs, (int32_t)b.Beff, (int32_t)b.W, objective,
-                                    b.D, b.st, e0, e1, s);
+                                    b.D, b.st, pinned ? &b.host_st[0] : nullptr, e0, e1, s);
   if (le != hipSuccess) {
     set_last_error("dual table launch", le);
     return RC_E_DEVICE;
   }
   DevStatus hs;
-  RC_HIP(hipMemcpyAsync(&hs, b.st, sizeof(hs), hipMemcpyDeviceToHost, s));
+  if (!pinned) RC_HIP(hipMemcpyAsync(&hs, b.st, sizeof(hs), hipMemcpyDeviceToHost, s));
   RC_HIP(hipStreamSynchronize(s));
+  if (pinned) hs = b.host_st[0];
   const bool schedule = k || chain_host || seg_host || cached_host || overhead || peak || cache_mem;
   if (schedule && hs.t_sel >= 0) {
-    const int n = f->g->n;
+    const size_t n = (size_t)f->g->n;
+    const ScheduleOut out{b.out_chain, b.seg, b.cached, pinned ? &b.host_st[1] : b.st};
     const hipError_t te = launch_dual_trace(f, (int32_t)b.Beff, (int32_t)b.W, objective, b.D,
-                                            b.st, b.chain, b.seg, b.cached, s);
+                                            b.st, b.chain, out, s);
     if (te != hipSuccess) {
       set_last_error("dual traceback launch", te);
       return RC_E_DEVICE;
     }
     DevStatus ts;
-    RC_HIP(hipMemcpyAsync(&ts, b.st, sizeof(ts), hipMemcpyDeviceToHost, s));
+    if (!pinned) RC_HIP(hipMemcpyAsync(&ts, b.st, sizeof(ts), hipMemcpyDeviceToHost, s));
     RC_HIP(hipStreamSynchronize(s));
+    if (pinned) ts = b.host_st[1];
     if (ts.error || ts.k < 0 || ts.k > f->F) {
       set_last_error_msg("dual traceback: the walk did not end at (empty set, 0, 0)");
       return RC_E_DEVICE;
     }
-    if (chain_host && ts.k > 0)
-      RC_HIP(hipMemcpyAsync(chain_host, b.chain, sizeof(int32_t) * (size_t)ts.k,
-                            hipMemcpyDeviceToHost, s));
-    if (seg_host && n > 0)
-      RC_HIP(hipMemcpyAsync(seg_host, b.seg, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost,
-                            s));
-    if (cached_host && n > 0)
-      RC_HIP(hipMemcpyAsync(cached_host, b.cached, (size_t)n, hipMemcpyDeviceToHost, s));
-    RC_HIP(hipStreamSynchronize(s));
+    auto bring = [&](void* dst, const void* src, size_t bytes) -> int {
+      if (!dst || bytes == 0) return RC_OK;
+      if (pinned)
+        std::memcpy(dst, src, bytes);
+      else
+        RC_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
+      return RC_OK;
+    };
+    if (bring(chain_host, b.out_chain, sizeof(int32_t) * (size_t)ts.k) != RC_OK ||
+        bring(seg_host, b.seg, sizeof(int32_t) * n) != RC_OK ||
+        bring(cached_host, b.cached, n) != RC_OK)
+      return RC_E_DEVICE;
+    if (!pinned) RC_HIP(hipStreamSynchronize(s));
     if (k) *k = ts.k;
     if (overhead) *overhead = ts.overhead;
     if (peak) *peak = ts.peak;
     if (cache_mem) *cache_mem = ts.cache_mem;
   }
+  if (pinned) b.host->landed();
   if (t_opt) *t_opt = hs.t_sel;
   if (m_opt) *m_opt = hs.t_sel >= 0 ? hs.m_sel : -1;
   return hs.t_sel >= 0 ? RC_OK : RC_INFEASIBLE;
@@ -426,16 +437,6 @@ static int upload_blocks(rc_family f, int64_t* counts, std::unique_ptr<Staging>&
 static int64_t pruned_family_size(rc_graph g) {
   if (g->n == 0) return 1;
   return (int64_t)g->n + 1 + (g->num_sinks > 1 ? 1 : 0);
-}
-
-// Gathers L into the device buffer dev (at least bytes) and enqueues one
-// copy of it into the staging buffer.
-static int pack_to_host(const PackList& L, void* dev, size_t bytes, Staging& st, hipStream_t s) {
-  if (launch_pack(L, dev, s) != hipSuccess) return RC_E_DEVICE;
-  st.in_flight();
-  if (hipMemcpyAsync(st.data(), dev, bytes, hipMemcpyDeviceToHost, s) != hipSuccess)
-    return RC_E_DEVICE;
-  return RC_OK;
 }
 
 // Record buffers up to this many records are sized from an upper bound
@@ -844,9 +845,17 @@ int rc_solve_dual(rc_family f, int64_t B, int32_t objective, void* stream, int64
   buf.D = A.get_n<uint32_t>(need.cells);
   buf.st = A.get_n<DevStatus>(1);
   buf.chain = A.get_n<int32_t>(f->F);
-  buf.seg = A.get_n<int32_t>(f->g->n);
-  buf.cached = A.get_n<uint8_t>(f->g->n);
-  if (!buf.D || !buf.st || !buf.chain || !buf.seg || !buf.cached) return finish(RC_E_NOMEM);
+  const int64_t n = f->g->n, kmax = std::min<int64_t>(f->F, n + 1);
+  StageLayout lay;
+  const size_t o_st = lay.add<DevStatus>(2), o_ch = lay.add<int32_t>(kmax),
+               o_sg = lay.add<int32_t>(n), o_ca = lay.add<uint8_t>(n);
+  Staging stage(lay.bytes);
+  if (!buf.D || !buf.st || !buf.chain || !stage.data()) return finish(RC_E_NOMEM);
+  buf.host = &stage;
+  buf.host_st = stage.at<DevStatus>(o_st);
+  buf.out_chain = stage.at<int32_t>(o_ch);
+  buf.seg = stage.at<int32_t>(o_sg);
+  buf.cached = stage.at<uint8_t>(o_ca);
   if (fill_ms && (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess))
     return finish(RC_E_DEVICE);
   const int st = dual_solve(f, objective, buf, e0, e1, s, t_opt, m_opt, k, chain_host, seg_host,
@@ -973,10 +982,7 @@ static int new_solution(rc_family f, int64_t B, int32_t objective, hipStream_t s
     sol->m = sol->arena.get_n<uint16_t>(f->cells_alloc);
   sol->status = sol->arena.get_n<DevStatus>(1);
   sol->chain = sol->arena.get_n<int32_t>(f->F);
-  sol->seg = sol->arena.get_n<int32_t>(f->g->n);
-  sol->cached = sol->arena.get_n<uint8_t>(f->g->n);
-  if (!(sol->m || sol->m32) || !sol->status || !sol->chain || !sol->seg || !sol->cached)
-    return fail(RC_E_NOMEM);
+  if (!(sol->m || sol->m32) || !sol->status || !sol->chain) return fail(RC_E_NOMEM);
   if (hipEventCreate(&sol->ev0) != hipSuccess || hipEventCreate(&sol->ev1) != hipSuccess)
     return fail(RC_E_DEVICE);
   if (!cell32) {
@@ -987,20 +993,8 @@ static int new_solution(rc_family f, int64_t B, int32_t objective, hipStream_t s
       (hipEventCreate(&sol->evk0) != hipSuccess || hipEventCreate(&sol->evk1) != hipSuccess))
     return fail(RC_E_DEVICE);
   if (sol->fill_path == 3) {
-    const int64_t K = wide_columns(f), R = f->wrec_total;
-    sol->progress = sol->arena.get_n<int32_t>(K);
-    sol->ticket = sol->arena.get_n<int32_t>(1);
-    sol->wkey = sol->arena.get_n<int64_t>(R);
-    sol->wbl_tmp = sol->arena.get_n<int32_t>(2 * R);
-    sol->wtd_tmp = sol->arena.get_n<int32_t>(kWTd * R);
-    sol->wbl = sol->arena.get_n<int32_t>(2 * (R + kWPad));
-    sol->wtd = sol->arena.get_n<int32_t>(kWTd * (R + kWPad));
-    sol->wmeta = sol->arena.get_n<int32_t>(f->nblk * kWMeta);
-    sol->wlive = sol->arena.get_n<int32_t>(f->nblk * K);
-    sol->wpush = sol->arena.get_n<int32_t>(f->nblk * kJB * kWPush);
-    if (!sol->progress || !sol->ticket || !sol->wkey || !sol->wbl_tmp || !sol->wtd_tmp ||
-        !sol->wbl || !sol->wtd || !sol->wmeta || !sol->wlive || !sol->wpush)
-      return fail(RC_E_NOMEM);
+    sol->wslab = static_cast<char*>(sol->arena.get(wide_slab_bytes(f)));
+    if (!sol->wslab) return fail(RC_E_NOMEM);
   } else if (sol->fill_path != 0) {
     const int64_t K = sol->fill_path == 2 ? ghost_columns(f) : blocked_columns(f);
     sol->progress = sol->arena.get_n<int32_t>(K);
@@ -1072,7 +1066,7 @@ static int solve_one(rc_family f, int64_t B, int32_t objective, void* stream, rc
     drop_solution(sol);
     return st;
   };
-  if (launch_solve_init(sol, s) != hipSuccess) return fail(RC_E_DEVICE);
+  if (launch_solve_init(&sol, 1, s) != hipSuccess) return fail(RC_E_DEVICE);
   if (hipEventRecord(sol->ev0, s) != hipSuccess) return fail(RC_E_DEVICE);
   hipError_t fe = sol->fill_path == 3   ? launch_fill_wide(sol, s)
                   : sol->fill_path == 2 ? launch_fill_ghost(sol, s)
@@ -1088,12 +1082,10 @@ static int solve_one(rc_family f, int64_t B, int32_t objective, void* stream, rc
     return fail(RC_E_DEVICE);
   }
   if (hipEventRecord(sol->ev1, s) != hipSuccess) return fail(RC_E_DEVICE);
-  if (launch_select(sol, s) != hipSuccess) return fail(RC_E_DEVICE);
   Staging stage(sizeof(DevStatus));
   if (!stage.data()) return fail(RC_E_NOMEM);
   stage.in_flight();
-  if (hipMemcpyAsync(stage.data(), sol->status, sizeof(DevStatus), hipMemcpyDeviceToHost, s) !=
-          hipSuccess ||
+  if (launch_select(&sol, 1, stage.at<DevStatus>(0), s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess)
     return fail(RC_E_DEVICE);
   stage.landed();
@@ -1136,8 +1128,7 @@ int rc_solve_batch(rc_family f, const int64_t* B_host, int32_t nb, int32_t objec
     if (st != RC_OK) return fail(st);
     sols.push_back(x);
   }
-  for (rc_solution x : sols)
-    if (launch_solve_init(x, s) != hipSuccess) return fail(RC_E_DEVICE);
+  if (launch_solve_init(sols.data(), nb, s) != hipSuccess) return fail(RC_E_DEVICE);
   rc_solution s0 = sols[0];
   if (hipEventRecord(s0->ev0, s) != hipSuccess) return fail(RC_E_DEVICE);
   std::vector<BParams> host_prm;
@@ -1195,16 +1186,12 @@ int rc_solve_batch(rc_family f, const int64_t* B_host, int32_t nb, int32_t objec
     }
   }
   if (hipEventRecord(s0->ev1, s) != hipSuccess) return fail(RC_E_DEVICE);
-  for (rc_solution x : sols)
-    if (launch_select(x, s) != hipSuccess) return fail(RC_E_DEVICE);
   Staging stage(sizeof(DevStatus) * (size_t)nb);
   if (!stage.data()) return fail(RC_E_NOMEM);
   stage.in_flight();
-  for (int32_t b = 0; b < nb; b++)
-    if (hipMemcpyAsync(stage.at<DevStatus>(0) + b, sols[b]->status, sizeof(DevStatus),
-                       hipMemcpyDeviceToHost, s) != hipSuccess)
-      return fail(RC_E_DEVICE);
-  if (hipStreamSynchronize(s) != hipSuccess) return fail(RC_E_DEVICE);
+  if (launch_select(sols.data(), nb, stage.at<DevStatus>(0), s) != hipSuccess ||
+      hipStreamSynchronize(s) != hipSuccess)
+    return fail(RC_E_DEVICE);
   stage.landed();
   const float fill_ms = elapsed(s0->ev0, s0->ev1);
   const float kernel_ms = s0->evk0 ? elapsed(s0->evk0, s0->evk1) : fill_ms;
@@ -1258,21 +1245,19 @@ int rc_reconstruct(rc_solution sol, void* stream, int32_t* k, int32_t* chain_hos
   const size_t o_st = lay.add<DevStatus>(1), o_ch = lay.add<int32_t>(kmax),
                o_sg = lay.add<int32_t>(n), o_ca = lay.add<uint8_t>(n);
   Staging stage(lay.bytes);
-  if (!sol->pack) sol->pack = sol->arena.get(lay.bytes);
-  if (!stage.data() || !sol->pack) return RC_E_NOMEM;
-  const hipError_t te = launch_trace(sol, s);
-  if (te == hipErrorOutOfMemory) return RC_E_NOMEM;
+  if (!stage.data()) return RC_E_NOMEM;
+  const ScheduleOut sched{stage.at<int32_t>(o_ch), stage.at<int32_t>(o_sg),
+                          stage.at<uint8_t>(o_ca), stage.at<DevStatus>(o_st)};
+  stage.in_flight();
+  const hipError_t te = launch_trace(sol, sched, s);
+  if (te == hipErrorOutOfMemory) {
+    stage.landed();
+    return RC_E_NOMEM;
+  }
   if (te != hipSuccess) {
     set_last_error("traceback launch", te);
     return RC_E_DEVICE;
   }
-  PackList PL;
-  PL.add(sol->status, sizeof(DevStatus), (int64_t)o_st);
-  PL.add(sol->chain, sizeof(int32_t) * kmax, (int64_t)o_ch);
-  PL.add(sol->seg, sizeof(int32_t) * n, (int64_t)o_sg);
-  PL.add(sol->cached, (n + 3) / 4 * 4, (int64_t)o_ca);   // whole words of the padded buffer
-  const int pc = pack_to_host(PL, sol->pack, lay.bytes, stage, s);
-  if (pc != RC_OK) return pc;
   RC_HIP(hipStreamSynchronize(s));
   stage.landed();
   const DevStatus hs = *stage.at<DevStatus>(o_st);

@@ -206,10 +206,7 @@ struct rc_solution_s {
   uint16_t* m = nullptr;          // [cells] opt values, kInfM = infinity
   uint16_t* arg = nullptr;        // [cells] optarg, derived on demand by rc_export_table
   rcdp::DevStatus* status = nullptr;
-  int32_t* chain = nullptr;       // [F]
-  int32_t* seg = nullptr;         // [n]
-  uint8_t* cached = nullptr;      // [n]
-  void* pack = nullptr;           // the traceback's results gathered for one copy to the host
+  int32_t* chain = nullptr;       // [F] the traceback's walk
   uint32_t* nxt = nullptr;        // the traceback's optarg slice [F * (t* + 1)] (fill.hip)
   int64_t nxt_cells = 0;
   int32_t trace_path = -1;        // the last traceback: 0 predecessor scans, 1 optarg slice
@@ -222,14 +219,7 @@ struct rc_solution_s {
   int32_t* blk_meta = nullptr;    // blocked fill: per block metadata [nblk * kMetaInts]
   int32_t* push = nullptr;        // blocked fill: row push lists [nblk * kJB * kPushInts]
   int32_t* tri = nullptr;         // ghost-zone fill: in-block lists [nblk * kJB * kTriInts]
-  int64_t* wkey = nullptr;        // split-panel fill: sort keys of the unsorted records
-  int32_t* wbl_tmp = nullptr;     // split-panel fill: unsorted window base / limit
-  int32_t* wtd_tmp = nullptr;     // split-panel fill: unsorted budgets / additions
-  int32_t* wbl = nullptr;         // split-panel fill: [2 (R + kWPad)] sorted
-  int32_t* wtd = nullptr;         // split-panel fill: [kWTd (R + kWPad)] sorted
-  int32_t* wmeta = nullptr;       // split-panel fill: [nblk * kWMeta]
-  int32_t* wlive = nullptr;       // split-panel fill: [nblk * K] records reaching each column
-  int32_t* wpush = nullptr;       // split-panel fill: [nblk * kJB * kWPush]
+  char* wslab = nullptr;          // split-panel fill: records, push lists, progress (wide.hip)
   int32_t cpt = 1;                // blocked fill: cells per thread of a column
   uint16_t* sentinel = nullptr;   // 8 cells of infinity
   int32_t fill_path = 0;          // 0 level launches, 1 row-push wavefront, 2 ghost-zone
@@ -288,25 +278,6 @@ struct StageLayout {
   }
 };
 
-// ---- utilities (family.hip)
-hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);  // bytes % 8 == 0
-// Device segments gathered into one device buffer (whole 32-bit words; the
-// byte counts, offsets and pointers are multiples of 4).
-struct PackSeg {
-  const void* src;
-  int64_t bytes;
-  int64_t dst_off;
-};
-constexpr int kPackMax = 8;
-struct PackList {
-  PackSeg seg[kPackMax];
-  int32_t n = 0;
-  void add(const void* src, int64_t bytes, int64_t dst_off) {
-    if (bytes > 0) seg[n++] = PackSeg{src, bytes, dst_off};
-  }
-};
-hipError_t launch_pack(const PackList& L, void* dst, hipStream_t s);
-
 // ---- graph kernels (family.hip)
 hipError_t launch_graph_masks(rc_graph g, const int32_t* d_row_ptr, const int32_t* d_col_idx,
                               hipStream_t s);
@@ -329,10 +300,13 @@ hipError_t launch_scan(const int64_t* in, int64_t* out, int64_t count, hipStream
 hipError_t launch_pair_write(rc_family f, const uint64_t* mask, hipStream_t s);
 
 // ---- DP kernels (fill.hip)
-hipError_t launch_solve_init(rc_solution sol, hipStream_t s);
+hipError_t launch_solve_init(const rc_solution* sols, int32_t nb, hipStream_t s);
 hipError_t launch_fill(rc_solution sol, hipStream_t s);
-hipError_t launch_select(rc_solution sol, hipStream_t s);
-hipError_t launch_trace(rc_solution sol, hipStream_t s);
+// t* and opt[V, t*] of nb solutions of one family; host[b] (pinned) receives
+// solution b's status.
+hipError_t launch_select(const rc_solution* sols, int32_t nb, DevStatus* host, hipStream_t s);
+struct ScheduleOut;
+hipError_t launch_trace(rc_solution sol, const ScheduleOut& out, hipStream_t s);
 hipError_t launch_arg_all(rc_solution sol, hipStream_t s);
 // The dominance skip: every row of the filled 16-bit table reduced to its
 // weak front (dominated cells stored as infinity).
@@ -346,8 +320,6 @@ hipError_t launch_blk_clusters(rc_family f, int64_t* count, hipStream_t s);
 hipError_t launch_rec_prepare(rc_solution sol, hipStream_t s);
 hipError_t launch_push_prepare(rc_solution sol, int32_t C, hipStream_t s);
 hipError_t launch_rec_sort(rc_solution sol, int32_t C, int32_t H, hipStream_t s);
-hipError_t launch_fill_pending(rc_solution sol, hipStream_t s);
-hipError_t launch_pad_init(rc_solution sol, hipStream_t s);
 int blocked_cells_per_thread(rc_family f);
 int num_cus();                          // compute units of the current device (cached)
 
@@ -412,12 +384,12 @@ size_t min_budget_scratch_bytes(rc_family f, int32_t hi0);
 hipError_t launch_min_budget(rc_family f, int32_t hi0, uint32_t* scratch, hipStream_t s);
 // Memory-indexed table of Algorithm 1's recursion (dual.hip): D[F * W]
 // uint32, W = min(B, M(V)) + 1; t and the least m of the objective into
-// st->t_sel / st->m_sel (-1 when no chain reaches V).  level_pairs[l]: the
+// st->t_sel / st->m_sel (-1 when no chain reaches V)  level_pairs[l]: the
 // most pairs of a target of size level l.  e0/e1 (may be null) are recorded
 // around the table's launches.
 hipError_t launch_dual(rc_family f, const std::vector<int64_t>& level_pairs, int32_t B, int32_t W,
-                       int objective, uint32_t* D, DevStatus* st, hipEvent_t e0, hipEvent_t e1,
-                       hipStream_t s);
+                       int objective, uint32_t* D, DevStatus* st, DevStatus* host, hipEvent_t e0,
+                       hipEvent_t e1, hipStream_t s);
 int64_t blocked_columns(rc_family f);
 
 // One memory-indexed solve (rc_api.hip): the sizes it needs and the device
@@ -427,9 +399,14 @@ struct DualBuffers {
   int64_t Beff = 0, W = 0, cells = 0;
   uint32_t* D = nullptr;          // [cells]
   DevStatus* st = nullptr;
-  int32_t* chain = nullptr;       // [F]
+  int32_t* chain = nullptr;       // [F] the traceback's walk
+  // results: the pinned buffers of host_st and host, or (host null) device
+  // buffers that are copied
+  int32_t* out_chain = nullptr;   // [min(F, n + 1)]
   int32_t* seg = nullptr;         // [n]
   uint8_t* cached = nullptr;      // [n]
+  Staging* host = nullptr;
+  DevStatus* host_st = nullptr;   // [2]: after the selection, after the traceback
 };
 int dual_buffers(rc_family f, int64_t B, int32_t objective, DualBuffers* out);
 int dual_solve(rc_family f, int32_t objective, const DualBuffers& b, hipEvent_t e0,
@@ -465,6 +442,7 @@ struct WParams {
 // panel waves: sixteen waves, four per SIMD.
 __host__ __device__ constexpr int wide_slots_per_cu(int np) { return 16 / (np + 1); }
 int64_t wide_columns(rc_family f);
+size_t wide_slab_bytes(rc_family f);
 hipError_t launch_wide_count(rc_family f, int64_t* count, hipStream_t s);
 hipError_t launch_fill_wide(rc_solution sol, hipStream_t s);
 hipError_t launch_fill_wide_batch(rc_solution* sols, int32_t nb, WParams* host_prm,

@@ -33,11 +33,18 @@ __device__ __forceinline__ V wave_max(V x) {
 
 }  // namespace sched
 
+// Where a traced schedule goes: device memory, or the host's pinned buffer
+// (then a traceback costs no gather and no copy).
+struct ScheduleOut {
+  int32_t* chain;     // [k] in increasing order (L_1 .. L_k)
+  int32_t* seg;       // [n] segment index of each node
+  uint8_t* cached;    // [n] 1 iff in U_k
+  DevStatus* st;      // error (2: the walk failed), k, overhead, peak, cache_mem
+};
+
 // Every thread of the block calls it after the walk: chain[0 .. k) holds the
-// chain from V back to its first set; it is written back in increasing order
-// (L_1 .. L_k), seg[n] (segment index of each node), cached[n] (1 iff in U_k)
-// and st->{k, overhead, peak, cache_mem} are filled.  s_chain[k] and s_M[n]
-// are LDS scratch of the caller.
+// chain from V back to its first set (k < 0: the walk failed); out is
+// filled.  s_chain[k] and s_M[n] are LDS scratch of the caller.
 //
 // The chain's steps are evaluated together rather than one after another:
 // a node v lies in V_i for exactly one i (the chain is increasing and ends
@@ -51,8 +58,8 @@ template <int kThreads>
 __device__ __forceinline__ void finish_schedule(int32_t k, int n, int words, int64_t fstride,
                                 const uint64_t* __restrict__ bits, const uint64_t* __restrict__ bd,
                                 const int32_t* __restrict__ A, const int32_t* __restrict__ T,
-                                const int32_t* __restrict__ M, int64_t T_total, DevStatus* st,
-                                int32_t* chain, int32_t* seg, uint8_t* cached, int32_t* s_chain,
+                                const int32_t* __restrict__ M, int64_t T_total,
+                                const int32_t* chain, const ScheduleOut& out, int32_t* s_chain,
                                 int32_t* s_M) {
   using sched::kWave;
   constexpr int kWaves = kThreads / kWave;
@@ -63,6 +70,13 @@ __device__ __forceinline__ void finish_schedule(int32_t k, int n, int words, int
   __shared__ int64_t s_red[3][kWaves];
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wave = tid / kWave;
+  if (k < 0) {
+    if (tid == 0) {
+      out.st->error = 2;
+      out.st->k = -1;
+    }
+    return;
+  }
   for (int c = tid; c < k; c += kThreads) {
     s_chain[c] = chain[k - 1 - c];
     s_mv[c] = 0;
@@ -74,7 +88,7 @@ __device__ __forceinline__ void finish_schedule(int32_t k, int n, int words, int
     s_M[v] = M[v];
   }
   __syncthreads();
-  for (int c = tid; c < k; c += kThreads) chain[c] = s_chain[c];
+  for (int c = tid; c < k; c += kThreads) out.chain[c] = s_chain[c];
   // one (step, word) per item: the nodes V_i of the step and the boundary of L_i
   for (int x = tid; x < k * words; x += kThreads) {
     const int c = x / words, wd = x - c * words;
@@ -95,9 +109,9 @@ __device__ __forceinline__ void finish_schedule(int32_t k, int n, int words, int
   // per node: its segment, whether U_k holds it, and the step at which U gains it
   int64_t tu = 0;
   for (int v = tid; v < n; v += kThreads) {
-    seg[v] = s_seg[v];
+    out.seg[v] = s_seg[v];
     const int32_t f = s_first[v];
-    cached[v] = f < k ? 1 : 0;
+    out.cached[v] = f < k ? 1 : 0;
     if (f < k) {
       atomicAdd(&s_gain[f], s_M[v]);
       tu += T[v];
@@ -139,10 +153,11 @@ __device__ __forceinline__ void finish_schedule(int32_t k, int n, int words, int
       tsum += s_red[2][q];
       mtot += s_red[0][q];
     }
-    st->k = k;
-    st->overhead = T_total - tsum;
-    st->peak = pk;
-    st->cache_mem = mtot;
+    out.st->error = 0;
+    out.st->k = k;
+    out.st->overhead = T_total - tsum;
+    out.st->peak = pk;
+    out.st->cache_mem = mtot;
   }
 }
 

@@ -527,12 +527,6 @@ __attribute__((amdgpu_waves_per_eu((wide_slots_per_cu(NP) * (NP + 1) + 3) / 4)))
   }
 }
 
-__global__ void k_wide_init(int32_t* progress, int32_t K, int32_t* ticket) {
-  for (int32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < K; k += gridDim.x * blockDim.x)
-    progress[k] = 1;                        // the empty set's row is written by the init kernel
-  if (blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;
-}
-
 // ------------------------------------------------------------ preparation
 // Distinct shifts among the slots of e[kJB] (e >= 0) whose bit is set in
 // mask; returns their number and writes them in ascending order.
@@ -579,66 +573,147 @@ __global__ __launch_bounds__(256) void k_wide_count(const int64_t* rec_ptr, Bloc
   if (threadIdx.x == 0) count[b] = (int64_t)s_n;
 }
 
-// Per solve: the live records of block b (slot with a pair and B - c >= 0),
-// one per distinct shift, unsorted, from wptr[b] on: {cm, base, lim} into key
-// and bl_tmp, budgets and additions into td_tmp.  meta[b] = {records, reach,
-// rows, largest P of the rows, sources' end, ...}.
-__global__ __launch_bounds__(256) void k_wide_prepare(int32_t F, int32_t Beff, const int32_t* w,
-                                                      const int64_t* row_off,
-                                                      const int64_t* rec_ptr, BlockRecords R,
-                                                      const int64_t* wptr, int64_t* key,
-                                                      int32_t* bl_tmp, int32_t* td_tmp,
-                                                      int32_t* meta) {
-  const int64_t b = blockIdx.x;
+// ---- per solve
+// Everything a table's fill reads besides the family and the table itself, in
+// one slab per table: [K] progress, the ticket, [nblk * kWMeta] meta, records
+// (bl, td), [nblk * K] live, push lists; byte offsets, multiples of 256.
+struct WSlab {
+  int64_t progress, ticket, meta, bl, td, live, push, bytes;
+};
+
+WSlab wide_slab(rc_family f) {
+  const int64_t K = (f->max_row + kWC - 1) / kWC, R = f->wrec_total + kWPad;
+  WSlab o{};
+  auto add = [&](int64_t words) {
+    const int64_t at = o.bytes;
+    o.bytes += (4 * words + 255) & ~(int64_t)255;
+    return at;
+  };
+  o.progress = add(K);
+  o.ticket = add(1);
+  o.meta = add(f->nblk * kWMeta);
+  o.bl = add(2 * R);
+  o.td = add(kWTd * R);
+  o.live = add(f->nblk * K);
+  o.push = add(f->nblk * kJB * kWPush);
+  return o;
+}
+
+constexpr int kSetupTables = 64;
+struct SetupTables {
+  char* slab[kSetupTables];
+  int32_t Beff[kSetupTables];
+};
+
+// Records of block b: one per source and distinct shift with a live pair
+// (slot with a pair and B - c >= 0), ordered by the last column their window
+// reaches, descending, so that a column streams a prefix.  Keys (column,
+// record, shift number) are appended to LDS, sorted there (bitonic, at most
+// kWMaxRec) and the records written in that order.  live[x] = the records
+// that reach column x; meta = {records, columns to the right the windows
+// reach, rows, largest P of the rows, rows the panel reads}.
+constexpr int kKeyRec = 3, kKeyCol = 19;       // key: column << 19 | record << 3 | shift number
+
+__device__ __forceinline__ uint32_t live_slots(const BlockRecords& R, int64_t r, int32_t Beff) {
+  uint32_t mask = 0;
+  for (int s = 0; s < kJB; s++)
+    if (R.e[r * kJB + s] >= 0 && Beff - R.c[r * kJB + s] >= 0) mask |= 1u << s;
+  return mask;
+}
+
+__device__ void setup_records(int64_t b, int32_t F, int32_t K, int32_t Beff, const int32_t* w,
+                              const int64_t* row_off, const int64_t* rec_ptr,
+                              const BlockRecords& R, const int64_t* wptr, char* slab,
+                              const WSlab& o, uint64_t* s_key, int32_t* s_n, int32_t* s_emax) {
   const int64_t end = panel_end(b);
-  __shared__ int32_t s_n, s_emax;
+  const int64_t rbase = rec_ptr[b];
   if (threadIdx.x == 0) {
-    s_n = 0;
-    s_emax = 0;
+    *s_n = 0;
+    *s_emax = 0;
   }
   __syncthreads();
-  const int64_t base = wptr[b];
-  for (int64_t r = rec_ptr[b] + threadIdx.x; r < rec_ptr[b + 1]; r += blockDim.x) {
+  for (int64_t r = rbase + threadIdx.x; r < rec_ptr[b + 1]; r += blockDim.x) {
     const int32_t i = R.src[r];
     if (i >= end) continue;
-    uint32_t livemask = 0;
-    for (int s = 0; s < kJB; s++)
-      if (R.e[r * kJB + s] >= 0 && Beff - R.c[r * kJB + s] >= 0) livemask |= 1u << s;
     int32_t sh[kJB];
-    const int nsh = distinct_shifts(R.e + r * kJB, livemask, sh);
-    const int32_t Pi = w[i] - 1;
-    const int64_t endi = row_off[i] + Pi;
+    const int nsh = distinct_shifts(R.e + r * kJB, live_slots(R, r, Beff), sh);
+    if (nsh == 0) continue;
+    const int32_t at = atomicAdd(s_n, nsh);
     for (int x = 0; x < nsh; x++) {
-      const int32_t e = sh[x];
-      const int32_t o = atomicAdd(&s_n, 1);
-      const int64_t d = base + o;
-      uint32_t tau2[kJB / 2] = {0, 0, 0, 0}, dm2[kJB / 2] = {0, 0, 0, 0};
-      for (int s = 0; s < kJB; s++) {
-        const bool ok = ((livemask >> s) & 1) && R.e[r * kJB + s] == e;
-        const uint32_t tv = ok ? (uint32_t)(Beff - R.c[r * kJB + s]) : 0u;
-        const uint32_t dv = ok ? (R.kadd[r * kJB + s] >> 16) : 0xFFFFu;
-        tau2[s / 2] |= tv << (16 * (s & 1));
-        dm2[s / 2] |= dv << (16 * (s & 1));
-      }
-      const int64_t cm = ((int64_t)Pi + e) / kWC;        // last column the window reaches
-      key[d] = (cm << 20) | (int64_t)o;
-      bl_tmp[2 * d] = (int32_t)(2 * (endi + e - kWC + 1));
-      bl_tmp[2 * d + 1] = (int32_t)(2 * (endi + 1));
-      for (int q = 0; q < kJB / 2; q++) {
-        td_tmp[d * kWTd + q] = (int32_t)tau2[q];
-        td_tmp[d * kWTd + 4 + q] = (int32_t)dm2[q];
-      }
-      atomicMax(&s_emax, e);
+      const int64_t cm = ((int64_t)w[i] - 1 + sh[x]) / kWC;  // last column the window reaches
+      s_key[at + x] = ((uint64_t)(((int64_t)1 << 40) - 1 - cm) << kKeyCol) |
+                      ((uint64_t)(r - rbase) << kKeyRec) | (uint64_t)x;
     }
+    atomicMax(s_emax, sh[nsh - 1]);
   }
   __syncthreads();
+  const int32_t n = *s_n;
+  int32_t N = 1;
+  while (N < n) N <<= 1;
+  for (int32_t x = n + threadIdx.x; x < N; x += blockDim.x) s_key[x] = ~0ull;
+  __syncthreads();
+  for (int32_t kk = 2; kk <= N; kk <<= 1)
+    for (int32_t j = kk >> 1; j > 0; j >>= 1) {
+      for (int32_t q = threadIdx.x; q < N / 2; q += blockDim.x) {
+        const int32_t x = 2 * q - (q & (j - 1)), y = x + j;
+        const bool up = (x & kk) == 0;
+        const uint64_t a = s_key[x], c = s_key[y];
+        if ((a > c) == up) {
+          s_key[x] = c;
+          s_key[y] = a;
+        }
+      }
+      __syncthreads();
+    }
+  const int64_t base = wptr[b];
+  int32_t* bl = reinterpret_cast<int32_t*>(slab + o.bl) + 2 * base;
+  uint32_t* td = reinterpret_cast<uint32_t*>(slab + o.td) + kWTd * base;
+  for (int32_t x = threadIdx.x; x < n; x += blockDim.x) {
+    const uint64_t key = s_key[x];
+    const int64_t r = rbase + (int64_t)((key >> kKeyRec) & ((1u << (kKeyCol - kKeyRec)) - 1));
+    const uint32_t mask = live_slots(R, r, Beff);
+    int32_t sh[kJB];
+    distinct_shifts(R.e + r * kJB, mask, sh);
+    const int32_t e = sh[key & ((1u << kKeyRec) - 1)];
+    uint32_t tau2[kJB / 2] = {0, 0, 0, 0}, dm2[kJB / 2] = {0, 0, 0, 0};
+#pragma unroll
+    for (int s = 0; s < kJB; s++) {
+      const bool ok = ((mask >> s) & 1) && R.e[r * kJB + s] == e;
+      const uint32_t tv = ok ? (uint32_t)(Beff - R.c[r * kJB + s]) : 0u;
+      const uint32_t dv = ok ? (R.kadd[r * kJB + s] >> 16) : 0xFFFFu;
+      tau2[s / 2] |= tv << (16 * (s & 1));
+      dm2[s / 2] |= dv << (16 * (s & 1));
+    }
+    const int32_t i = R.src[r];
+    const int64_t endi = row_off[i] + w[i] - 1;
+    bl[2 * x] = (int32_t)(2 * (endi + e - kWC + 1));
+    bl[2 * x + 1] = (int32_t)(2 * (endi + 1));
+#pragma unroll
+    for (int q = 0; q < kJB / 2; q++) {
+      td[x * kWTd + q] = tau2[q];
+      td[x * kWTd + 4 + q] = dm2[q];
+    }
+  }
+  int32_t* live = reinterpret_cast<int32_t*>(slab + o.live) + b * (int64_t)K;
+  for (int32_t x = threadIdx.x; x < K; x += blockDim.x) {
+    int32_t lo = 0, hi = n;                              // first record with cm < x
+    while (lo < hi) {
+      const int32_t mid = (lo + hi) >> 1;
+      const int64_t cm = ((int64_t)1 << 40) - 1 - (int64_t)(s_key[mid] >> kKeyCol);
+      if (cm >= x)
+        lo = mid + 1;
+      else
+        hi = mid;
+    }
+    live[x] = lo;
+  }
   if (threadIdx.x == 0) {
     const int64_t j0 = 1 + b * kJB, j1 = min<int64_t>(j0 + kJB, F);
     int32_t mp = -1;
     for (int64_t j = j0; j < j1; j++) mp = max(mp, w[j] - 1);
-    int32_t* mt = meta + b * kWMeta;
-    mt[0] = s_n;
-    mt[1] = (s_emax + kWC - 1) / kWC + 1;           // columns to the right the windows reach
+    int32_t* mt = reinterpret_cast<int32_t*>(slab + o.meta) + b * kWMeta;
+    mt[0] = n;
+    mt[1] = (*s_emax + kWC - 1) / kWC + 1;          // columns to the right the windows reach
     mt[2] = (int32_t)(j1 - j0);
     mt[3] = mp;
     mt[4] = (int32_t)end;                           // rows the panel reads
@@ -646,71 +721,12 @@ __global__ __launch_bounds__(256) void k_wide_prepare(int32_t F, int32_t Beff, c
   }
 }
 
-// Per solve: sort block b's records by the last column they reach,
-// descending (bitonic sort in LDS of at most kWMaxRec keys), write them in
-// that order to bl / td, and live[b * K + x] = the records reaching column x.
-__global__ __launch_bounds__(256) void k_wide_sort(int32_t K, const int64_t* wptr,
-                                                   const int64_t* key, const int32_t* bl_tmp,
-                                                   const int32_t* td_tmp, const int32_t* meta,
-                                                   int32_t* bl, int32_t* td, int32_t* live) {
-  __shared__ int64_t s_key[kWMaxRec];
-  const int64_t b = blockIdx.x;
-  const int64_t base = wptr[b];
-  const int32_t n = meta[b * kWMeta];
-  int32_t N = 1;
-  while (N < n) N <<= 1;
-  for (int32_t x = threadIdx.x; x < N; x += blockDim.x)
-    s_key[x] = x < n ? ((((int64_t)1 << 23) - 1 - (key[base + x] >> 20)) << 20) |
-                           (key[base + x] & 0xFFFFF)
-                     : INT64_MAX;                      // ascending key = descending column
-  __syncthreads();
-  for (int32_t kk = 2; kk <= N; kk <<= 1)
-    for (int32_t j = kk >> 1; j > 0; j >>= 1) {
-      for (int32_t x = threadIdx.x; x < N; x += blockDim.x) {
-        const int32_t y = x ^ j;
-        if (y > x) {
-          const bool up = (x & kk) == 0;
-          const int64_t a = s_key[x], c = s_key[y];
-          if ((a > c) == up) {
-            s_key[x] = c;
-            s_key[y] = a;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  for (int32_t x = threadIdx.x; x < n; x += blockDim.x) {
-    const int64_t src = base + (s_key[x] & 0xFFFFF);
-    const int64_t d = base + x;
-    bl[2 * d] = bl_tmp[2 * src];
-    bl[2 * d + 1] = bl_tmp[2 * src + 1];
-    for (int q = 0; q < kWTd; q++) td[d * kWTd + q] = td_tmp[src * kWTd + q];
-  }
-  // live[x]: records whose last column is >= x (a prefix of the sorted list)
-  for (int32_t x = threadIdx.x; x < K; x += blockDim.x) {
-    int32_t lo = 0, hi = n;                              // first record with cm < x
-    while (lo < hi) {
-      const int32_t mid = (lo + hi) >> 1;
-      const int64_t cm = ((int64_t)1 << 23) - 1 - (s_key[mid] >> 20);
-      if (cm >= x)
-        lo = mid + 1;
-      else
-        hi = mid;
-    }
-    live[b * (int64_t)K + x] = lo;
-  }
-}
-
-// Per solve, row pushes: for row s of block b (source j = j0 + s) the
+// Row pushes: for row s of block b (source j = j0 + s) the
 // targets are the later rows of the block (slots 0..7, only s2 > s) and the
 // rows of block b + 1 (slots 8..15).  List layout: see kWp*.
-__global__ __launch_bounds__(64) void k_wide_push(int64_t F, int64_t nblk, int32_t Beff,
-                                                  const int32_t* w, const int64_t* row_off,
-                                                  const int64_t* rec_ptr, BlockRecords R,
-                                                  int32_t* push) {
-  const int64_t b = blockIdx.x;
-  const int s = threadIdx.x;
-  if (s >= kJB) return;
+__device__ void setup_push(int64_t b, int s, int64_t F, int64_t nblk, int32_t Beff,
+                           const int32_t* w, const int64_t* row_off, const int64_t* rec_ptr,
+                           const BlockRecords& R, int32_t* push) {
   const int64_t j0 = 1 + b * kJB;
   const int64_t j = j0 + s;
   int32_t* d = push + (b * kJB + s) * kWPush;
@@ -778,6 +794,34 @@ __global__ __launch_bounds__(64) void k_wide_push(int64_t F, int64_t nblk, int32
   d[kWpNear] = (int32_t)near_pairs;
 }
 
+// One launch for up to kSetupTables tables (y): blocks [0, nblk) the records,
+// [nblk, 2 nblk) the push lists of a block, the last one progress and ticket.
+// (Four launches per table, with the unsorted records through memory, took
+// 52 us on DenseNet-121; a sweep of 32 ResNet-50 tables 1.2 ms.)
+__global__ __launch_bounds__(256) void k_wide_setup(int32_t F, int64_t nblk, int32_t K,
+                                                    const int32_t* w, const int64_t* row_off,
+                                                    const int64_t* rec_ptr, BlockRecords R,
+                                                    const int64_t* wptr, SetupTables tabs,
+                                                    WSlab o) {
+  __shared__ uint64_t s_key[kWMaxRec];
+  __shared__ int32_t s_n, s_emax;
+  char* const slab = tabs.slab[blockIdx.y];
+  const int32_t Beff = tabs.Beff[blockIdx.y];
+  const int64_t x = blockIdx.x;
+  if (x < nblk) {
+    setup_records(x, F, K, Beff, w, row_off, rec_ptr, R, wptr, slab, o, s_key, &s_n, &s_emax);
+  } else if (x < 2 * nblk) {
+    if (threadIdx.x < kJB)
+      setup_push(x - nblk, threadIdx.x, F, nblk, Beff, w, row_off, rec_ptr, R,
+                 reinterpret_cast<int32_t*>(slab + o.push));
+  } else {
+    int32_t* progress = reinterpret_cast<int32_t*>(slab + o.progress);
+    for (int32_t k = threadIdx.x; k < K; k += blockDim.x)
+      progress[k] = 1;                      // the empty set's row is written by the init kernel
+    if (threadIdx.x == 0) *reinterpret_cast<int32_t*>(slab + o.ticket) = 0;
+  }
+}
+
 int64_t wait_ticks() {
   int dev = 0;
   int clock_khz = 0;
@@ -812,44 +856,51 @@ hipError_t launch_wide_count(rc_family f, int64_t* count, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Per-table preparation (records, pushes, progress) and kernel parameters.
-static hipError_t prepare_wide(rc_solution sol, int32_t K, int32_t* ticket, WParams* prm,
-                               hipStream_t s) {
-  rc_family f = sol->f;
-  hipLaunchKernelGGL(k_wide_init, dim3((K + 255) / 256), dim3(256), 0, s, sol->progress, K,
-                     ticket);
-  hipError_t pe = launch_fill_pending(sol, s);
-  if (pe == hipSuccess) pe = launch_pad_init(sol, s);
-  if (pe != hipSuccess) return pe;
-  const int64_t R = f->wrec_total;
-  hipLaunchKernelGGL(k_wide_prepare, dim3((unsigned)f->nblk), dim3(256), 0, s, (int32_t)f->F,
-                     (int32_t)sol->Beff, f->w, f->row_off, f->rec_ptr, f->rec, f->wrec_ptr,
-                     sol->wkey, sol->wbl_tmp, sol->wtd_tmp, sol->wmeta);
-  hipLaunchKernelGGL(k_wide_sort, dim3((unsigned)f->nblk), dim3(256), 0, s, K, f->wrec_ptr,
-                     sol->wkey, sol->wbl_tmp, sol->wtd_tmp, sol->wmeta, sol->wbl, sol->wtd,
-                     sol->wlive);
-  hipLaunchKernelGGL(k_wide_push, dim3((unsigned)f->nblk), dim3(64), 0, s, f->F, f->nblk,
-                     (int32_t)sol->Beff, f->w, f->row_off, f->rec_ptr, f->rec, sol->wpush);
-  pe = hipGetLastError();
-  if (pe != hipSuccess) return pe;
-  prm->F = (int32_t)f->F;
-  prm->nblk = (int32_t)f->nblk;
-  prm->K = K;
-  prm->meta = sol->wmeta;
-  prm->rptr = f->wrec_ptr;
-  prm->live = sol->wlive;
-  prm->bl = sol->wbl;
-  prm->td = sol->wtd;
-  prm->rec_cap = (int32_t)R;
-  prm->push = sol->wpush;
-  prm->m = sol->m;
-  prm->m_bytes = 2 * f->cells_alloc;
-  prm->null_off = (int32_t)(2 * f->cells);         // the trailing guard: kGuard infinite cells
-  prm->progress = sol->progress;
-  prm->ticket = ticket;
-  prm->st = sol->status;
-  prm->timeout_ticks = wait_ticks();
-  prm->jitter = jitter_seed();
+size_t wide_slab_bytes(rc_family f) { return (size_t)wide_slab(f).bytes; }
+
+// Preparation of nb tables (records, pushes, progress) and their kernel
+// parameters; every table takes its columns by the first one's ticket.
+static hipError_t prepare_wide(rc_solution* sols, int32_t nb, WParams* prm, hipStream_t s) {
+  rc_family f = sols[0]->f;
+  const int32_t K = (int32_t)wide_columns(f);
+  const WSlab o = wide_slab(f);
+  for (int32_t t0 = 0; t0 < nb; t0 += kSetupTables) {
+    SetupTables tabs{};
+    const int32_t n = std::min<int32_t>(kSetupTables, nb - t0);
+    for (int32_t t = 0; t < n; t++) {
+      tabs.slab[t] = sols[t0 + t]->wslab;
+      tabs.Beff[t] = (int32_t)sols[t0 + t]->Beff;
+    }
+    hipLaunchKernelGGL(k_wide_setup, dim3((unsigned)(2 * f->nblk + 1), (unsigned)n), dim3(256), 0,
+                       s, (int32_t)f->F, f->nblk, K, f->w, f->row_off, f->rec_ptr, f->rec,
+                       f->wrec_ptr, tabs, o);
+  }
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int64_t ticks = wait_ticks();
+  for (int32_t t = 0; t < nb; t++) {
+    char* slab = sols[t]->wslab;
+    auto at = [&](int64_t off) { return reinterpret_cast<int32_t*>(slab + off); };
+    WParams& q = prm[t];
+    q.F = (int32_t)f->F;
+    q.nblk = (int32_t)f->nblk;
+    q.K = K;
+    q.rec_cap = (int32_t)f->wrec_total;
+    q.meta = at(o.meta);
+    q.rptr = f->wrec_ptr;
+    q.live = at(o.live);
+    q.bl = at(o.bl);
+    q.td = at(o.td);
+    q.push = at(o.push);
+    q.m = sols[t]->m;
+    q.m_bytes = 2 * f->cells_alloc;
+    q.null_off = (int32_t)(2 * f->cells);          // the trailing guard: kGuard infinite cells
+    q.progress = at(o.progress);
+    q.ticket = reinterpret_cast<int32_t*>(sols[0]->wslab + o.ticket);
+    q.st = sols[t]->status;
+    q.timeout_ticks = ticks;
+    q.jitter = jitter_seed();
+  }
   return hipSuccess;
 }
 
@@ -877,25 +928,18 @@ static hipError_t launch_wide_kernel(const WParams& prm, const WParams* dev, int
 }
 
 hipError_t launch_fill_wide(rc_solution sol, hipStream_t s) {
-  rc_family f = sol->f;
-  if (f->F < 2) return hipSuccess;
-  const int32_t K = (int32_t)wide_columns(f);
+  if (sol->f->F < 2) return hipSuccess;
   WParams prm;
-  const hipError_t pe = prepare_wide(sol, K, sol->ticket, &prm, s);
+  const hipError_t pe = prepare_wide(&sol, 1, &prm, s);
   if (pe != hipSuccess) return pe;
   return launch_wide_kernel(prm, nullptr, 1, sol->evk0, sol->evk1, s);
 }
 
 hipError_t launch_fill_wide_batch(rc_solution* sols, int32_t nb, WParams* host_prm,
                                   WParams* dev_prm, hipStream_t s) {
-  rc_family f = sols[0]->f;
-  if (f->F < 2) return hipSuccess;
-  const int32_t K = (int32_t)wide_columns(f);
-  for (int32_t b = 0; b < nb; b++) {
-    // every table resets the shared ticket; they all run before the kernel
-    const hipError_t pe = prepare_wide(sols[b], K, sols[0]->ticket, &host_prm[b], s);
-    if (pe != hipSuccess) return pe;
-  }
+  if (sols[0]->f->F < 2) return hipSuccess;
+  const hipError_t pe = prepare_wide(sols, nb, host_prm, s);
+  if (pe != hipSuccess) return pe;
   const hipError_t ce = hipMemcpyAsync(dev_prm, host_prm, sizeof(WParams) * (size_t)nb,
                                        hipMemcpyHostToDevice, s);
   if (ce != hipSuccess) return ce;

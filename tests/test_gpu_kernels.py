@@ -123,3 +123,24 @@ def test_fill_switched_after_the_build(rc, oracle_mod, monkeypatch, name):
             for got, want in zip(sol.table(), ref):
                 assert (got == want).all(), path
             sol.free()
+
+
+@pytest.mark.parametrize("path", ["wide", "level", None])
+def test_sweep_of_many_budgets(rc, oracle_mod, monkeypatch, path):
+    """More tables than one preparation or selection launch takes, feasible
+    and infeasible, 16- and 32-bit cells side by side."""
+    if path:
+        monkeypatch.setenv("RCDP_FILL", path)
+    g = W.random_dag(9, 0.3, 12, tmax=60, mmax=9000)
+    top = 2 * sum(g.M)
+    assert top > 65532
+    budgets = [(j * top) // 69 for j in range(70)] + [65532, 65533]
+    fam = rc.Graph.create(g).build_family("exact")
+    for objective in ("tc", "mc"):
+        sols = fam.sweep(budgets, objective)
+        for B, sol in sols:
+            ref = oracle_mod.solve(g, "exact", B, objective)
+            assert (sol.t_star, sol.m_star) == (ref.t_star, ref.m_star), B
+            if ref.t_star >= 0 and B % 3 == 0:
+                assert sol.reconstruct().chain.tolist() == list(ref.schedule()[0])
+            sol.free()
