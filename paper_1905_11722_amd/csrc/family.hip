@@ -747,7 +747,9 @@ __global__ __launch_bounds__(256) void k_pair_count(int64_t F, int words, int64_
 // two sums over L & bd(L') depend on the pair; bd(L') is small: its nodes,
 // the same for every pair of the workgroup, are walked with their costs in
 // scalars while each thread tests its own L_i.  kMask: the pairs come from
-// k_pair_count's bits (prefix of their counts in LDS, no barrier per chunk).
+// k_pair_count's bits (prefix of their counts in LDS, no barrier per chunk),
+// and split (null: not wanted) gets, per target, its first pair from the sets
+// of the block of `rows` targets before its own, and from its own block.
 constexpr int64_t kMaskSets = 8192;      // families whose pair bits are kept (8 MB)
 
 template <bool kMask>
@@ -758,7 +760,7 @@ __global__ __launch_bounds__(256) void k_pair_write(
     const int32_t* __restrict__ Tbd, const int32_t* __restrict__ Mbd,
     const int32_t* __restrict__ A, const int32_t* __restrict__ T, const int32_t* __restrict__ M,
     const int64_t* __restrict__ pred_ptr, const uint64_t* __restrict__ mask, int64_t mw,
-    int32_t* pidx, int32_t* pdt, int32_t* pdm, int32_t* pc) {
+    int32_t* pidx, int32_t* pdt, int32_t* pdm, int32_t* pc, int32_t rows, int64_t* split) {
   const int64_t j = blockIdx.x;
   __shared__ int64_t base;
   __shared__ int32_t wave_cnt[4];
@@ -786,6 +788,17 @@ __global__ __launch_bounds__(256) void k_pair_write(
     base = p0;
   }
   __syncthreads();
+  if (kMask && split && threadIdx.x < 2 && j > 0) {
+    // first pair from the previous block's sets, and from the block's own
+    const int64_t j0 = 1 + (j - 1) / rows * rows;
+    const int64_t x = threadIdx.x == 0 ? max((int64_t)0, j0 - rows) : j0;
+    const uint64_t below = x / kWave * kWave < j
+                               ? mask[j * mw + x / kWave] & ((1ull << (x & (kWave - 1))) - 1)
+                               : 0ull;
+    const int nw = (int)((j + kWave - 1) / kWave);
+    split[2 * j + threadIdx.x] = x / kWave < nw ? p0 + s_pre[x / kWave] + __popcll(below)
+                                                : pred_ptr[j + 1];
+  }
   const int sj = size[j];
   const int64_t tj = (int64_t)Tsum[j] - Tbd[j], mbj = Mbd[j], cj = 2 * (int64_t)Msum[j] + A[j];
   for (int64_t i0 = 0; i0 < j; i0 += blockDim.x) {
@@ -877,21 +890,22 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(const int64_t* in, int64_
 // counted from the row end is made of whole 128-byte lines, and at least
 // kGuard padding cells separate it from the previous row), predecessor
 // offsets, the relaxation count, and what the host needs of them, written
-// straight to its pinned buffer (the status, sizes, widths and both offset
-// arrays at the byte offsets of o).
+// straight to its pinned buffer (the status, sizes, widths, both offset
+// arrays and M(L) at the byte offsets of o).
 struct ShapeOut {
   char* host;
-  int64_t o_st, o_size, o_w, o_off, o_pp;
+  int64_t o_st, o_size, o_w, o_off, o_pp, o_msum;
 };
 
 __global__ __launch_bounds__(kScanThreads) void k_shape(int64_t F, const int32_t* size,
-                                                        const int32_t* w, const int64_t* counts,
+                                                        const int32_t* w, const int32_t* Msum, const int64_t* counts,
                                                         const int64_t* walg, int64_t* row_off,
                                                         int64_t* pred_ptr, DevStatus* st,
                                                         ShapeOut o) {
   __shared__ int64_t s_part[kScanThreads / kWave];
   int32_t* h_size = reinterpret_cast<int32_t*>(o.host + o.o_size);
   int32_t* h_w = reinterpret_cast<int32_t*>(o.host + o.o_w);
+  int32_t* h_msum = reinterpret_cast<int32_t*>(o.host + o.o_msum);
   int64_t* h_off = reinterpret_cast<int64_t*>(o.host + o.o_off);
   int64_t* h_pp = reinterpret_cast<int64_t*>(o.host + o.o_pp);
   int64_t cells = 0, pairs = 0, relax = 0;
@@ -913,6 +927,7 @@ __global__ __launch_bounds__(kScanThreads) void k_shape(int64_t F, const int32_t
       h_pp[i] = pp;
       h_size[i] = size[i];
       h_w[i] = wi;
+      h_msum[i] = Msum[i];
     }
   }
   if (threadIdx.x == 0) {
@@ -1044,10 +1059,10 @@ hipError_t launch_pair_count(rc_family f, int64_t* counts, int64_t* walg, uint64
 }
 
 hipError_t launch_shape(rc_family f, const int64_t* counts, const int64_t* walg, char* host,
-                        const int64_t (&o)[5], hipStream_t s) {
-  hipLaunchKernelGGL(k_shape, dim3(1), dim3(kScanThreads), 0, s, f->F, f->size, f->w, counts, walg,
-                     f->row_off, f->pred_ptr, f->status,
-                     ShapeOut{host, o[0], o[1], o[2], o[3], o[4]});
+                        const int64_t (&o)[6], hipStream_t s) {
+  hipLaunchKernelGGL(k_shape, dim3(1), dim3(kScanThreads), 0, s, f->F, f->size, f->w, f->Msum,
+                     counts, walg, f->row_off, f->pred_ptr, f->status,
+                     ShapeOut{host, o[0], o[1], o[2], o[3], o[4], o[5]});
   return hipGetLastError();
 }
 
@@ -1062,7 +1077,8 @@ hipError_t launch_pair_write(rc_family f, const uint64_t* mask, hipStream_t s) {
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)f->F), dim3(256), 0, s, f->F, g->words, f->fstride,
                        f->bits, f->bd, f->size, f->Tsum, f->Msum, f->Tbd, f->Mbd, f->A, g->dT,
-                       g->dM, f->pred_ptr, mask, mw, f->pidx, f->pdt, f->pdm, f->pc);
+                       g->dM, f->pred_ptr, mask, mw, f->pidx, f->pdt, f->pdm, f->pc, f->dual_rows,
+                       f->dual_split);
   };
   if (mask)
     go(k_pair_write<true>);

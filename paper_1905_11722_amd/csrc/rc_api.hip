@@ -540,12 +540,12 @@ static int build_family_impl(rc_family f, int64_t max_sets, hipStream_t s) {
   StageLayout L1;
   const size_t o_st = L1.add<DevStatus>(1), o_size = L1.add<int32_t>(F),
                o_w = L1.add<int32_t>(F), o_off = L1.add<int64_t>(F + 1),
-               o_pp = L1.add<int64_t>(F + 1);
+               o_pp = L1.add<int64_t>(F + 1), o_ms = L1.add<int32_t>(F);
   {
     Staging st1(L1.bytes);
     if (!st1.data()) return RC_E_NOMEM;
-    const int64_t o[5] = {(int64_t)o_st, (int64_t)o_size, (int64_t)o_w, (int64_t)o_off,
-                          (int64_t)o_pp};
+    const int64_t o[6] = {(int64_t)o_st,  (int64_t)o_size, (int64_t)o_w,
+                          (int64_t)o_off, (int64_t)o_pp,   (int64_t)o_ms};
     st1.in_flight();
     RC_HIP(launch_shape(f, counts, walg, st1.data(), o, s));
     const int ss = sync_landed(st1, s);
@@ -592,10 +592,15 @@ static int build_family_impl(rc_family f, int64_t max_sets, hipStream_t s) {
     f->block_pairs = 0;
     for (int64_t j = 1; j < F; j += kJB)
       f->block_pairs = std::max(f->block_pairs, pp_h[std::min<int64_t>(j + kJB, F)] - pp_h[j]);
+    if (mask) f->dual_rows = dual_block_rows(F, st1.at<int32_t>(o_ms), &f->dual_halo);
   }
 
   // ---- a4: the pairs themselves
   const int64_t P = f->P;
+  if (f->dual_rows > 0) {
+    f->dual_split = A.get_n<int64_t>(2 * F);
+    if (!f->dual_split) return RC_E_NOMEM;
+  }
   f->pidx = A.get_n<int32_t>(P);
   f->pdt = A.get_n<int32_t>(P);
   f->pdm = A.get_n<int32_t>(P);

@@ -166,6 +166,12 @@ struct rc_family_s {
   // device: predecessor pairs, CSR by target
   int64_t* pred_ptr = nullptr;    // [F+1]
   int32_t *pidx = nullptr, *pdt = nullptr, *pdm = nullptr, *pc = nullptr;
+  // memory-indexed table by blocks (dual.hip): rows per block (0: never), each
+  // block's halo, and per target its first pair from the previous block's
+  // sets and from its own block's
+  int32_t dual_rows = 0;
+  std::vector<int32_t> dual_halo;
+  int64_t* dual_split = nullptr;  // [2 F]
   rcdp::LevelPair* lpair = nullptr; // [P] the level fill's pair records (built on first use)
   // blocked fill: records per block of at most kJB targets (absent when too large)
   int32_t blk_kind = 0;           // kBlocksFixed or kBlocksGhost (0: no records)
@@ -295,7 +301,7 @@ int64_t pair_mask_words(rc_family f);
 hipError_t launch_pair_count(rc_family f, int64_t* counts, int64_t* walg, uint64_t* mask,
                              hipStream_t s);
 hipError_t launch_shape(rc_family f, const int64_t* counts, const int64_t* walg, char* host,
-                        const int64_t (&o)[5], hipStream_t s);
+                        const int64_t (&o)[6], hipStream_t s);
 hipError_t launch_scan(const int64_t* in, int64_t* out, int64_t count, hipStream_t s);
 hipError_t launch_pair_write(rc_family f, const uint64_t* mask, hipStream_t s);
 
@@ -390,6 +396,7 @@ hipError_t launch_min_budget(rc_family f, int32_t hi0, uint32_t* scratch, hipStr
 hipError_t launch_dual(rc_family f, const std::vector<int64_t>& level_pairs, int32_t B, int32_t W,
                        int objective, uint32_t* D, DevStatus* st, DevStatus* host, hipEvent_t e0,
                        hipEvent_t e1, hipStream_t s);
+int32_t dual_block_rows(int64_t F, const int32_t* Msum, std::vector<int32_t>* halo);
 int64_t blocked_columns(rc_family f);
 
 // One memory-indexed solve (rc_api.hip): the sizes it needs and the device

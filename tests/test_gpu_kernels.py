@@ -7,6 +7,7 @@ import pytest
 from paper_1905_11722_amd import workloads as W
 
 from tests.test_gpu_dominance import compare as compare_dominance
+from tests.test_gpu_dual import check as check_dual
 from tests.test_gpu_parity import compare
 
 pytestmark = pytest.mark.gpu
@@ -144,3 +145,19 @@ def test_sweep_of_many_budgets(rc, oracle_mod, monkeypatch, path):
             if ref.t_star >= 0 and B % 3 == 0:
                 assert sol.reconstruct().chain.tolist() == list(ref.schedule()[0])
             sol.free()
+
+
+@pytest.mark.parametrize("nodes,mmax", [(2, 9), (7, 9), (8, 9), (9, 60), (16, 60), (17, 170),
+                                        (40, 170), (33, 300), (40, 380), (24, 900)])
+def test_dual_blocks(rc, nodes, mmax):
+    """The memory-indexed table by blocks of eight and of four targets and by
+    levels (the halo too wide for either), rows of up to many columns, blocks
+    cut short at the end, budgets that close some pairs."""
+    g = W.chain(nodes, seed=nodes, tmax=50, mmax=mmax)
+    check_dual(rc, g, "pruned", (2 * max(g.M), sum(g.M), 2 * sum(g.M)))
+
+
+def test_dual_blocks_branching(rc):
+    """Blocks whose sets are not all nested."""
+    g = W.random_dag(60, 0.08, 5, tmax=40, mmax=30)
+    check_dual(rc, g, "pruned", (sum(g.M), (3 * sum(g.M)) // 2, 2 * sum(g.M)))
