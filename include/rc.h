@@ -41,9 +41,11 @@
  * Environment switches (read when a family is built or a table is solved;
  * none changes a result, only which kernels compute it and how they are
  * shaped; an unrecognised value is ignored):
- *  - RCDP_FILL = level | wavefront | wide | ghost: the fill of Algorithm 1.
- *    level: one launch per group of equal-size sets (k_fill_level_vec on
- *    16-bit cells, k_fill_level on 32-bit cells).
+ *  - RCDP_FILL = level | block | wavefront | wide | ghost: the fill of
+ *    Algorithm 1.  level: one launch per group of equal-size sets
+ *    (k_fill_level_vec; rows beyond 2^31 bytes take k_fill_level).  block: one
+ *    launch per 16 consecutive sets (k_fill_block; families whose shifts
+ *    inside a block reach at most 864 cells, level otherwise).
  *    wavefront: the persistent row-push wavefront over fixed blocks of
  *    targets (k_fill_blocked).  wide: the split-panel wavefront over fixed
  *    blocks (k_fill_wide).  ghost: the wavefront over ghost-zone blocks
@@ -296,17 +298,16 @@ int rc_solve_batch(rc_family f, const int64_t* B_host, int32_t nb, int32_t objec
 int rc_solution_fill_ms(rc_solution s, float* ms);
 /* Milliseconds between HIP events recorded on the solve's stream just
  * before and just after the one wavefront kernel of the blocked fill
- * (without the kernels that prepare its records).  On the level path,
- * which runs one launch per group of equal-size sets, this equals
- * rc_solution_fill_ms.  Returns RC_OK or RC_E_ARG (NULL argument). */
+ * (without the kernels that prepare its records).  On the level and block
+ * paths, which run many launches, this equals rc_solution_fill_ms.  Returns RC_OK or RC_E_ARG (NULL argument). */
 int rc_solution_fill_kernel_ms(rc_solution s, float* ms);
 /* Which fill the solve ran (all of them compute the same table, Algorithm 1
  * of Section 4.2): *path = 0 one launch per group of equal-size sets on
  * 16-bit cells (k_fill_level_vec), 1 the persistent row-push wavefront
  * (k_fill_blocked), 2 the ghost-zone wavefront (k_fill_ghost), 3 the
  * split-panel wavefront (k_fill_wide), 4 one launch per group of equal-size
- * sets on 32-bit cells (k_fill_level).  Returns RC_OK or RC_E_ARG (NULL
- * argument). */
+ * sets on 32-bit cells, 5 one launch per block of 16 sets (k_fill_block).
+ * Returns RC_OK or RC_E_ARG (NULL argument). */
 int rc_solution_fill_path(rc_solution s, int32_t* path);
 /* Which traceback the last rc_reconstruct of the handle ran (both follow
  * the optarg rule of Section 4.2 and give the same chain): *path = 0 a

@@ -748,8 +748,13 @@ __global__ __launch_bounds__(256) void k_pair_count(int64_t F, int words, int64_
 // the same for every pair of the workgroup, are walked with their costs in
 // scalars while each thread tests its own L_i.  kMask: the pairs come from
 // k_pair_count's bits (prefix of their counts in LDS, no barrier per chunk),
-// and split (null: not wanted) gets, per target, its first pair from the sets
-// of the block of `rows` targets before its own, and from its own block.
+// and sp gets, per target, its first pair from the sets of the block of
+// `rows` targets before its own, and from its own block (two block sizes; a
+// null array is not wanted).
+struct PairSplit {
+  int32_t rows[2];
+  int64_t* split[2];
+};
 constexpr int64_t kMaskSets = 8192;      // families whose pair bits are kept (8 MB)
 
 template <bool kMask>
@@ -760,7 +765,7 @@ __global__ __launch_bounds__(256) void k_pair_write(
     const int32_t* __restrict__ Tbd, const int32_t* __restrict__ Mbd,
     const int32_t* __restrict__ A, const int32_t* __restrict__ T, const int32_t* __restrict__ M,
     const int64_t* __restrict__ pred_ptr, const uint64_t* __restrict__ mask, int64_t mw,
-    int32_t* pidx, int32_t* pdt, int32_t* pdm, int32_t* pc, int32_t rows, int64_t* split) {
+    int32_t* pidx, int32_t* pdt, int32_t* pdm, int32_t* pc, PairSplit sp) {
   const int64_t j = blockIdx.x;
   __shared__ int64_t base;
   __shared__ int32_t wave_cnt[4];
@@ -788,15 +793,16 @@ __global__ __launch_bounds__(256) void k_pair_write(
     base = p0;
   }
   __syncthreads();
-  if (kMask && split && threadIdx.x < 2 && j > 0) {
+  if (kMask && threadIdx.x < 4 && j > 0 && sp.split[threadIdx.x / 2]) {
     // first pair from the previous block's sets, and from the block's own
+    const int32_t rows = sp.rows[threadIdx.x / 2];
     const int64_t j0 = 1 + (j - 1) / rows * rows;
-    const int64_t x = threadIdx.x == 0 ? max((int64_t)0, j0 - rows) : j0;
+    const int64_t x = threadIdx.x % 2 == 0 ? max((int64_t)0, j0 - rows) : j0;
     const uint64_t below = x / kWave * kWave < j
                                ? mask[j * mw + x / kWave] & ((1ull << (x & (kWave - 1))) - 1)
                                : 0ull;
     const int nw = (int)((j + kWave - 1) / kWave);
-    split[2 * j + threadIdx.x] = x / kWave < nw ? p0 + s_pre[x / kWave] + __popcll(below)
+    sp.split[threadIdx.x / 2][2 * j + threadIdx.x % 2] = x / kWave < nw ? p0 + s_pre[x / kWave] + __popcll(below)
                                                 : pred_ptr[j + 1];
   }
   const int sj = size[j];
@@ -1077,8 +1083,8 @@ hipError_t launch_pair_write(rc_family f, const uint64_t* mask, hipStream_t s) {
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)f->F), dim3(256), 0, s, f->F, g->words, f->fstride,
                        f->bits, f->bd, f->size, f->Tsum, f->Msum, f->Tbd, f->Mbd, f->A, g->dT,
-                       g->dM, f->pred_ptr, mask, mw, f->pidx, f->pdt, f->pdm, f->pc, f->dual_rows,
-                       f->dual_split);
+                       g->dM, f->pred_ptr, mask, mw, f->pidx, f->pdt, f->pdm, f->pc,
+                       PairSplit{{f->dual_rows, block_fill_rows()}, {f->dual_split, f->fb_split}});
   };
   if (mask)
     go(k_pair_write<true>);

@@ -250,24 +250,22 @@ __device__ __forceinline__ LevelCells<T> load_cells(const char* base, int32_t of
   return r;
 }
 
+// Tile `tile` of target j, over its pairs [p0, p1); the whole workgroup calls
+// it.  s_acc: NW - 1 waves of LDS.
 template <class T, int NW>
-__global__ __launch_bounds__(NW * kWave) void k_fill_level_vec(
-    int64_t lb, const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
-    const int64_t* __restrict__ pred_ptr, const LevelPair* __restrict__ lp, int32_t Beff,
-    T* __restrict__ m) {
+__device__ __forceinline__ void level_tile(int32_t tile, int32_t wj, int64_t rj,
+                                           int64_t p0, int64_t p1,
+                                           const LevelPair* __restrict__ lp, int32_t Beff,
+                                           T* m, LevelCells<T> (*s_acc)[kWave]) {
   constexpr int kB = (int)sizeof(T);
   constexpr int kVec = 16 / kB;
   constexpr int kTileCells = kWave * kVec;
-  __shared__ LevelCells<T> s_acc[NW > 1 ? NW - 1 : 1][kWave];
-  const int64_t j = lb + blockIdx.y;
-  const int32_t wj = w[j];
-  const int32_t hi_t = wj - (int32_t)blockIdx.x * kTileCells;    // the tile is [hi_t - kTileCells, hi_t)
+  const int32_t hi_t = wj - tile * kTileCells;                   // the tile is [hi_t - kTileCells, hi_t)
   if (hi_t <= 0) return;                                         // the whole workgroup leaves
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
   const int32_t t0 = hi_t - kVec * (lane + 1);                   // the lane's first cell
   LevelCells<T> acc = {{~0u, ~0u, ~0u, ~0u}};
-  const int64_t p0 = pred_ptr[j], p1 = pred_ptr[j + 1];
   typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
   typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
   auto record = [&](int64_t p, i32x4& a, i32x2& b) {
@@ -336,7 +334,185 @@ __global__ __launch_bounds__(NW * kWave) void k_fill_level_vec(
     for (int c = 0; c < kVec; c++)
       if (t0 + c < 0) o.c[c] = (T)cell_inf<T>();
   }
-  *reinterpret_cast<uint4*>(m + row_off[j] + t0) = o.q;
+  *reinterpret_cast<uint4*>(m + rj + t0) = o.q;
+}
+
+template <class T, int NW>
+__global__ __launch_bounds__(NW * kWave) void k_fill_level_vec(
+    int64_t lb, const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
+    const int64_t* __restrict__ pred_ptr, const LevelPair* __restrict__ lp, int32_t Beff,
+    T* __restrict__ m) {
+  __shared__ LevelCells<T> s_acc[NW > 1 ? NW - 1 : 1][kWave];
+  const int64_t j = lb + blockIdx.y;
+  level_tile<T, NW>((int32_t)blockIdx.x, w[j], row_off[j], pred_ptr[j], pred_ptr[j + 1], lp, Beff,
+                    m, s_acc);
+}
+
+// The block fill, for narrow tables of many levels: one launch per kFbRows
+// consecutive targets.  Rows are right-aligned, x = the distance of a cell
+// from its row's end; along a pair the target cell x reads the source cell
+// x - e, e = P_j - P_i - dt >= 0 (P = w - 1).  Launch b has two kinds of
+// workgroups, beside each other:
+//  - panel (block b + 1): the pairs from sources before block b, final by now,
+//    as a tile of the level fill; the minima lie in the table itself;
+//  - rows (block b): for kFbOwn cells, the rows start from their panel (the
+//    launch before), take the pairs from the previous block's rows, then
+//    finish one after the other in LDS, each relaxing the later rows.
+// A step reads cells closer to the row's end only, so a rows workgroup
+// recomputes the `halo` cells to the right of its own instead of waiting for
+// their owner: along a path inside the block the shifts sum to at most
+// P_last - P_first (every dt >= 0), and the host passes the largest
+// difference of P over the block.  Halo cells are stored final by their owner
+// meanwhile; reading either value gives the same minimum.
+//
+// A slot of one wave per target, a lane up to kFbK cells, in registers; one
+// barrier per row.  Bound by a launch's chain of cold loads and by the
+// instructions of the sixteen waves of a rows workgroup, so few own cells and
+// many workgroups are best although they repeat more of the halo:
+// densenet121_t10 (27 blocks, halos of 31 to 271 cells) 0.29 ms with 32 own
+// cells, 0.32 with 64, 0.42 with 128, 0.54 with 256; the split-panel
+// wavefront, 2 us a row whatever the row's length, 0.92.
+constexpr int kFbRows = 16;
+constexpr int kFbOwn = 32;
+constexpr int kFbK = 14;
+constexpr int kFbSpan = kFbK * kWave;
+constexpr int kFbHalo = kFbSpan - kFbOwn;
+constexpr int kFbThreads = kFbRows * kWave;
+
+struct FbTables {
+  uint16_t* m[kTables];
+  int32_t Beff[kTables];
+};
+struct FbBlock {
+  int64_t j0, j1;             // rows of the block
+  int64_t n0, n1;             // rows of the next block
+  int32_t halo, row_blocks;   // rows workgroups
+  int32_t tiles;              // panel: tiles of a target
+};
+
+__global__ __launch_bounds__(kFbThreads) void k_fill_block(
+    FbTables tabs, FbBlock g, const int32_t* __restrict__ w, const int64_t* __restrict__ row_off,
+    const int64_t* __restrict__ pred_ptr, const int64_t* __restrict__ split,
+    const int32_t* __restrict__ pidx, const int32_t* __restrict__ pdt,
+    const int32_t* __restrict__ pdm, const int32_t* __restrict__ pc,
+    const LevelPair* __restrict__ lp) {
+  __shared__ LevelCells<uint16_t> s_acc[kFbRows - 1][kWave];
+  __shared__ uint16_t s_row[kFbRows][kFbSpan];
+  __shared__ int4 s_tri[kFbRows][kFbRows];      // [target][source] e, dm, B - c (-1: none)
+  uint16_t* const m = tabs.m[blockIdx.y];
+  const int32_t Beff = tabs.Beff[blockIdx.y];
+  const int tid = threadIdx.x;
+  if ((int32_t)blockIdx.x >= g.row_blocks) {
+    const int32_t item = (int32_t)blockIdx.x - g.row_blocks;
+    const int64_t j = g.n0 + item / g.tiles;
+    level_tile<uint16_t, kFbRows>(item % g.tiles, w[j], row_off[j], pred_ptr[j], split[2 * j], lp,
+                                  Beff, m, s_acc);
+    return;
+  }
+  const int slot = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int lane = tid & (kWave - 1);
+  const int nrows = (int)(g.j1 - g.j0);
+  const int64_t j = g.j0 + slot;
+  const int32_t x0 = (int32_t)blockIdx.x * kFbOwn;
+  const int32_t xb = max(0, x0 - g.halo);                 // first cell computed
+  const int32_t cells = x0 + kFbOwn - xb;                 // at most kFbSpan
+  if (tid < kFbRows * kFbRows) s_tri[tid / kFbRows][tid % kFbRows].z = -1;
+  uint32_t acc[kFbK];
+#pragma unroll
+  for (int k = 0; k < kFbK; k++) acc[k] = kInfM;
+  __syncthreads();
+  int32_t wj = 0;
+  int64_t end = 0;
+  if (slot < nrows) {
+    wj = w[j];
+    end = row_off[j] + wj - 1;
+    const int64_t p1 = split[2 * j], p2 = split[2 * j + 1], p3 = pred_ptr[j + 1];
+    // lane q: the q-th pair from the previous block's rows, and from the block's
+    int32_t cend = 0, ce = 0, cp = 0, cdm = 0, ctau = -1;
+    if (lane < (int)(p2 - p1)) {
+      const int32_t i = pidx[p1 + lane];
+      const int32_t wi = w[i];
+      cend = (int32_t)(row_off[i] + wi - 1);
+      ce = wj - wi - pdt[p1 + lane];
+      cp = wi;
+      cdm = pdm[p1 + lane];
+      ctau = Beff - pc[p1 + lane];
+    }
+    if (lane < (int)(p3 - p2)) {
+      const int64_t p = p2 + lane;
+      const int32_t i = pidx[p];
+      s_tri[slot][i - g.j0] = make_int4(wj - w[i] - pdt[p], pdm[p], Beff - pc[p], 0);
+    }
+    if (g.j0 > 1) {                                       // block 0 has no panel
+#pragma unroll
+      for (int k = 0; k < kFbK; k++) {
+        const int x = xb + lane + kWave * k;
+        if (kWave * k < cells) acc[k] = m[end - min(x, wj)];   // x = wj: padding, infinite
+      }
+    }
+    // the pairs from the previous block for H cells of a lane, their sixteen
+    // loads each in flight together; a source cell outside its row is read in
+    // its padding
+    const int nc = (int)(p2 - p1);
+    auto cross = [&](auto H, uint32_t* a, int32_t x) __attribute__((always_inline)) {
+      constexpr int kH = decltype(H)::value;
+      uint32_t v[kH][kFbRows];
+#pragma unroll
+      for (int q = 0; q < kFbRows; q++) {
+        const int32_t e = __builtin_amdgcn_readlane(ce, q);
+        const int32_t pe = __builtin_amdgcn_readlane(cp, q);
+        const int32_t qe = __builtin_amdgcn_readlane(cend, q);
+#pragma unroll
+        for (int h = 0; h < kH; h++) v[h][q] = m[qe - min(max(x + kWave * h - e, -1), pe)];
+      }
+#pragma unroll
+      for (int q = 0; q < kFbRows; q++) {
+        const int32_t tau = __builtin_amdgcn_readlane(ctau, q);     // -1 past the list
+        const uint32_t dm = (uint32_t)__builtin_amdgcn_readlane(cdm, q);
+#pragma unroll
+        for (int h = 0; h < kH; h++)
+          a[h] = min(a[h], (int32_t)v[h][q] <= tau ? v[h][q] + dm : kInfM);
+      }
+    };
+    if (nc > 0) {
+      if (cells <= kWave) {
+        cross(std::integral_constant<int, 1>{}, &acc[0], xb + lane);
+      } else {
+#pragma unroll
+        for (int k = 0; k < kFbK; k += 2) {
+          if (kWave * k >= cells) break;
+          cross(std::integral_constant<int, 2>{}, &acc[k], xb + lane + kWave * k);
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kFbK; k++)
+      if (xb + lane + kWave * k >= wj) acc[k] = kInfM;
+  }
+  for (int s = 0; s < nrows; s++) {
+    if (slot == s) {                                      // the row is final
+#pragma unroll
+      for (int k = 0; k < kFbK; k++) {
+        if (kWave * k >= cells) break;
+        const int y = lane + kWave * k;
+        s_row[s][y] = (uint16_t)acc[k];
+        const int x = xb + y;
+        if (x >= x0 && y < cells && x < wj) m[end - x] = (uint16_t)acc[k];
+      }
+    }
+    __syncthreads();
+    if (slot <= s || slot >= nrows) continue;
+    const int4 pr = s_tri[slot][s];
+    if (pr.z < 0) continue;
+#pragma unroll
+    for (int k = 0; k < kFbK; k++) {
+      if (kWave * k >= cells) break;
+      const int y = lane + kWave * k - pr.x;              // left of the window: not needed
+      const uint32_t v = y >= 0 ? s_row[s][y] : kInfM;
+      if ((int32_t)v <= pr.z && xb + lane + kWave * k < wj)
+        acc[k] = min(acc[k], v + (uint32_t)pr.y);
+    }
+  }
 }
 
 // The level fill's record of each pair (built once per family).
@@ -1001,6 +1177,56 @@ static hipError_t ensure_level_pairs(rc_family f, hipStream_t s) {
   if (!f->lpair) return hipErrorOutOfMemory;
   hipLaunchKernelGGL(k_level_pairs, dim3((unsigned)((f->P + 255) / 256)), dim3(256), 0, s, f->P,
                      f->pidx, f->pdt, f->pdm, f->pc, f->w, f->row_off, f->lpair);
+  return hipGetLastError();
+}
+
+// The halo of every block of the block fill; empty where one leaves a
+// workgroup's window or the pair bits were not kept.
+void block_fill_halos(rc_family f) {
+  f->fb_halo.clear();
+  for (int64_t j = 1; j < f->F; j += kFbRows) {
+    const auto mm = std::minmax_element(f->w_host.begin() + j,
+                                        f->w_host.begin() + std::min<int64_t>(j + kFbRows, f->F));
+    const int32_t halo = *mm.second - *mm.first;
+    if (halo > kFbHalo) {
+      f->fb_halo.clear();
+      return;
+    }
+    f->fb_halo.push_back(halo);
+  }
+}
+int32_t block_fill_rows() { return kFbRows; }
+
+hipError_t launch_fill_block(const rc_solution* sols, int32_t nb, hipStream_t s) {
+  rc_family f = sols[0]->f;
+  const hipError_t e = ensure_level_pairs(f, s);
+  if (e != hipSuccess) return e;
+  const int64_t nblk = (int64_t)f->fb_halo.size();
+  auto start = [&](int64_t b) { return std::min<int64_t>(1 + b * kFbRows, f->F); };
+  auto widest = [&](int64_t a, int64_t b) {
+    return b > a ? *std::max_element(f->w_host.begin() + a, f->w_host.begin() + b) : 0;
+  };
+  for (int32_t t0 = 0; t0 < nb; t0 += kTables) {
+    FbTables tabs{};
+    const int32_t n = std::min<int32_t>(kTables, nb - t0);
+    for (int32_t t = 0; t < n; t++) {
+      tabs.m[t] = sols[t0 + t]->m;
+      tabs.Beff[t] = (int32_t)sols[t0 + t]->Beff;
+    }
+    for (int64_t b = 0; b < nblk; b++) {
+      FbBlock g{};
+      g.j0 = start(b);
+      g.j1 = g.n0 = start(b + 1);
+      g.n1 = start(b + 2);
+      g.halo = f->fb_halo[(size_t)b];
+      g.row_blocks = (widest(g.j0, g.j1) + kFbOwn - 1) / kFbOwn;
+      constexpr int kTileCells = kWave * 8;
+      g.tiles = std::max(1, (widest(g.n0, g.n1) + kTileCells - 1) / kTileCells);
+      const dim3 grid((unsigned)(g.row_blocks + (g.n1 - g.n0) * g.tiles), (unsigned)n);
+      hipLaunchKernelGGL(k_fill_block, grid, dim3(kFbThreads), 0, s, tabs, g, f->w, f->row_off,
+                         f->pred_ptr, f->fb_split, f->pidx, f->pdt, f->pdm, f->pc, f->lpair);
+    }
+  }
   return hipGetLastError();
 }
 

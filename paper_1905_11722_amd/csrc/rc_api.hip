@@ -453,7 +453,7 @@ static int sync_landed(Staging& st, hipStream_t s) {
 }
 
 static int ensure_records(rc_family f, hipStream_t s);
-static bool level_is_default(rc_family f);
+static int launch_fill_choice(rc_family f);
 
 static int build_family_impl(rc_family f, int64_t max_sets, hipStream_t s) {
   rc_graph g = f->g;
@@ -592,7 +592,10 @@ static int build_family_impl(rc_family f, int64_t max_sets, hipStream_t s) {
     f->block_pairs = 0;
     for (int64_t j = 1; j < F; j += kJB)
       f->block_pairs = std::max(f->block_pairs, pp_h[std::min<int64_t>(j + kJB, F)] - pp_h[j]);
-    if (mask) f->dual_rows = dual_block_rows(F, st1.at<int32_t>(o_ms), &f->dual_halo);
+    if (mask) {
+      f->dual_rows = dual_block_rows(F, st1.at<int32_t>(o_ms), &f->dual_halo);
+      if (f->cells_alloc < (int64_t)1 << 30) block_fill_halos(f);
+    }
   }
 
   // ---- a4: the pairs themselves
@@ -600,6 +603,10 @@ static int build_family_impl(rc_family f, int64_t max_sets, hipStream_t s) {
   if (f->dual_rows > 0) {
     f->dual_split = A.get_n<int64_t>(2 * F);
     if (!f->dual_split) return RC_E_NOMEM;
+  }
+  if (!f->fb_halo.empty()) {
+    f->fb_split = A.get_n<int64_t>(2 * F);
+    if (!f->fb_split) return RC_E_NOMEM;
   }
   f->pidx = A.get_n<int32_t>(P);
   f->pdt = A.get_n<int32_t>(P);
@@ -612,7 +619,7 @@ static int build_family_impl(rc_family f, int64_t max_sets, hipStream_t s) {
   // this family's fill or most budgets take 32-bit cells (then the first
   // solve that needs them builds them)
   f->blk_kind = family_block_kind(f);
-  if (f->blk_kind != 0 && 2 * g->M_total <= kMaxBudget && !level_is_default(f)) {
+  if (f->blk_kind != 0 && 2 * g->M_total <= kMaxBudget && launch_fill_choice(f) < 0) {
     const int er = ensure_records(f, s);
     if (er != RC_OK) return er;
   }
@@ -903,23 +910,32 @@ static void destroy_events(rc_solution sol) {
     }
 }
 
-// The level launches against the family's wavefront, by their measured costs
-// on this GPU.  The wavefront runs its 256-cell columns at most three (the
-// split-panel fill: four) per compute unit at a time, each through every row
-// of the table at about 2.5 us per row.  A level launch costs about 4 us,
-// plus the source reads of its pairs (2 bytes per relaxation) at about
-// 6 TB/s, partly beside each other.  Few levels of many sets or of very long
-// rows take the level launches (ms, level against wavefront: ladder40
-// 0.17 / 0.49, layered36 1.7, U-Net 0.44 / 1.05), many levels the wavefront
-// (ResNet-50 0.85 / 0.61).
-static bool level_is_cheaper(rc_family f) {
+// The cheapest fill of a family by measured costs on this GPU: 0 the level
+// launches, 5 the block launches, 3 the family's wavefront.  The wavefront
+// runs its 256-cell columns at most three (the split-panel fill: four) per
+// compute unit at a time, each through every row of the table at about 2.5 us
+// per row (2 us where only a few columns run).  A level launch costs about
+// 3.5 us, plus the source reads of its pairs (2 bytes per relaxation) at about
+// 6 TB/s, partly beside each other; a block launch of 16 rows about 9.5 us,
+// 27 ns per cell of its halo and the same reads.  Few levels of many sets or of
+// very long rows take the level launches, many levels of short rows the
+// blocks, of long ones the wavefront (ms, level / block / wavefront:
+// densenet121_t10 2.24 / 0.29 / 0.92, resnet50_t10 0.66 / 0.12 / 0.34, a
+// 16-node chain 0.046 / 0.013 / 0.039, layered24 0.077 / 0.084 / 0.11,
+// ladder40 0.16 / 0.35 / 0.53, U-Net 0.44 / - / 0.65, ResNet-50 0.86 / - /
+// 0.63, DenseNet-121 4.0 / - / 1.7).
+static int cheapest_fill(rc_family f) {
   const int64_t levels = (int64_t)f->level_ptr.size() - 1;
   const int64_t slots = (f->blk_kind == kBlocksGhost ? 3 : wide_slots_per_cu(3)) *
                         (int64_t)num_cus();
   const int64_t col_rounds = ((f->max_row + kWC - 1) / kWC + slots - 1) / slots;
+  const double reads = 2.0 * (double)f->relax / 6.0e6;
   const double wave_us = 2.5 * (double)f->F * (double)col_rounds;
-  const double level_us = 4.0 * (double)levels + 2.0 * (double)f->relax / 6.0e6;
-  return level_us < wave_us;
+  const double level_us = 3.5 * (double)levels + reads;
+  double block_us = reads;
+  for (int32_t h : f->fb_halo) block_us += 9.5 + 0.027 * (double)h;
+  if (!f->fb_halo.empty() && block_us < wave_us && block_us < level_us) return 5;
+  return level_us < wave_us ? 0 : 3;
 }
 
 static bool forces_wavefront(const char* env) {
@@ -927,17 +943,27 @@ static bool forces_wavefront(const char* env) {
                  std::strcmp(env, "ghost") == 0);
 }
 
-static bool level_is_default(rc_family f) {
+// The fill without records (0 or 5) that a solve of the family takes now, or
+// -1: a wavefront.
+static int launch_fill_choice(rc_family f) {
   const char* env = std::getenv("RCDP_FILL");
-  if (env && std::strcmp(env, "level") == 0) return true;
-  return !forces_wavefront(env) && level_is_cheaper(f);
+  if (env && std::strcmp(env, "level") == 0) return 0;
+  if (env && std::strcmp(env, "block") == 0) return f->fb_halo.empty() ? 0 : 5;
+  if (forces_wavefront(env)) return -1;
+  const int c = cheapest_fill(f);
+  return c == 3 ? -1 : c;
 }
 
 // The fill of a solve (rc_solution_fill_path's numbers), with the records it
 // reads built.
 static int choose_fill_path(rc_family f, hipStream_t s, int32_t* path) {
   *path = 0;
-  if (f->blk_kind == 0 || level_is_default(f)) return RC_OK;
+  if (f->blk_kind == 0) return RC_OK;
+  const int launches = launch_fill_choice(f);
+  if (launches >= 0) {
+    *path = launches;
+    return RC_OK;
+  }
   const int er = ensure_records(f, s);
   if (er != RC_OK) return er;
   if (!f->has_records) return RC_OK;
@@ -950,7 +976,7 @@ static int choose_fill_path(rc_family f, hipStream_t s, int32_t* path) {
   else if (env && (std::strcmp(env, "wide") == 0 || std::strcmp(env, "ghost") == 0))
     *path = wave;
   else
-    *path = wave == 1 || level_is_cheaper(f) ? 0 : wave;
+    *path = wave == 1 ? 0 : wave;
   return *path == 1 || *path == 2 ? ensure_clusters(f, s) : RC_OK;
 }
 
@@ -994,13 +1020,13 @@ static int new_solution(rc_family f, int64_t B, int32_t objective, hipStream_t s
     const int cp = choose_fill_path(f, s, &sol->fill_path);
     if (cp != RC_OK) return fail(cp);
   }
-  if (sol->fill_path != 0 &&
+  if (sol->fill_path != 0 && sol->fill_path != 5 &&
       (hipEventCreate(&sol->evk0) != hipSuccess || hipEventCreate(&sol->evk1) != hipSuccess))
     return fail(RC_E_DEVICE);
   if (sol->fill_path == 3) {
     sol->wslab = static_cast<char*>(sol->arena.get(wide_slab_bytes(f)));
     if (!sol->wslab) return fail(RC_E_NOMEM);
-  } else if (sol->fill_path != 0) {
+  } else if (sol->fill_path == 1 || sol->fill_path == 2) {
     const int64_t K = sol->fill_path == 2 ? ghost_columns(f) : blocked_columns(f);
     sol->progress = sol->arena.get_n<int32_t>(K);
     sol->ticket = sol->arena.get_n<int32_t>(1);
@@ -1073,13 +1099,15 @@ static int solve_one(rc_family f, int64_t B, int32_t objective, void* stream, rc
   };
   if (launch_solve_init(&sol, 1, s) != hipSuccess) return fail(RC_E_DEVICE);
   if (hipEventRecord(sol->ev0, s) != hipSuccess) return fail(RC_E_DEVICE);
-  hipError_t fe = sol->fill_path == 3   ? launch_fill_wide(sol, s)
+  hipError_t fe = sol->fill_path == 5   ? launch_fill_block(&sol, 1, s)
+                  : sol->fill_path == 3 ? launch_fill_wide(sol, s)
                   : sol->fill_path == 2 ? launch_fill_ghost(sol, s)
                   : sol->fill_path == 1 ? launch_fill_blocked(sol, s)
                                         : launch_fill(sol, s);
   if (fe == hipSuccess && dominance) fe = launch_fronts(sol, s);
   if (fe != hipSuccess) {
-    set_last_error(sol->fill_path == 3   ? "split-panel fill launch"
+    set_last_error(sol->fill_path == 5   ? "block fill launch"
+                   : sol->fill_path == 3 ? "split-panel fill launch"
                    : sol->fill_path == 2 ? "ghost fill launch"
                    : sol->fill_path == 1 ? "blocked fill launch"
                                          : "level fill launch",
@@ -1145,7 +1173,8 @@ int rc_solve_batch(rc_family f, const int64_t* B_host, int32_t nb, int32_t objec
   for (rc_solution x : sols) same = same && x->fill_path == s0->fill_path;
   if (!same) {
     for (rc_solution x : sols) {
-      const hipError_t fe = x->fill_path == 3   ? launch_fill_wide(x, s)
+      const hipError_t fe = x->fill_path == 5   ? launch_fill_block(&x, 1, s)
+                            : x->fill_path == 3 ? launch_fill_wide(x, s)
                             : x->fill_path == 2 ? launch_fill_ghost(x, s)
                             : x->fill_path == 1 ? launch_fill_blocked(x, s)
                                                 : launch_fill(x, s);
@@ -1153,6 +1182,12 @@ int rc_solve_batch(rc_family f, const int64_t* B_host, int32_t nb, int32_t objec
         set_last_error("fill launch", fe);
         return fail(RC_E_DEVICE);
       }
+    }
+  } else if (s0->fill_path == 5) {
+    const hipError_t fe = launch_fill_block(sols.data(), nb, s);
+    if (fe != hipSuccess) {
+      set_last_error("batched block fill launch", fe);
+      return fail(RC_E_DEVICE);
     }
   } else if (s0->fill_path == 3) {
     host_wprm.resize((size_t)nb);

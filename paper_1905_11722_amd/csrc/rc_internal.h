@@ -172,6 +172,10 @@ struct rc_family_s {
   int32_t dual_rows = 0;
   std::vector<int32_t> dual_halo;
   int64_t* dual_split = nullptr;  // [2 F]
+  // block fill (fill.hip): each block's halo (empty: the fill cannot take the
+  // family), and the same first pairs for its blocks
+  std::vector<int32_t> fb_halo;
+  int64_t* fb_split = nullptr;    // [2 F]
   rcdp::LevelPair* lpair = nullptr; // [P] the level fill's pair records (built on first use)
   // blocked fill: records per block of at most kJB targets (absent when too large)
   int32_t blk_kind = 0;           // kBlocksFixed or kBlocksGhost (0: no records)
@@ -229,7 +233,7 @@ struct rc_solution_s {
   int32_t cpt = 1;                // blocked fill: cells per thread of a column
   uint16_t* sentinel = nullptr;   // 8 cells of infinity
   int32_t fill_path = 0;          // 0 level launches, 1 row-push wavefront, 2 ghost-zone
-                                  // wavefront, 3 split-panel wavefront
+                                  // wavefront, 3 split-panel wavefront, 5 block launches
   hipEvent_t ev0 = nullptr, ev1 = nullptr;    // around the whole fill
   hipEvent_t evk0 = nullptr, evk1 = nullptr;  // around the wavefront kernel alone
   float fill_ms = 0.f;
@@ -308,6 +312,9 @@ hipError_t launch_pair_write(rc_family f, const uint64_t* mask, hipStream_t s);
 // ---- DP kernels (fill.hip)
 hipError_t launch_solve_init(const rc_solution* sols, int32_t nb, hipStream_t s);
 hipError_t launch_fill(rc_solution sol, hipStream_t s);
+void block_fill_halos(rc_family f);
+int32_t block_fill_rows();
+hipError_t launch_fill_block(const rc_solution* sols, int32_t nb, hipStream_t s);
 // t* and opt[V, t*] of nb solutions of one family; host[b] (pinned) receives
 // solution b's status.
 hipError_t launch_select(const rc_solution* sols, int32_t nb, DevStatus* host, hipStream_t s);

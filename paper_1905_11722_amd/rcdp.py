@@ -392,7 +392,7 @@ class Solution:
         return ms.value
 
     FILL_KERNELS = ("k_fill_level_vec", "k_fill_blocked", "k_fill_ghost", "k_fill_wide",
-                    "k_fill_level")
+                    "k_fill_level", "k_fill_block")
 
     def fill_kernel(self):
         """Name of the fill kernel the solve ran (see rc_solution_fill_path)."""

@@ -161,3 +161,31 @@ def test_dual_blocks_branching(rc):
     """Blocks whose sets are not all nested."""
     g = W.random_dag(60, 0.08, 5, tmax=40, mmax=30)
     check_dual(rc, g, "pruned", (sum(g.M), (3 * sum(g.M)) // 2, 2 * sum(g.M)))
+
+
+@pytest.mark.parametrize("nodes,tmax", [(2, 3), (15, 9), (16, 9), (17, 40), (31, 2), (32, 9),
+                                        (33, 50), (50, 57), (100, 9), (20, 120)])
+def test_block_fill(rc, oracle_mod, monkeypatch, nodes, tmax):
+    """The block fill with blocks cut short, halos of a few cells up to the
+    window (and beyond it: the level launches), rows of one to many columns."""
+    monkeypatch.setenv("RCDP_FILL", "block")
+    g = W.chain(nodes, seed=nodes, tmax=tmax, mmax=9)
+    for B in (2 * max(g.M) + 6, sum(g.M), 2 * sum(g.M)):
+        compare(rc, oracle_mod, g, "exact", B)
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_block_fill_branching(rc, oracle_mod, monkeypatch, seed):
+    """Blocks that hold sets of equal size and sets that are not nested, both
+    families, single solves and a sweep in one set of launches."""
+    monkeypatch.setenv("RCDP_FILL", "block")
+    g = W.random_dag(14, 0.25, seed, tmax=20, mmax=12)
+    for mode in ("exact", "pruned"):
+        fam = compare(rc, oracle_mod, g, mode, (7 * sum(g.M)) // 4)
+        assert fam.solve(10, "tc").fill_kernel() == "k_fill_block"
+        budgets = list(range(0, 2 * sum(g.M) + 1, max(1, sum(g.M) // 33)))
+        assert len(budgets) > 64
+        for B, sol in fam.sweep(budgets, "mc"):
+            ref = oracle_mod.solve(g, mode, B, "mc")
+            assert (sol.t_star, sol.m_star) == (ref.t_star, ref.m_star)
+            sol.free()
