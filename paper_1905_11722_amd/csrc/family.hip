@@ -954,9 +954,8 @@ __global__ __launch_bounds__(kScanThreads) void k_shape(int64_t F, const int32_t
 
 hipError_t launch_graph_masks(rc_graph g, const int32_t* d_row_ptr, const int32_t* d_col_idx,
                               hipStream_t s) {
-  const int64_t cnt = (int64_t)g->n * g->words;
+  const int64_t cnt = 2 * (int64_t)g->n * g->words;      // dPred follows dSucc
   hipLaunchKernelGGL(k_zero_u64, dim3(64), dim3(256), 0, s, g->dSucc, cnt);
-  hipLaunchKernelGGL(k_zero_u64, dim3(64), dim3(256), 0, s, g->dPred, cnt);
   hipLaunchKernelGGL(k_graph_masks, dim3((g->n + 255) / 256), dim3(256), 0, s, g->n, g->words,
                      d_row_ptr, d_col_idx, g->dSucc, g->dPred);
   return hipGetLastError();

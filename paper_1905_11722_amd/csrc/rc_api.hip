@@ -214,15 +214,6 @@ void Arena::release_all() {
 
 static hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
-template <class T>
-static int upload(Arena& a, const T* host, int64_t count, T** dev, hipStream_t s) {
-  *dev = a.get_n<T>(count);
-  if (!*dev) return RC_E_NOMEM;
-  if (count > 0)
-    RC_HIP(hipMemcpyAsync(*dev, host, sizeof(T) * (size_t)count, hipMemcpyHostToDevice, s));
-  return RC_OK;
-}
-
 extern "C" {
 
 const char* rc_last_error(void) { return g_last_error; }
@@ -328,31 +319,49 @@ int rc_graph_create(int32_t n, const int32_t* row_ptr, const int32_t* col_idx, c
   for (int v = 0; v < n; v++) g->num_sinks += succs[v].empty() ? 1 : 0;
   hipStream_t s = as_stream(stream);
   int st = RC_OK;
+  // every array through one pinned buffer and one copy (eight copies from
+  // pageable memory waited for one after the other)
   int32_t *d_row_ptr = nullptr, *d_col_idx = nullptr;
-  std::vector<int32_t> rp(row_ptr ? row_ptr : nullptr, row_ptr ? row_ptr + n + 1 : nullptr);
-  std::vector<int32_t> ci(col_idx ? col_idx : nullptr, col_idx ? col_idx + nnz : nullptr);
-  if (st == RC_OK) st = upload(g->arena, T, n, &g->dT, s);
-  if (st == RC_OK) st = upload(g->arena, M, n, &g->dM, s);
-  if (st == RC_OK) st = upload(g->arena, pred_ptr.data(), n + 1, &g->dPredPtr, s);
+  StageLayout lay;
+  const size_t o_T = lay.add<int32_t>(n), o_M = lay.add<int32_t>(n),
+               o_pp = lay.add<int32_t>(n + 1),
+               o_pi = lay.add<int32_t>((int64_t)pred_idx.size()), o_bd = lay.add<int32_t>(n),
+               o_dp = lay.add<int32_t>(D + 1), o_rp = lay.add<int32_t>(n + 1),
+               o_ci = lay.add<int32_t>(nnz);
+  Staging stage(lay.bytes);
+  char* dev = static_cast<char*>(g->arena.get(lay.bytes));
+  if (!stage.data() || !dev) st = RC_E_NOMEM;
   g->num_pred_edges = (int32_t)pred_idx.size();
-  if (st == RC_OK) st = upload(g->arena, pred_idx.data(), (int64_t)pred_idx.size(), &g->dPredIdx, s);
-  if (st == RC_OK) st = upload(g->arena, by_depth.data(), n, &g->dByDepth, s);
-  if (st == RC_OK) st = upload(g->arena, depth_ptr.data(), D + 1, &g->dDepthPtr, s);
-  if (st == RC_OK) st = upload(g->arena, rp.data(), (int64_t)rp.size(), &d_row_ptr, s);
-  if (st == RC_OK) st = upload(g->arena, ci.data(), (int64_t)ci.size(), &d_col_idx, s);
   if (st == RC_OK) {
-    g->dSucc = g->arena.get_n<uint64_t>((int64_t)n * g->words);
-    g->dPred = g->arena.get_n<uint64_t>((int64_t)n * g->words);
+    auto put = [&](size_t off, const int32_t* host, int64_t count) {
+      if (count > 0) std::memcpy(stage.data() + off, host, sizeof(int32_t) * (size_t)count);
+      return reinterpret_cast<int32_t*>(dev + off);
+    };
+    g->dT = put(o_T, T, n);
+    g->dM = put(o_M, M, n);
+    g->dPredPtr = put(o_pp, pred_ptr.data(), n + 1);
+    g->dPredIdx = put(o_pi, pred_idx.data(), (int64_t)pred_idx.size());
+    g->dByDepth = put(o_bd, by_depth.data(), n);
+    g->dDepthPtr = put(o_dp, depth_ptr.data(), D + 1);
+    d_row_ptr = put(o_rp, row_ptr, row_ptr && n > 0 ? n + 1 : 0);
+    d_col_idx = put(o_ci, col_idx, nnz);
+    stage.in_flight();
+    if (hipMemcpyAsync(dev, stage.data(), lay.bytes, hipMemcpyHostToDevice, s) != hipSuccess)
+      st = RC_E_DEVICE;
+  }
+  if (st == RC_OK) {
+    g->dSucc = g->arena.get_n<uint64_t>(2 * (int64_t)n * g->words);
+    g->dPred = g->dSucc + (int64_t)n * g->words;
     g->dAnc = g->arena.get_n<uint64_t>((int64_t)n * g->words);
-    if (!g->dSucc || !g->dPred || !g->dAnc) st = RC_E_NOMEM;
+    if (!g->dSucc || !g->dAnc) st = RC_E_NOMEM;
   }
   if (st == RC_OK && n > 0 && launch_graph_masks(g, d_row_ptr, d_col_idx, s) != hipSuccess)
     st = RC_E_DEVICE;
   // the ancestor sets (Section 4.3's generators of the pruned family) are a
   // property of the graph: computed once here, read by every pruned family
   if (st == RC_OK && n > 0 && launch_ancestors(g, g->dAnc, s) != hipSuccess) st = RC_E_DEVICE;
-  // the host vectors above must stay alive until the copies have completed
   if (st == RC_OK && hipStreamSynchronize(s) != hipSuccess) st = RC_E_DEVICE;
+  if (st == RC_OK) stage.landed();
   if (st != RC_OK) {
     (void)hipStreamSynchronize(s);
     g->arena.release_all();
@@ -820,16 +829,17 @@ int rc_min_budget(rc_family f, void* stream, int64_t* B_min) {
   const int64_t hi0 = 2 * f->g->M_total;           // the chain {V} peaks at 2 M(V)
   if (hi0 >= INT32_MAX) return RC_E_OVERFLOW;
   hipStream_t s = as_stream(stream);
-  const size_t scratch = min_budget_scratch_bytes(f, (int32_t)hi0);
-  if (scratch > 0 && !f->bmin_scratch) {
-    f->bmin_scratch = static_cast<uint32_t*>(f->arena.get(scratch));
+  if (!f->bmin_scratch) {
+    f->bmin_scratch = f->arena.get(min_budget_scratch_bytes(f, (int32_t)hi0));
     if (!f->bmin_scratch) return RC_E_NOMEM;
   }
-  RC_HIP(launch_min_budget(f, (int32_t)hi0, f->bmin_scratch, s));
-  DevStatus hs;
-  RC_HIP(hipMemcpyAsync(&hs, f->status, sizeof(hs), hipMemcpyDeviceToHost, s));
-  RC_HIP(hipStreamSynchronize(s));
-  *B_min = hs.bmin;
+  Staging stage(sizeof(int64_t));
+  if (!stage.data()) return RC_E_NOMEM;
+  stage.in_flight();
+  RC_HIP(launch_min_budget(f, (int32_t)hi0, f->bmin_scratch, stage.at<int64_t>(0), s));
+  const int ss = sync_landed(stage, s);
+  if (ss != RC_OK) return ss;
+  *B_min = *stage.at<int64_t>(0);
   return RC_OK;
 }
 

@@ -101,7 +101,6 @@ struct DevStatus {
   int32_t k;             // chain length
   int32_t pad0;
   int64_t overhead, peak, cache_mem;
-  int64_t bmin;          // smallest feasible budget (rc_min_budget)
   int32_t done;          // workgroups of the selection that have finished
   int32_t pad1;
 };
@@ -192,7 +191,7 @@ struct rc_family_s {
   bool has_wide = false;          // the split-panel fill can take this family
   rcdp::BlockRecords rec;
   rcdp::DevStatus* status = nullptr;
-  uint32_t* bmin_scratch = nullptr; // rc_min_budget: f values of large families
+  void* bmin_scratch = nullptr;   // rc_min_budget: its intervals, f values of large families
   // host copies used for launches
   std::vector<int64_t> level_ptr; // family index ranges of equal set size
   std::vector<int64_t> level_pairs; // the most pairs of a target in each level
@@ -394,7 +393,9 @@ hipError_t launch_fill_ghost_batch(rc_solution* sols, int32_t nb, GParams* host_
 
 // ---- smallest feasible budget (budget.hip)
 size_t min_budget_scratch_bytes(rc_family f, int32_t hi0);
-hipError_t launch_min_budget(rc_family f, int32_t hi0, uint32_t* scratch, hipStream_t s);
+// The smallest feasible budget to *host (pinned).
+hipError_t launch_min_budget(rc_family f, int32_t hi0, void* scratch, int64_t* host,
+                             hipStream_t s);
 // Memory-indexed table of Algorithm 1's recursion (dual.hip): D[F * W]
 // uint32, W = min(B, M(V)) + 1; t and the least m of the objective into
 // st->t_sel / st->m_sel (-1 when no chain reaches V)  level_pairs[l]: the

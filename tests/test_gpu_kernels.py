@@ -189,3 +189,19 @@ def test_block_fill_branching(rc, oracle_mod, monkeypatch, seed):
             ref = oracle_mod.solve(g, mode, B, "mc")
             assert (sol.t_star, sol.m_star) == (ref.t_star, ref.m_star)
             sol.free()
+
+
+@pytest.mark.parametrize("scale", [1, 3, 40, 9000])
+@pytest.mark.parametrize("graph,mode", [(W.chain(5, 1), "exact"), (W.chain(40, 2), "exact"),
+                                        (W.random_dag(10, 0.4, 3), "exact"),
+                                        (W.antichain(9, 4), "exact"), (W.ladder(12), "exact")],
+                         ids=["chain5", "chain40", "random10", "antichain9", "ladder24"])
+def test_min_budget_rounds(rc, oracle_mod, graph, mode, scale):
+    """Budget ranges of one round and of several, f in 16 and in 32 bits, in
+    LDS and in global memory."""
+    g = W.Graph(graph.n, [list(x) for x in graph.succ], list(graph.T),
+                [m * scale + (m & 1) for m in graph.M])
+    fam = rc.Graph.create(g).build_family(mode)
+    want = oracle_mod.min_budget(g, mode)
+    assert fam.min_budget() == want
+    assert fam.min_budget() == want
