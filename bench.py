@@ -46,6 +46,7 @@ FILL_SOURCES = {
                      _CSRC + "rc_internal.h", _CSRC + "ghost_cut.h"],
     "k_fill_level_vec": [_CSRC + "fill.hip", _CSRC + "wavefront.h", _CSRC + "rc_internal.h"],
     "k_fill_level": [_CSRC + "fill.hip", _CSRC + "rc_internal.h"],
+    "k_fill_block": [_CSRC + "fill.hip", _CSRC + "wavefront.h", _CSRC + "rc_internal.h"],
 }
 
 
