@@ -154,19 +154,34 @@ __global__ __launch_bounds__(64) void k_ancestors_wave(int n, int words, int num
 // Transitive closure of the predecessor relation in one workgroup (graphs
 // whose masks fit LDS and have at most kClosureWords words): A[v] starts as
 // the direct predecessors of v; for every node k, each mask that contains k
-// absorbs A[k] (Warshall's algorithm, any order of k).  A[k] never contains
-// k in a DAG, so the bit tests of step k read values that step k does not
-// change.  One barrier per node, every (node, word) item of a step in
-// parallel; then L^v = A[v] + {v}.
+// absorbs A[k] (Warshall's algorithm, any order of k).  The 64 nodes of a
+// mask word are taken as one block, so that a block costs four barriers
+// instead of a barrier per node:
+//  - the block's own rows absorb one another in registers, lane i row
+//    64 kb + i, wave w word w beside its own copy of word kb, which says who
+//    absorbs whom; row k reaches the other lanes by readlane;
+//  - a row outside absorbs the closed rows of the block that it contains, the
+//    highest first, and skips those that are below one already taken: with
+//    ids in a topological order the block's antichain, not its 64 nodes.
+// Then L^v = A[v] + {v}.  Bound by the chain of 64 register steps per word:
+// DenseNet-121's 426 nodes 28 us, against 132 with a barrier per node.
 constexpr int kClosureWords = 8;
 constexpr int kClosureThreads = 1024;
 constexpr int kClosureItems = 4;        // items per thread: n * words <= 4096
+static_assert(kClosureWords <= kClosureThreads / kWave, "a wave per word");
+
+__device__ __forceinline__ uint64_t row_word(uint64_t x, int lane) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane) |
+         ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), lane) << 32);
+}
 
 __global__ __launch_bounds__(kClosureThreads) void k_ancestors_closure(int n, int words,
                                                                        const uint64_t* pred_mask,
                                                                        uint64_t* anc_out) {
   extern __shared__ uint64_t A[];
   const int items = n * words;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   for (int x = threadIdx.x; x < items; x += kClosureThreads) A[x] = pred_mask[x];
   int vw[kClosureItems], wo[kClosureItems];          // row offset v * words and word w
 #pragma unroll
@@ -177,15 +192,43 @@ __global__ __launch_bounds__(kClosureThreads) void k_ancestors_closure(int n, in
     wo[r] = it - v * words;
   }
   __syncthreads();
-  for (int k = 0; k < n; k++) {
-    const int kw = k >> 6;
-    const uint64_t kb = 1ull << (k & 63);
-    const int kr = k * words;
+  for (int kb = 0; kb < words; kb++) {
+    const int row0 = 64 * kb * words;                   // the block's rows
+    const int row1 = min(64 * (kb + 1), n) * words;
+    const int own = row0 + lane * words;
+    const bool mine = wave < words && own < row1;
+    uint64_t x = 0;
+    if (wave < words) {
+      uint64_t d = mine ? A[own + kb] : 0;
+      x = mine ? A[own + wave] : 0;
+#pragma unroll
+      for (int k = 0; k < 64; k++) {
+        if (k % 16 == 0 && row0 + k * words >= row1) break;   // lanes past the last row hold 0
+        const uint64_t take = 0 - (d >> k & 1);
+        x |= row_word(x, k) & take;
+        d |= row_word(d, k) & take;
+      }
+    }
+    __syncthreads();
+    if (mine) A[own + wave] = x;
+    __syncthreads();
+    uint64_t acc[kClosureItems];
 #pragma unroll
     for (int r = 0; r < kClosureItems; r++) {
-      if (vw[r] < 0) continue;
-      if (A[vw[r] + kw] & kb) A[vw[r] + wo[r]] |= A[kr + wo[r]];
+      acc[r] = 0;
+      if (vw[r] < 0 || (vw[r] >= row0 && vw[r] < row1)) continue;
+      uint64_t left = A[vw[r] + kb];
+      while (left) {
+        const int j = 63 - __builtin_clzll(left);
+        const uint64_t* const aj = A + row0 + j * words;
+        acc[r] |= aj[wo[r]];
+        left &= ~(aj[kb] | 1ull << j);
+      }
     }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kClosureItems; r++)
+      if (acc[r]) A[vw[r] + wo[r]] |= acc[r];
     __syncthreads();
   }
   for (int x = threadIdx.x; x < items; x += kClosureThreads) {

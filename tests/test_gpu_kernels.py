@@ -2,6 +2,7 @@
 wrong (edges of tiles and groups, remainders, the smallest and the largest of
 its range), against the oracle, bit for bit."""
 
+import numpy as np
 import pytest
 
 from paper_1905_11722_amd import workloads as W
@@ -205,3 +206,24 @@ def test_min_budget_rounds(rc, oracle_mod, graph, mode, scale):
     want = oracle_mod.min_budget(g, mode)
     assert fam.min_budget() == want
     assert fam.min_budget() == want
+
+
+@pytest.mark.parametrize("nodes", [1, 15, 17, 63, 64, 65, 127, 129, 300, 448, 511, 512])
+def test_ancestor_closure_blocks(rc, oracle_mod, nodes):
+    """Ancestors by blocks of 64 nodes: blocks cut short, one to eight mask
+    words, node ids in a topological order, reversed and mixed."""
+    import random
+    rng = random.Random(nodes)
+    g = W.random_dag(nodes, min(0.3, 4 / nodes), nodes)
+    for order in ("as is", "reversed", "mixed"):
+        new = list(range(nodes))
+        if order == "reversed":
+            new.reverse()
+        elif order == "mixed":
+            rng.shuffle(new)
+        succ = [None] * nodes
+        for v in range(nodes):
+            succ[new[v]] = sorted(new[x] for x in g.succ[v])
+        h = W.Graph(nodes, succ, list(g.T), list(g.M))
+        fam = rc.Graph.create(h).build_family("pruned")
+        np.testing.assert_array_equal(fam.sets(), oracle_mod.family(h, "pruned").sets())
