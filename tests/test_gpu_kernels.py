@@ -227,3 +227,21 @@ def test_ancestor_closure_blocks(rc, oracle_mod, nodes):
         h = W.Graph(nodes, succ, list(g.T), list(g.M))
         fam = rc.Graph.create(h).build_family("pruned")
         np.testing.assert_array_equal(fam.sets(), oracle_mod.family(h, "pruned").sets())
+
+
+@pytest.mark.parametrize("nodes,tmax", [(24, 9), (40, 60), (33, 3000)])
+def test_wide_records_without_a_test(rc, oracle_mod, monkeypatch, nodes, tmax):
+    """Panel records whose budgets no source cell can exceed, records where
+    one slot's can by one unit, and both kinds in one block: budgets one by
+    one around every M(L) + c, single solves and a batch."""
+    monkeypatch.setenv("RCDP_FILL", "wide")
+    g = W.chain(nodes, seed=nodes, tmax=tmax, mmax=4)
+    fam = rc.Graph.create(g).build_family("pruned")
+    budgets = list(range(2 * max(g.M), 2 * sum(g.M) + 1, 1 if tmax < 100 else 17))
+    for B, sol in fam.sweep(budgets, "tc"):
+        assert sol.fill_kernel() == "k_fill_wide"
+        ref = oracle_mod.solve(g, "pruned", B, "tc")
+        assert (sol.t_star, sol.m_star) == (ref.t_star, ref.m_star)
+        sol.free()
+    for B in (sum(g.M), sum(g.M) + 1, (3 * sum(g.M)) // 2, 2 * sum(g.M)):
+        compare(rc, oracle_mod, g, "pruned", B, objectives=("tc",))
