@@ -241,9 +241,9 @@ def dual_tables(rcdp, torch, reps=5, names=None):
 
 
 def dominance_fills(rcdp, torch, reps=5, names=None):
-    """rc_solve_dominance (the skip of Section 4.2 on the level fill) against
+    """rc_solve_dominance (the skip of Section 4.2) against
     rc_solve on the same family, with its default fill and with the level
-    fill forced (RCDP_FILL=level: the skip's own cost and gain): fill_ms of
+    fill forced (RCDP_FILL=level): fill_ms of
     each (median of reps), and `agrees` = equal (t*, opt[V, t*])."""
     from paper_1905_11722_amd import workloads
     out = {}
@@ -430,7 +430,7 @@ def main():
     ap.add_argument("--no-other-graphs", action="store_true")
     ap.add_argument("--copy-calibration", type=int, default=0, metavar="BYTES")
     ap.add_argument("--dominance", action="store_true",
-                    help="time only the level fill with the dominance skip (rc_solve_dominance) "
+                    help="time only the solve with the dominance skip (rc_solve_dominance) "
                          "against rc_solve on --workload")
     ap.add_argument("--dual", action="store_true",
                     help="time only the memory-indexed table (rc_solve_dual) on --workload")
