@@ -992,7 +992,10 @@ static int choose_fill_path(rc_family f, hipStream_t s, int32_t* path) {
 
 }  // extern "C"
 
-// A solution handle with its buffers and events; nothing enqueued yet.
+// A solution handle with its buffers and events.  Nothing of the solve is
+// enqueued yet, but the family's records are where this is the first solve
+// that reads them: on an error s has been waited for, so that a later solve,
+// on whatever stream, finds them written.
 static int new_solution(rc_family f, int64_t B, int32_t objective, hipStream_t s,
                         rc_solution* out) {
   if (!f || B < 0) return RC_E_ARG;
@@ -1011,6 +1014,7 @@ static int new_solution(rc_family f, int64_t B, int32_t objective, hipStream_t s
   sol->arena.free_fn = f->arena.free_fn;
   sol->arena.user = f->arena.user;
   auto fail = [&](int st) {
+    (void)hipStreamSynchronize(s);           // the family's records may be on their way
     destroy_events(sol);
     sol->arena.release_all();
     delete sol;

@@ -1,0 +1,85 @@
+"""Calls that fail and the calls after them: device allocations refused in
+turn.  A call that returns an error leaves nothing behind on its stream that a
+later call could read unfinished."""
+
+import numpy as np
+import pytest
+
+from paper_1905_11722_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def rc(monkeypatch):
+    """The binding with an allocator that can be told to refuse a call."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1905_11722_amd import rcdp
+    rcdp.load_library()
+
+    class Refusing(rcdp._TorchAllocator):
+        left = None                       # allocations until one is refused
+
+        def _alloc(self, nbytes, user):
+            if self.left is not None:
+                self.left -= 1
+                if self.left < 0:
+                    return None
+            return super()._alloc(nbytes, user)
+
+    allocator = Refusing()
+    monkeypatch.setattr(rcdp, "_get_allocator", lambda: allocator)
+    monkeypatch.setattr(rcdp, "refusing", allocator, raising=False)
+    return rcdp
+
+
+def busy(torch, stream):
+    """Some milliseconds of work on the stream."""
+    with torch.cuda.stream(stream):
+        x = torch.empty(1 << 28, dtype=torch.float32, device="cuda")
+        y = torch.empty_like(x)
+        for _ in range(16):
+            y.copy_(x)
+
+
+@pytest.mark.parametrize("path,kernel,nodes", [("wide", "k_fill_wide", 300),
+                                               ("wavefront", "k_fill_blocked", 300),
+                                               ("ghost", "k_fill_ghost", 90)])
+def test_failed_solve_leaves_its_stream_idle(rc, oracle_mod, monkeypatch, path, kernel, nodes):
+    """Records that the first solve of a wavefront fill builds: a solve that
+    is refused memory after it enqueued them has waited for them when it
+    returns, and a solve on another stream then reads them whole."""
+    import torch
+    g = W.chain(nodes, seed=7, tmax=9, mmax=9)
+    B = (3 * sum(g.M)) // 2
+    ref = oracle_mod.solve(g, "pruned", B, "tc").table()[0]
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    refused = 0
+    for k in range(32):
+        with torch.cuda.stream(one):
+            monkeypatch.setenv("RCDP_FILL", "level")          # builds no records
+            fam = rc.Graph.create(g).build_family("pruned")
+        monkeypatch.setenv("RCDP_FILL", path)
+        busy(torch, one)
+        with torch.cuda.stream(one):
+            rc.refusing.left = k
+            try:
+                sol = fam.solve(B, "tc")
+            except rc.RcError:
+                sol = None
+            finally:
+                rc.refusing.left = None
+            assert one.query(), f"allocation {k}: work left on the stream"
+        if sol is not None:
+            break
+        refused += 1
+        with torch.cuda.stream(two):
+            again = fam.solve(B, "tc")
+            np.testing.assert_array_equal(again.table()[0], ref)
+            again.free()
+    assert sol is not None and refused >= (2 if path == "wide" else 1)
+    assert sol.fill_kernel() == kernel
+    np.testing.assert_array_equal(sol.table()[0], ref)
+    sol.free()
