@@ -1094,6 +1094,14 @@ extern "C" {
 
 }  // extern "C"
 
+// Status of a launcher that failed: it reports the family's allocator
+// returning NULL as hipErrorOutOfMemory.
+static int launch_status(const char* what, hipError_t e) {
+  if (e == hipErrorOutOfMemory) return RC_E_NOMEM;
+  set_last_error(what, e);
+  return RC_E_DEVICE;
+}
+
 // rc_solve and rc_solve_dominance: one table fill, then the selection of t*.
 static int solve_one(rc_family f, int64_t B, int32_t objective, void* stream, rc_solution* out,
                      int64_t* t_opt, int64_t* m_opt, bool dominance) {
@@ -1119,15 +1127,13 @@ static int solve_one(rc_family f, int64_t B, int32_t objective, void* stream, rc
                   : sol->fill_path == 1 ? launch_fill_blocked(sol, s)
                                         : launch_fill(sol, s);
   if (fe == hipSuccess && dominance) fe = launch_fronts(sol, s);
-  if (fe != hipSuccess) {
-    set_last_error(sol->fill_path == 5   ? "block fill launch"
-                   : sol->fill_path == 3 ? "split-panel fill launch"
-                   : sol->fill_path == 2 ? "ghost fill launch"
-                   : sol->fill_path == 1 ? "blocked fill launch"
-                                         : "level fill launch",
-                   fe);
-    return fail(RC_E_DEVICE);
-  }
+  if (fe != hipSuccess)
+    return fail(launch_status(sol->fill_path == 5   ? "block fill launch"
+                              : sol->fill_path == 3 ? "split-panel fill launch"
+                              : sol->fill_path == 2 ? "ghost fill launch"
+                              : sol->fill_path == 1 ? "blocked fill launch"
+                                                    : "level fill launch",
+                              fe));
   if (hipEventRecord(sol->ev1, s) != hipSuccess) return fail(RC_E_DEVICE);
   Staging stage(sizeof(DevStatus));
   if (!stage.data()) return fail(RC_E_NOMEM);
@@ -1192,51 +1198,33 @@ int rc_solve_batch(rc_family f, const int64_t* B_host, int32_t nb, int32_t objec
                             : x->fill_path == 2 ? launch_fill_ghost(x, s)
                             : x->fill_path == 1 ? launch_fill_blocked(x, s)
                                                 : launch_fill(x, s);
-      if (fe != hipSuccess) {
-        set_last_error("fill launch", fe);
-        return fail(RC_E_DEVICE);
-      }
+      if (fe != hipSuccess) return fail(launch_status("fill launch", fe));
     }
   } else if (s0->fill_path == 5) {
     const hipError_t fe = launch_fill_block(sols.data(), nb, s);
-    if (fe != hipSuccess) {
-      set_last_error("batched block fill launch", fe);
-      return fail(RC_E_DEVICE);
-    }
+    if (fe != hipSuccess) return fail(launch_status("batched block fill launch", fe));
   } else if (s0->fill_path == 3) {
     host_wprm.resize((size_t)nb);
     WParams* dev_prm = s0->arena.get_n<WParams>(nb);
     if (!dev_prm) return fail(RC_E_NOMEM);
     const hipError_t fe = launch_fill_wide_batch(sols.data(), nb, host_wprm.data(), dev_prm, s);
-    if (fe != hipSuccess) {
-      set_last_error("batched split-panel fill launch", fe);
-      return fail(RC_E_DEVICE);
-    }
+    if (fe != hipSuccess) return fail(launch_status("batched split-panel fill launch", fe));
   } else if (s0->fill_path == 2) {
     host_gprm.resize((size_t)nb);
     GParams* dev_prm = s0->arena.get_n<GParams>(nb);
     if (!dev_prm) return fail(RC_E_NOMEM);
     const hipError_t fe = launch_fill_ghost_batch(sols.data(), nb, host_gprm.data(), dev_prm, s);
-    if (fe != hipSuccess) {
-      set_last_error("batched ghost fill launch", fe);
-      return fail(RC_E_DEVICE);
-    }
+    if (fe != hipSuccess) return fail(launch_status("batched ghost fill launch", fe));
   } else if (s0->fill_path == 1) {
     host_prm.resize((size_t)nb);
     BParams* dev_prm = s0->arena.get_n<BParams>(nb);
     if (!dev_prm) return fail(RC_E_NOMEM);
     const hipError_t fe = launch_fill_blocked_batch(sols.data(), nb, host_prm.data(), dev_prm, s);
-    if (fe != hipSuccess) {
-      set_last_error("batched blocked fill launch", fe);
-      return fail(RC_E_DEVICE);
-    }
+    if (fe != hipSuccess) return fail(launch_status("batched blocked fill launch", fe));
   } else {
     for (rc_solution x : sols) {
       const hipError_t fe = launch_fill(x, s);
-      if (fe != hipSuccess) {
-        set_last_error("level fill launch", fe);
-        return fail(RC_E_DEVICE);
-      }
+      if (fe != hipSuccess) return fail(launch_status("level fill launch", fe));
     }
   }
   if (hipEventRecord(s0->ev1, s) != hipSuccess) return fail(RC_E_DEVICE);

@@ -83,3 +83,70 @@ def test_failed_solve_leaves_its_stream_idle(rc, oracle_mod, monkeypatch, path, 
     assert sol.fill_kernel() == kernel
     np.testing.assert_array_equal(sol.table()[0], ref)
     sol.free()
+
+
+def calls(rc, g):
+    """Name, environment, and a call on a new family of g that returns what
+    the caller compares."""
+    B = (3 * sum(g.M)) // 2
+    budgets = [B - 9, B, B + 9]
+
+    def outcome(sol):
+        out = (sol.t_star, sol.m_star, sol.reconstruct().chain.tolist())
+        sol.free()
+        return out
+
+    def table(fam):
+        sol = fam.solve(B, "tc")
+        m, a = sol.table(first=fam.info["num_sets"] - 1)
+        sol.free()
+        return m.tolist(), a.tolist()
+
+    for path in ("level", "block", "wide", "wavefront", "ghost"):
+        yield f"solve {path}", path, lambda fam: outcome(fam.solve(B, "tc"))
+        yield f"sweep {path}", path, lambda fam: [outcome(s) for _, s in fam.sweep(budgets, "mc")]
+    yield "dominance", None, lambda fam: outcome(fam.solve_dominance(B))
+    yield "dominance level", "level", lambda fam: outcome(fam.solve_dominance(B))
+    yield "table", None, table
+    yield "budget", None, lambda fam: fam.min_budget()
+    yield "dual", None, lambda fam: fam.solve_dual(B, "tc", schedule=True)[:2]
+
+
+@pytest.mark.parametrize("nodes,scale", [(70, 1), (300, 1), (70, 400)])
+def test_refused_memory_is_reported_as_such(rc, monkeypatch, nodes, scale):
+    """Every allocation of every call refused in turn (as the allocator is
+    asked in chunks, a handful of calls each): RC_E_NOMEM, and the same call
+    then gives what it gives on a family that never saw a refusal.  Budgets
+    of 16 and (sizes scaled) of 32 bits."""
+    g = W.chain(nodes, seed=nodes, tmax=9, mmax=9)
+    g.M = [m * scale for m in g.M]
+    seen = 0
+    for name, path, call in calls(rc, g):
+        if scale > 1 and name.startswith("dominance"):
+            continue                               # the skip takes 16-bit cells only
+        if path:
+            monkeypatch.setenv("RCDP_FILL", path)
+        else:
+            monkeypatch.delenv("RCDP_FILL", raising=False)
+        h = rc.Graph.create(g)
+        want = call(h.build_family("pruned"))
+        for k in range(64):
+            fam, done, got = None, False, None
+            rc.refusing.left = k
+            try:
+                fam = h.build_family("pruned")
+                got = call(fam)
+                done = True
+            except rc.RcError as e:
+                assert e.status == rc.E_NOMEM, (name, k, str(e))
+                seen += 1
+            finally:
+                rc.refusing.left = None
+            if fam is not None and not done:
+                got = call(fam)
+            if fam is not None:
+                assert got == want, (name, k)
+            if done:
+                break
+        assert done, name
+    assert seen > 20
