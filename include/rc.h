@@ -294,12 +294,14 @@ int rc_solve_dominance(rc_family f, int64_t B, void* stream, rc_solution* out, i
 int rc_solve_batch(rc_family f, const int64_t* B_host, int32_t nb, int32_t objective,
                    void* stream, rc_solution* out_host, int64_t* t_opt, int64_t* m_opt);
 /* Milliseconds between HIP events recorded on the solve's stream just
- * before the first and just after the last DP-fill kernel of the solve. */
+ * before the first and just after the last kernel of the solve's fill: the
+ * table's padding and starting values, the records of the fill, the fill. */
 int rc_solution_fill_ms(rc_solution s, float* ms);
 /* Milliseconds between HIP events recorded on the solve's stream just
  * before and just after the one wavefront kernel of the blocked fill
- * (without the kernels that prepare its records).  On the level and block
- * paths, which run many launches, this equals rc_solution_fill_ms.  Returns RC_OK or RC_E_ARG (NULL argument). */
+ * (without the kernels that prepare the table and its records).  On the
+ * level and block paths, which run many launches, this equals
+ * rc_solution_fill_ms.  Returns RC_OK or RC_E_ARG (NULL argument). */
 int rc_solution_fill_kernel_ms(rc_solution s, float* ms);
 /* Which fill the solve ran (all of them compute the same table, Algorithm 1
  * of Section 4.2): *path = 0 one launch per group of equal-size sets on

@@ -1119,8 +1119,8 @@ static int solve_one(rc_family f, int64_t B, int32_t objective, void* stream, rc
     drop_solution(sol);
     return st;
   };
-  if (launch_solve_init(&sol, 1, s) != hipSuccess) return fail(RC_E_DEVICE);
   if (hipEventRecord(sol->ev0, s) != hipSuccess) return fail(RC_E_DEVICE);
+  if (launch_solve_init(&sol, 1, s) != hipSuccess) return fail(RC_E_DEVICE);
   hipError_t fe = sol->fill_path == 5   ? launch_fill_block(&sol, 1, s)
                   : sol->fill_path == 3 ? launch_fill_wide(sol, s)
                   : sol->fill_path == 2 ? launch_fill_ghost(sol, s)
@@ -1181,9 +1181,9 @@ int rc_solve_batch(rc_family f, const int64_t* B_host, int32_t nb, int32_t objec
     if (st != RC_OK) return fail(st);
     sols.push_back(x);
   }
-  if (launch_solve_init(sols.data(), nb, s) != hipSuccess) return fail(RC_E_DEVICE);
   rc_solution s0 = sols[0];
   if (hipEventRecord(s0->ev0, s) != hipSuccess) return fail(RC_E_DEVICE);
+  if (launch_solve_init(sols.data(), nb, s) != hipSuccess) return fail(RC_E_DEVICE);
   std::vector<BParams> host_prm;
   std::vector<GParams> host_gprm;
   std::vector<WParams> host_wprm;
