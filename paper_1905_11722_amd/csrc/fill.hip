@@ -156,7 +156,8 @@ __global__ __launch_bounds__(kFillThreads) void k_fill_level(
     const int32_t dt = pdt[p];
     const int32_t i = pidx[p];
     const int32_t wi = w[i];                  // cells of the source row
-    if (dt >= tile0 + kTile || dt + wi <= tile0) continue;  // window misses the tile
+    // window misses the tile (whose end may lie past the last int32)
+    if (dt >= (int64_t)tile0 + kTile || dt + wi <= tile0) continue;
     const T* src = m + row_off[i];
     const uint32_t dm = (uint32_t)pdm[p];
 #pragma unroll
@@ -702,10 +703,11 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(SelectTables tabs,
   const int32_t wv = w[v];
   const bool tc = objective == RC_TIME_CENTRIC;
   int32_t best = tc ? INT32_MAX : -1;
-  const int32_t groups = (wv + kVec - 1) / kVec;
+  // a row has up to 2^31 - 2 cells: its rounded length is no int32
+  const int32_t groups = (int32_t)(((int64_t)wv + kVec - 1) / kVec);
   for (int32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < groups;
        g += gridDim.x * blockDim.x) {
-    const int32_t t0 = wv - kVec * (g + 1);           // may start before the row's first cell
+    const int32_t t0 = (int32_t)(wv - kVec * ((int64_t)g + 1));   // before the row for the last g
     union {
       uint4 q;
       T c[kVec];
@@ -1162,7 +1164,7 @@ static void fill_levels(rc_solution sol, T* m, hipStream_t s) {
     if (vec_rows<T>(f)) {
       launch_level_vec<T>(f, l, lb, le - lb, (int32_t)sol->Beff, m, s);
     } else {
-      const int64_t tiles = (f->level_maxw[l] + kTile - 1) / kTile;
+      const int64_t tiles = ((int64_t)f->level_maxw[l] + kTile - 1) / kTile;
       hipLaunchKernelGGL(k_fill_level<T>, dim3((unsigned)tiles, (unsigned)(le - lb)),
                          dim3(kFillThreads), 0, s, lb, f->w, f->row_off, f->pred_ptr, f->pidx,
                          f->pdt, f->pdm, f->pc, (int32_t)sol->Beff, m);

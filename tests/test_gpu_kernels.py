@@ -7,6 +7,7 @@ import pytest
 
 from paper_1905_11722_amd import workloads as W
 
+from tests.bruteforce import brute_table, select
 from tests.test_gpu_dominance import compare as compare_dominance
 from tests.test_gpu_dual import check as check_dual
 from tests.test_gpu_parity import compare
@@ -245,3 +246,30 @@ def test_wide_records_without_a_test(rc, oracle_mod, monkeypatch, nodes, tmax):
         sol.free()
     for B in (sum(g.M), sum(g.M) + 1, (3 * sum(g.M)) // 2, 2 * sum(g.M)):
         compare(rc, oracle_mod, g, "pruned", B, objectives=("tc",))
+
+
+@pytest.mark.parametrize("scale", [1, 4000])
+@pytest.mark.parametrize("T", [[(1 << 31) - 3], [(1 << 31) - 10], [(1 << 31) - 1026],
+                               [(1 << 30) + 5, 3, (1 << 30) - 20]])
+def test_rows_of_2_to_the_31_cells(rc, T, scale):
+    """Rows whose byte offsets leave 32 bits, up to the longest that T(V)
+    admits: the level fill with one cell per thread, the selection and the
+    traceback, in 16- and (sizes scaled) in 32-bit cells, against brute force
+    over the few chains."""
+    n = len(T)
+    g = W.Graph(n, [[v + 1] if v + 1 < n else [] for v in range(n)], T,
+                [(5 + 2 * v) * scale for v in range(n)])
+    fam = rc.Graph.create(g).build_family("pruned")
+    for B in (2 * max(g.M) + g.M[0], 2 * sum(g.M)):
+        F, opt, arg = brute_table(g, "pruned", B)
+        for objective in ("tc", "mc"):
+            sol = fam.solve(B, objective)
+            t = select(opt, F, objective)
+            if t is None:
+                assert (sol.t_star, sol.m_star) == (-1, -1)
+            else:
+                assert (sol.t_star, sol.m_star) == (t, opt[len(F) - 1, t])
+                sched = sol.reconstruct()
+                assert (sched.overhead, sched.cache_mem) == (sol.t_star, sol.m_star)
+                assert sched.peak <= B and sched.chain[-1] == len(F) - 1
+            sol.free()
