@@ -308,7 +308,9 @@ int rc_solution_fill_kernel_ms(rc_solution s, float* ms);
  * 16-bit cells (k_fill_level_vec), 1 the persistent row-push wavefront
  * (k_fill_blocked), 2 the ghost-zone wavefront (k_fill_ghost), 3 the
  * split-panel wavefront (k_fill_wide), 4 one launch per group of equal-size
- * sets on 32-bit cells, 5 one launch per block of 16 sets (k_fill_block).
+ * sets on 32-bit cells (k_fill_level_vec), 5 one launch per block of 16 sets
+ * (k_fill_block).  0 and 4 run k_fill_level where a row of the family, with
+ * 64 cells added, takes 2^31 - 1 bytes or more.
  * Returns RC_OK or RC_E_ARG (NULL argument). */
 int rc_solution_fill_path(rc_solution s, int32_t* path);
 /* Which traceback the last rc_reconstruct of the handle ran (both follow

@@ -392,13 +392,17 @@ class Solution:
         return ms.value
 
     FILL_KERNELS = ("k_fill_level_vec", "k_fill_blocked", "k_fill_ghost", "k_fill_wide",
-                    "k_fill_level", "k_fill_block")
+                    "k_fill_level_vec", "k_fill_block")
 
     def fill_kernel(self):
-        """Name of the fill kernel the solve ran (see rc_solution_fill_path)."""
+        """Name of the fill kernel the solve ran (see rc_solution_fill_path).
+        The level fill of rows beyond 2^31 bytes is k_fill_level."""
         path = ctypes.c_int32()
         _check(load_library().rc_solution_fill_path(self._h, ctypes.byref(path)),
                "rc_solution_fill_path")
+        cell = {0: 2, 4: 4}.get(path.value, 0)             # bytes, of the level fill
+        if (self.family.info["max_row"] + 64) * cell >= 2 ** 31 - 1:
+            return "k_fill_level"
         return self.FILL_KERNELS[path.value]
 
     TRACE_KERNELS = ("k_trace", "k_trace_follow")

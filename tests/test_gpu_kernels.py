@@ -75,7 +75,8 @@ def test_level_fill_lists_and_tiles(rc, oracle_mod, monkeypatch, nodes, tmax, sc
     monkeypatch.setenv("RCDP_FILL", "level")
     g = W.chain(nodes, seed=nodes, tmax=tmax, mmax=15)
     g.M = [m * scale for m in g.M]
-    compare(rc, oracle_mod, g, "pruned", (3 * sum(g.M)) // 2, objectives=("tc",))
+    fam = compare(rc, oracle_mod, g, "pruned", (3 * sum(g.M)) // 2, objectives=("tc",))
+    assert fam.solve((3 * sum(g.M)) // 2, "tc").fill_kernel() == "k_fill_level_vec"
 
 
 @pytest.mark.parametrize("scale", [1, 8192])
@@ -264,6 +265,7 @@ def test_rows_of_2_to_the_31_cells(rc, T, scale):
         F, opt, arg = brute_table(g, "pruned", B)
         for objective in ("tc", "mc"):
             sol = fam.solve(B, objective)
+            assert sol.fill_kernel() == "k_fill_level"
             t = select(opt, F, objective)
             if t is None:
                 assert (sol.t_star, sol.m_star) == (-1, -1)

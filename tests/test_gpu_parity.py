@@ -229,7 +229,7 @@ def test_budgets_beyond_16_bits(rc, oracle_mod, B):
         fam = compare(rc, oracle_mod, g, "exact", B)
         sol = fam.solve(B, "tc")
         wide = min(B, 2 * sum(g.M)) > 65532
-        assert (sol.fill_kernel() == "k_fill_level") or not wide
+        assert (sol.fill_kernel() == "k_fill_level_vec") or not wide
         sol.free()
 
 
