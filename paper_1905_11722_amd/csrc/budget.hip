@@ -141,8 +141,8 @@ __global__ void k_mb_init(int32_t hi0, MbRange* range) {
   if (threadIdx.x < kMbRounds) range[threadIdx.x] = MbRange{-1, hi0};
 }
 
-__global__ void k_mb_end(const MbRange* range, int rounds, int32_t hi0, int64_t* host) {
-  *host = rounds > 0 ? range[rounds - 1].hi : hi0;
+__global__ void k_mb_end(const MbRange* range, int rounds, int32_t hi0, int64_t* out) {
+  *out = rounds > 0 ? range[rounds - 1].hi : hi0;
 }
 
 }  // namespace
@@ -151,6 +151,8 @@ __global__ void k_mb_end(const MbRange* range, int rounds, int32_t hi0, int64_t*
 // 2 M(V)) fits below the infinity code, LDS when [F][64] fits beside the
 // waves' partial minima.
 constexpr size_t kMbLds = 60 * 1024;
+constexpr size_t kMbHead = 256;                         // the rounds' intervals, the result
+static_assert(kMbRounds * sizeof(MbRange) <= kMbHead / 2, "the result lies in the other half");
 constexpr size_t kMbScratch = (size_t)32 << 20;         // f in global memory, all workgroups
 
 static int min_budget_kind(rc_family f, int32_t hi0) {
@@ -171,18 +173,19 @@ static int64_t min_budget_groups(rc_family f, int32_t hi0, int kind) {
 
 size_t min_budget_scratch_bytes(rc_family f, int32_t hi0) {
   const int kind = min_budget_kind(f, hi0);
-  size_t bytes = 256;                                    // the rounds' intervals
+  size_t bytes = kMbHead;
   if (kind == 2)
     bytes += sizeof(uint32_t) * (size_t)f->F * kLanes * (size_t)min_budget_groups(f, hi0, kind);
   return bytes;
 }
 
-hipError_t launch_min_budget(rc_family f, int32_t hi0, void* scratch, int64_t* host,
+hipError_t launch_min_budget(rc_family f, int32_t hi0, void* scratch, int64_t** out,
                              hipStream_t s) {
   const int kind = min_budget_kind(f, hi0);
   const int64_t groups = min_budget_groups(f, hi0, kind);
   MbRange* range = static_cast<MbRange*>(scratch);
-  uint32_t* fglob = reinterpret_cast<uint32_t*>(static_cast<char*>(scratch) + 256);
+  uint32_t* fglob = reinterpret_cast<uint32_t*>(static_cast<char*>(scratch) + kMbHead);
+  if (!*out) *out = reinterpret_cast<int64_t*>(static_cast<char*>(scratch) + kMbHead / 2);
   hipLaunchKernelGGL(k_mb_init, dim3(1), dim3(64), 0, s, hi0, range);
   int rounds = 0;
   for (int64_t span = (int64_t)hi0 + 1; span > 1 && rounds < kMbRounds; rounds++) {
@@ -201,7 +204,7 @@ hipError_t launch_min_budget(rc_family f, int32_t hi0, void* scratch, int64_t* h
     const int64_t parts = groups * kLanes + 1;
     span = (span + parts - 1) / parts;
   }
-  hipLaunchKernelGGL(k_mb_end, dim3(1), dim3(1), 0, s, range, rounds, hi0, host);
+  hipLaunchKernelGGL(k_mb_end, dim3(1), dim3(1), 0, s, range, rounds, hi0, *out);
   return hipGetLastError();
 }
 

@@ -76,7 +76,10 @@ Staging::Staging(size_t bytes) {
   size_t n = (size_t)64 << 10;
   while (n < bytes) n <<= 1;
   void* p = nullptr;
-  if (hipHostMalloc(&p, n, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) return;
+  if (hipHostMalloc(&p, n, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+    (void)hipGetLastError();               // no launch after it has failed
+    return;
+  }
   p_ = static_cast<char*>(p);
   n_ = n;
 }
@@ -320,7 +323,8 @@ int rc_graph_create(int32_t n, const int32_t* row_ptr, const int32_t* col_idx, c
   hipStream_t s = as_stream(stream);
   int st = RC_OK;
   // every array through one pinned buffer and one copy (eight copies from
-  // pageable memory waited for one after the other)
+  // pageable memory waited for one after the other); one copy from pageable
+  // memory where no pinned memory can be had
   int32_t *d_row_ptr = nullptr, *d_col_idx = nullptr;
   StageLayout lay;
   const size_t o_T = lay.add<int32_t>(n), o_M = lay.add<int32_t>(n),
@@ -329,12 +333,14 @@ int rc_graph_create(int32_t n, const int32_t* row_ptr, const int32_t* col_idx, c
                o_dp = lay.add<int32_t>(D + 1), o_rp = lay.add<int32_t>(n + 1),
                o_ci = lay.add<int32_t>(nnz);
   Staging stage(lay.bytes);
+  std::vector<char> pageable(stage.data() ? 0 : lay.bytes);
+  char* const host = stage.data() ? stage.data() : pageable.data();
   char* dev = static_cast<char*>(g->arena.get(lay.bytes));
-  if (!stage.data() || !dev) st = RC_E_NOMEM;
+  if (!dev) st = RC_E_NOMEM;
   g->num_pred_edges = (int32_t)pred_idx.size();
   if (st == RC_OK) {
-    auto put = [&](size_t off, const int32_t* host, int64_t count) {
-      if (count > 0) std::memcpy(stage.data() + off, host, sizeof(int32_t) * (size_t)count);
+    auto put = [&](size_t off, const int32_t* from, int64_t count) {
+      if (count > 0) std::memcpy(host + off, from, sizeof(int32_t) * (size_t)count);
       return reinterpret_cast<int32_t*>(dev + off);
     };
     g->dT = put(o_T, T, n);
@@ -346,7 +352,7 @@ int rc_graph_create(int32_t n, const int32_t* row_ptr, const int32_t* col_idx, c
     d_row_ptr = put(o_rp, row_ptr, row_ptr && n > 0 ? n + 1 : 0);
     d_col_idx = put(o_ci, col_idx, nnz);
     stage.in_flight();
-    if (hipMemcpyAsync(dev, stage.data(), lay.bytes, hipMemcpyHostToDevice, s) != hipSuccess)
+    if (hipMemcpyAsync(dev, host, lay.bytes, hipMemcpyHostToDevice, s) != hipSuccess)
       st = RC_E_DEVICE;
   }
   if (st == RC_OK) {
@@ -834,12 +840,15 @@ int rc_min_budget(rc_family f, void* stream, int64_t* B_min) {
     if (!f->bmin_scratch) return RC_E_NOMEM;
   }
   Staging stage(sizeof(int64_t));
-  if (!stage.data()) return RC_E_NOMEM;
   stage.in_flight();
-  RC_HIP(launch_min_budget(f, (int32_t)hi0, f->bmin_scratch, stage.at<int64_t>(0), s));
+  int64_t* out = stage.data() ? stage.at<int64_t>(0) : nullptr;
+  RC_HIP(launch_min_budget(f, (int32_t)hi0, f->bmin_scratch, &out, s));
+  int64_t found = 0;                       // no pinned memory: out is on the device
+  if (!stage.data())
+    RC_HIP(hipMemcpyAsync(&found, out, sizeof(found), hipMemcpyDeviceToHost, s));
   const int ss = sync_landed(stage, s);
   if (ss != RC_OK) return ss;
-  *B_min = *stage.at<int64_t>(0);
+  *B_min = stage.data() ? *out : found;
   return RC_OK;
 }
 

@@ -393,8 +393,9 @@ hipError_t launch_fill_ghost_batch(rc_solution* sols, int32_t nb, GParams* host_
 
 // ---- smallest feasible budget (budget.hip)
 size_t min_budget_scratch_bytes(rc_family f, int32_t hi0);
-// The smallest feasible budget to *host (pinned).
-hipError_t launch_min_budget(rc_family f, int32_t hi0, void* scratch, int64_t* host,
+// The smallest feasible budget to **out (pinned host memory; null: *out is
+// set to a place in scratch).
+hipError_t launch_min_budget(rc_family f, int32_t hi0, void* scratch, int64_t** out,
                              hipStream_t s);
 // Memory-indexed table of Algorithm 1's recursion (dual.hip): D[F * W]
 // uint32, W = min(B, M(V)) + 1; t and the least m of the objective into

@@ -69,3 +69,38 @@ def answer():
     for name, log in logs.items():
         assert log.count("E") in (2, 4), (name, log)     # 4: around the wavefront kernel too
         assert log.startswith("EL") and log.endswith("EL"), (name, log)
+
+
+def test_no_pinned_memory(child):
+    """rc_graph_create and rc_min_budget where pinned host memory cannot be
+    had and the pool holds none (a call whose wait reports an error gives its
+    buffer up): the same graph and budget as with it."""
+    got = child("""
+def answer():
+    g = W.random_dag(90, 0.06, 5, tmax=40, mmax=30)
+    calls.calls_refuse_pinned(1)
+    h = rc.Graph.create(g)
+    calls.calls_refuse_pinned(0)
+    fam, ref = h.build_family("pruned"), rc.Graph.create(g).build_family("pruned")
+    same = bool((fam.sets() == ref.sets()).all()) and fam.info == ref.info
+    want = ref.min_budget()
+    failed = 0
+    calls.calls_refuse_pinned(1)
+    for _ in range(16):
+        calls.calls_fail_sync(0)
+        try:
+            fam.min_budget()
+        except rc.RcError as e:
+            failed += e.status == rc.E_DEVICE
+        calls.calls_fail_sync(-1)
+    got = fam.min_budget()
+    try:
+        h.build_family("pruned")
+        pinned = True
+    except rc.RcError as e:
+        pinned = e.status != rc.E_NOMEM
+    calls.calls_refuse_pinned(0)
+    return dict(same=same, want=want, got=got, failed=failed, pinned=pinned)
+""")
+    assert got["same"] and got["got"] == got["want"]
+    assert got["failed"] == 16 and not got["pinned"]
