@@ -178,6 +178,7 @@ void* Arena::raw(size_t bytes) {
   if (alloc) {
     p = alloc(bytes, user);
   } else if (hipMalloc(&p, bytes) != hipSuccess) {
+    (void)hipGetLastError();               // no launch after it has failed
     p = nullptr;
   }
   if (p) ptrs.push_back(p);

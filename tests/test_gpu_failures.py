@@ -150,3 +150,29 @@ def test_refused_memory_is_reported_as_such(rc, monkeypatch, nodes, scale):
                 break
         assert done, name
     assert seen > 20
+
+
+def test_solve_after_a_refused_hipmalloc(oracle_mod):
+    """A table beyond the card's memory with the library's own hipMalloc:
+    RC_E_NOMEM, and the next solves are not reported as failed by the error
+    that hipMalloc left."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1905_11722_amd import rcdp as rc
+    n = 400
+    huge = W.Graph(n, [[v + 1] if v + 1 < n else [] for v in range(n)],
+                   [(1 << 31) - 3 - (n - 1)] + [1] * (n - 1), [1] * n)
+    hf = rc.Graph.create(huge, allocator=None).build_family("pruned")
+    assert 2 * hf.info["table_cells"] > 800 << 30
+    small = W.chain(30, seed=2)
+    sf = rc.Graph.create(small, allocator=None).build_family("pruned")
+    ref = oracle_mod.solve(small, "pruned", sum(small.M), "tc")
+    for call in (lambda: sf.solve(sum(small.M), "tc"), lambda: sf.solve_dominance(sum(small.M)),
+                 lambda: sf.sweep([sum(small.M)], "tc")[0][1]):
+        with pytest.raises(rc.RcError) as e:
+            hf.solve(2 * n, "tc")
+        assert e.value.status == rc.E_NOMEM
+        sol = call()
+        assert (sol.t_star, sol.m_star) == (ref.t_star, ref.m_star)
+        sol.free()
