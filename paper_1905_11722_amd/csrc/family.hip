@@ -264,12 +264,19 @@ __device__ __forceinline__ int enum_word(uint64_t Pw, uint64_t Sw, uint64_t pred
 }
 
 // The first levels in one workgroup, while the frontier fits LDS (frontier
-// sets x words <= kEnumWords): two barriers a level instead of two launches.
-// Small graphs end here: a 16-node chain, 16 levels, 14 us against 60, the
-// 40-node ladder's 40 levels 37 us against 247.  stop[0] = the first level
-// not expanded (n when done), stop[1] = sets found, stop[2] = overflow (host
-// memory).
+// sets x words <= kEnumWords) and its level is at most kEnumWork word tests
+// (sets x nodes x words, sixteen a thread): two barriers a level instead of
+// two launches.  Small graphs end here: a 16-node chain, 16 levels, 14 us
+// against 60, the 40-node ladder's 40 levels 37 us against 247.  A larger
+// level is faster over the whole chip.  Whole builds with the limit at 8 K /
+// 16 K / 32 K / 64 K / 128 K tests / LDS alone, in us: two chains of 60 nodes
+// (levels of up to 15 K tests) 575 / 559 / 555 / 556 / 559 / 571; of 100 (81
+// K) 1605 / 1613 / 1659 / 2053 / 3071 / 3100; of 150 (226 K) 4532 / 4562 /
+// 4537 / 4687 / 5581 / 11664; the antichain of 12 (11 K) 207 / 184 / 183 /
+// 183 / 182 / 187.  stop[0] = the first level not expanded (n when done),
+// stop[1] = sets found, stop[2] = overflow (host memory).
 constexpr int kEnumWords = 1024;
+constexpr int64_t kEnumWork = 16384;
 constexpr int kEnumMasks = 3072;          // n * words of the graphs taken
 constexpr int kEnumThreads = 1024;
 
@@ -335,7 +342,7 @@ __global__ __launch_bounds__(kEnumThreads) void k_enum_block(int n, int words,
     base += here;
     here = next;
     over = base + here > cap;
-    if (over || here * words > kEnumWords) {
+    if (over || here * words > kEnumWords || (int64_t)here * n * words > kEnumWork) {
       lev++;
       break;
     }

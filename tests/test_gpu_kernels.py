@@ -90,15 +90,27 @@ def test_level_fill_wide_levels(rc, oracle_mod, monkeypatch, seed, scale):
         compare(rc, oracle_mod, g, "exact", int(share * sum(g.M)))
 
 
+def parallel_chains(count, length):
+    """`count` chains of `length` nodes that do not meet: (length + 1)^count
+    lower sets."""
+    n = count * length
+    return W.Graph(n, [[v + 1] if (v + 1) % length else [] for v in range(n)],
+                   [1 + v % 9 for v in range(n)], [1 + v % 7 for v in range(n)])
+
+
 @pytest.mark.parametrize("graph", [W.chain(63), W.chain(64), W.chain(65), W.chain(130),
                                    W.chain(440), W.antichain(10), W.antichain(11),
-                                   W.ladder(24)],
+                                   W.ladder(24), parallel_chains(2, 64), parallel_chains(2, 65),
+                                   parallel_chains(2, 100), parallel_chains(3, 12),
+                                   W.antichain(13)],
                          ids=["chain63", "chain64", "chain65", "chain130", "chain440",
-                              "antichain10", "antichain11", "ladder24"])
+                              "antichain10", "antichain11", "ladder24", "chains2x64",
+                              "chains2x65", "chains2x100", "chains3x12", "antichain13"])
 def test_exact_enumeration(rc, oracle_mod, graph):
-    """The exact family where it ends in one workgroup, where a level (462 or
-    fewer sets, several words each) or the graph is too large for that, and
-    at caps that just hold it and just do not."""
+    """The exact family where it ends in one workgroup, where the graph is too
+    large for that, where a level is (handed over to one launch per level, in
+    sets of one, two, three and four words), and at caps that just hold it and
+    just do not."""
     ref = oracle_mod.family(graph, "exact")
     g = rc.Graph.create(graph)
     fam = g.build_family("exact", max_sets=ref.num_sets)
