@@ -87,8 +87,8 @@ def test_random_dags(rc, seed):
 
 
 def test_rows_of_several_tiles(rc):
-    """Rows of a few thousand cells: several 1024-cell tiles of the level
-    fill and 256-cell chunks of the front pass, with a ragged tail."""
+    """Rows of a few thousand cells: several 512-cell tiles of the level fill
+    and 2048-cell segments of the front passes, with a ragged tail."""
     g = W.random_dag(13, 0.3, 41, tmax=400, mmax=30)
     lo, hi = 2 * max(g.M), 2 * sum(g.M)
     for B in (lo, (lo + hi) // 2, hi):

@@ -41,16 +41,23 @@ def test_optarg_table_long_rows_short_lists(rc, oracle_mod):
     compare(rc, oracle_mod, g, "pruned", (3 * sum(g.M)) // 2, objectives=("tc",))
 
 
-@pytest.mark.parametrize("path", ["level", "wavefront", "wide", "ghost"])
+@pytest.mark.parametrize("path", ["level", "block", "wavefront", "wide", "ghost"])
 @pytest.mark.parametrize("total", [2040, 2048, 2049, 4097, 6151])
 def test_dominance_segments(rc, monkeypatch, path, total):
     """The weak fronts of rows that end just before, on and after a segment of
-    2048 cells, from the table of every fill."""
+    2048 cells, from the table of every fill (the block fill's from more rows,
+    so that those of a block are close in length)."""
     monkeypatch.setenv("RCDP_FILL", path)
-    g = W.chain(9, seed=total, tmax=total // 9, mmax=40)
-    g.T[4] += total - sum(g.T)
+    nodes = 160 if path == "block" else 9
+    g = W.chain(nodes, seed=total, tmax=total // nodes, mmax=40)
+    if path == "block":
+        g.T = [total // nodes + (v < total % nodes) for v in range(nodes)]
+    else:
+        g.T[4] += total - sum(g.T)
     for B in (2 * max(g.M) + 8, sum(g.M), 2 * sum(g.M)):
         compare_dominance(rc, g, "exact", B)
+    sol = rc.Graph.create(g).build_family("exact").solve_dominance(sum(g.M))
+    assert (sol.fill_kernel() == "k_fill_block") == (path == "block")
 
 
 @pytest.mark.parametrize("width", [1, 7, 8, 9, 64, 65, 2048, 2049, 131073])
@@ -129,7 +136,7 @@ def test_fill_switched_after_the_build(rc, oracle_mod, monkeypatch, name):
     c = W.case(name)
     fam = rc.Graph.create(c.graph).build_family(c.mode)
     ref = oracle_mod.solve(c.graph, c.mode, c.B, "tc").table()
-    for path in ("wide", "wavefront", "ghost", "level", None):
+    for path in ("wide", "wavefront", "block", "ghost", "level", None):
         if path:
             monkeypatch.setenv("RCDP_FILL", path)
         else:
@@ -143,17 +150,22 @@ def test_fill_switched_after_the_build(rc, oracle_mod, monkeypatch, name):
 
 @pytest.mark.parametrize("path", ["wide", "level", None])
 def test_sweep_of_many_budgets(rc, oracle_mod, monkeypatch, path):
-    """More tables than one preparation or selection launch takes, feasible
-    and infeasible, 16- and 32-bit cells side by side."""
+    """More tables than one preparation, starting or selection launch takes
+    (64), feasible and infeasible: of 16-bit cells alone, and of both widths
+    side by side, one after the other and in turn."""
     if path:
         monkeypatch.setenv("RCDP_FILL", path)
     g = W.random_dag(9, 0.3, 12, tmax=60, mmax=9000)
     top = 2 * sum(g.M)
-    assert top > 65532
-    budgets = [(j * top) // 69 for j in range(70)] + [65532, 65533]
+    assert top > 65533 + 70
+    narrow = [(j * 65532) // 69 for j in range(70)]
+    wide = [65533 + (j * (top - 65533)) // 69 for j in range(70)]
+    both = [B for pair in zip(narrow, wide) for B in pair]
     fam = rc.Graph.create(g).build_family("exact")
-    for objective in ("tc", "mc"):
+    for budgets, objective in ((narrow, "tc"), (narrow + wide, "mc"), (both[:20], "tc")):
         sols = fam.sweep(budgets, objective)
+        if path == "wide":
+            assert all((sol.fill_kernel() == "k_fill_wide") == (B <= 65532) for B, sol in sols)
         for B, sol in sols:
             ref = oracle_mod.solve(g, "exact", B, objective)
             assert (sol.t_star, sol.m_star) == (ref.t_star, ref.m_star), B
@@ -181,12 +193,26 @@ def test_dual_blocks_branching(rc):
 @pytest.mark.parametrize("nodes,tmax", [(2, 3), (15, 9), (16, 9), (17, 40), (31, 2), (32, 9),
                                         (33, 50), (50, 57), (100, 9), (20, 120)])
 def test_block_fill(rc, oracle_mod, monkeypatch, nodes, tmax):
-    """The block fill with blocks cut short, halos of a few cells up to the
-    window (and beyond it: the level launches), rows of one to many columns."""
+    """The block fill with blocks cut short, halos of a few cells to nearly
+    the window, rows of one to many columns."""
     monkeypatch.setenv("RCDP_FILL", "block")
     g = W.chain(nodes, seed=nodes, tmax=tmax, mmax=9)
     for B in (2 * max(g.M) + 6, sum(g.M), 2 * sum(g.M)):
-        compare(rc, oracle_mod, g, "exact", B)
+        fam = compare(rc, oracle_mod, g, "exact", B)
+    assert fam.solve(sum(g.M), "tc").fill_kernel() == "k_fill_block"
+
+
+@pytest.mark.parametrize("halo,kernel", [(863, "k_fill_block"), (864, "k_fill_block"),
+                                         (865, "k_fill_level_vec")])
+def test_block_fill_widest_halo(rc, oracle_mod, monkeypatch, halo, kernel):
+    """Halos up to the block fill's window, and the level launches beyond it:
+    row 1 of a chain has one cell, row 16 the first fifteen nodes' time more."""
+    monkeypatch.setenv("RCDP_FILL", "block")
+    g = W.chain(40, seed=halo, tmax=9, mmax=9)
+    g.T[3] += halo - sum(g.T[:15])
+    for B in (2 * max(g.M) + 6, sum(g.M), 2 * sum(g.M)):
+        fam = compare(rc, oracle_mod, g, "exact", B)
+    assert fam.solve(sum(g.M), "tc").fill_kernel() == kernel
 
 
 @pytest.mark.parametrize("seed", range(4))

@@ -311,15 +311,17 @@ def test_full_size_cases(rc, oracle_mod, name):
 
 
 # ---------------------------------------------------------------- fill paths
-# The library picks a persistent wavefront fill for wide tables and
-# per-level launches for narrow ones; RCDP_FILL forces one: "level", the
-# row-push wavefront ("wavefront", fixed blocks of 8 targets), the
+# The library picks a persistent wavefront fill for wide tables and launches
+# per level or per block of 16 targets for narrow ones; RCDP_FILL forces one:
+# "level", "block" (the level launches where the rows of a block differ too
+# much in length, as on the wide rows here), the row-push wavefront
+# ("wavefront", fixed blocks of 8 targets), the
 # split-panel wavefront ("wide", fixed blocks, panel records shared among
 # waves) or the ghost-zone wavefront ("ghost", blocks cut to fit its
 # recomputed halo).  Rows wider than one column make the wavefront's
 # cross-workgroup waits real.
 
-PATHS = ["level", "wavefront", "wide", "ghost"]
+PATHS = ["level", "block", "wavefront", "wide", "ghost"]
 
 WIDE = [(n, p, seed) for seed, (n, p) in enumerate(
     [(n, p) for n in (4, 6, 8, 10, 12) for p in (0.2, 0.45, 0.7)])]
@@ -357,6 +359,19 @@ def test_fill_path_is_reported(rc, monkeypatch, path, kernel):
     sol = fam.solve(2 * sum(g.M), "tc")
     assert sol.fill_kernel() == kernel
     sol.free()
+
+
+def test_block_fill_is_reported(rc, monkeypatch):
+    """The block fill, forced and (a chain of short rows) chosen."""
+    c = W.case("chain16")
+    for path in ("block", None):
+        if path:
+            monkeypatch.setenv("RCDP_FILL", path)
+        else:
+            monkeypatch.delenv("RCDP_FILL")
+        sol = rc.Graph.create(c.graph).build_family(c.mode).solve(c.B, "tc")
+        assert sol.fill_kernel() == "k_fill_block"
+        sol.free()
 
 
 @pytest.mark.parametrize("name,objective,kernel", [("densenet121", "tc", "k_trace_follow"),
