@@ -391,18 +391,18 @@ class Solution:
                "rc_solution_fill_kernel_ms")
         return ms.value
 
+    # by path; the last one is the level fill (paths 0 and 4) of rows beyond 2^31 bytes
     FILL_KERNELS = ("k_fill_level_vec", "k_fill_blocked", "k_fill_ghost", "k_fill_wide",
-                    "k_fill_level_vec", "k_fill_block")
+                    "k_fill_level_vec", "k_fill_block", "k_fill_level")
 
     def fill_kernel(self):
-        """Name of the fill kernel the solve ran (see rc_solution_fill_path).
-        The level fill of rows beyond 2^31 bytes is k_fill_level."""
+        """Name of the fill kernel the solve ran (see rc_solution_fill_path)."""
         path = ctypes.c_int32()
         _check(load_library().rc_solution_fill_path(self._h, ctypes.byref(path)),
                "rc_solution_fill_path")
         cell = {0: 2, 4: 4}.get(path.value, 0)             # bytes, of the level fill
         if (self.family.info["max_row"] + 64) * cell >= 2 ** 31 - 1:
-            return "k_fill_level"
+            return self.FILL_KERNELS[-1]
         return self.FILL_KERNELS[path.value]
 
     TRACE_KERNELS = ("k_trace", "k_trace_follow")
