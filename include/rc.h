@@ -143,7 +143,7 @@ typedef struct {
  *    family and solution made from it (NULL alloc: hipMalloc).
  * Errors: RC_E_ARG (NULL pointer, n < 0, n > 4096, index out of range,
  * row_ptr not monotone), RC_E_CYCLE (cycle or self-loop), RC_E_COST
- * (T_v or M_v < 1), RC_E_OVERFLOW (T(V) >= 2^31 - 1 or M(V) >= 2^31 / 4),
+ * (T_v or M_v < 1), RC_E_OVERFLOW (T(V) >= 2^31 - 2 or M(V) >= 2^31 / 4),
  * RC_E_NOMEM, RC_E_DEVICE.
  */
 int rc_graph_create(int32_t n, const int32_t* row_ptr_host, const int32_t* col_idx_host,

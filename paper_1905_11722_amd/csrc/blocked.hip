@@ -437,7 +437,8 @@ __global__ __launch_bounds__(kThreads) void k_fill_blocked(BParams p0, const BPa
             if (!out && has_half(v, kPendM)) {
               *ch = (u32x4)(kUnset | (kUnset << 16));
               wait_lds();
-              dma16(p.m + (E - cC + 8 * lane), __builtin_amdgcn_readfirstlane(lds_addr(&s_push[rb + C])));
+              dma16(p.m + (E - cC + 8 * lane),
+                    __builtin_amdgcn_readfirstlane(lds_addr(&s_push[rb + C])));
               unset = true;
             }
           }
@@ -455,8 +456,9 @@ __global__ __launch_bounds__(kThreads) void k_fill_blocked(BParams p0, const BPa
                 if (!out && has_half(v, kPendM)) {
                   *ch = (u32x4)(kUnset | (kUnset << 16));
                   wait_lds();
+                  const int at = 2 * RB + k * FB + 512 * i;
                   dma16(p.m + (astart + 8 * (int64_t)kc),
-                        __builtin_amdgcn_readfirstlane(lds_addr(&s_push[2 * RB + k * FB + 512 * i])));
+                        __builtin_amdgcn_readfirstlane(lds_addr(&s_push[at])));
                   unset = true;
                 }
               }

@@ -144,7 +144,8 @@ __global__ __launch_bounds__(64 * kJB) void k_blk_dense(int64_t F, int64_t nblk,
   }
   for (int64_t x = threadIdx.x; x < j0; x += blockDim.x) R.src[base + x] = (int32_t)x;
   int4* e4 = reinterpret_cast<int4*>(R.e + base * kJB);
-  for (int64_t x = threadIdx.x; x < j0 * kJB / 4; x += blockDim.x) e4[x] = make_int4(-1, -1, -1, -1);
+  for (int64_t x = threadIdx.x; x < j0 * kJB / 4; x += blockDim.x)
+    e4[x] = make_int4(-1, -1, -1, -1);
   for (int x = threadIdx.x; x < kJB * kJB; x += blockDim.x) R.tri_e[b * kJB * kJB + x] = -1;
   __syncthreads();
   const int slot = threadIdx.x / 64;                    // a wave per target
@@ -171,8 +172,8 @@ __global__ __launch_bounds__(64 * kJB) void k_blk_dense(int64_t F, int64_t nblk,
 }  // namespace
 
 hipError_t launch_blk_dense(rc_family f, hipStream_t s) {
-  hipLaunchKernelGGL(k_blk_dense, dim3((unsigned)f->nblk), dim3(64 * kJB), 0, s, f->F, f->nblk, f->w,
-                     f->pred_ptr, f->pidx, f->pdt, f->pdm, f->pc, f->bstart, f->rec_ptr,
+  hipLaunchKernelGGL(k_blk_dense, dim3((unsigned)f->nblk), dim3(64 * kJB), 0, s, f->F, f->nblk,
+                     f->w, f->pred_ptr, f->pidx, f->pdt, f->pdm, f->pc, f->bstart, f->rec_ptr,
                      f->wrec_ptr, f->rec);
   return hipGetLastError();
 }
@@ -184,8 +185,8 @@ hipError_t launch_blk_count(rc_family f, int64_t nblk, int64_t* count, hipStream
 }
 
 hipError_t launch_blk_fill(rc_family f, int64_t nblk, hipStream_t s) {
-  hipLaunchKernelGGL(k_blk_fill, dim3((unsigned)nblk), dim3(256), 0, s, f->bstart, f->w, f->pred_ptr,
-                     f->pidx, f->pdt, f->pdm, f->pc, f->rec_ptr, f->rec);
+  hipLaunchKernelGGL(k_blk_fill, dim3((unsigned)nblk), dim3(256), 0, s, f->bstart, f->w,
+                     f->pred_ptr, f->pidx, f->pdt, f->pdm, f->pc, f->rec_ptr, f->rec);
   return hipGetLastError();
 }
 

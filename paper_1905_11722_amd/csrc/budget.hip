@@ -41,9 +41,10 @@ typedef const __attribute__((address_space(4))) int64_t cint64;
 
 // 64 budgets of a round, one per lane, with f of every set for them ([F][64])
 // in LDS when it fits, else in the workgroup's part of global scratch.  The
-// pairs of a target are spread over kMbWaves waves: wave w, lane q holds pair p0 + kMbWaves q + w of the target (one coalesced
-// load per wave, issued a target ahead), every wave relaxes its pairs for
-// the 64 budgets (lane = budget, pair values taken with readlane), and the
+// pairs of a target are spread over kMbWaves waves: wave w, lane q holds pair
+// p0 + kMbWaves q + w of the target (one coalesced load per wave, issued a
+// target ahead), every wave relaxes its pairs for the 64 budgets (lane =
+// budget, pair values taken with readlane), and the
 // waves' partial minima meet in LDS.  Two barriers per target instead of a
 // dependent scalar load per pair.
 constexpr int kMbWaves = 16;

@@ -405,15 +405,15 @@ __global__ __launch_bounds__(kDualTraceThreads) void k_dual_trace(
   }
   if (t != 0 || m != 0) bad = true;                  // the walk must end at (empty set, 0, 0)
   __syncthreads();
-  finish_schedule<kDualTraceThreads>(bad ? -1 : k, n, words, fstride, bits, bd, A, T, M, T_total, chain, out,
-                      s_chain, s_M);
+  finish_schedule<kDualTraceThreads>(bad ? -1 : k, n, words, fstride, bits, bd, A, T, M, T_total,
+                                     chain, out, s_chain, s_M);
 }
 
 }  // namespace
 
 // Rows per block of k_dual_block (8 or 4; 0: the halo leaves a workgroup's
-// window, or blocks of 2 would fit, which cost more than levels) and every block's halo, the largest difference of M(L) over its
-// sets.
+// window, or blocks of 2 would fit, which cost more than levels) and every
+// block's halo, the largest difference of M(L) over its sets.
 int32_t dual_block_rows(int64_t F, const int32_t* Msum, std::vector<int32_t>* halo) {
   for (int32_t rows = kDualSlots; rows >= kDualSlots / 2; rows /= 2) {
     halo->clear();

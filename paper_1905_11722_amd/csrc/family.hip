@@ -170,9 +170,10 @@ constexpr int kClosureThreads = 1024;
 constexpr int kClosureItems = 4;        // items per thread: n * words <= 4096
 static_assert(kClosureWords <= kClosureThreads / kWave, "a wave per word");
 
-__device__ __forceinline__ uint64_t row_word(uint64_t x, int lane) {
-  return (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane) |
-         ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), lane) << 32);
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t x, int l) {
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, l);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(x >> 32), l);
+  return ((uint64_t)hi << 32) | lo;
 }
 
 __global__ __launch_bounds__(kClosureThreads) void k_ancestors_closure(int n, int words,
@@ -205,8 +206,8 @@ __global__ __launch_bounds__(kClosureThreads) void k_ancestors_closure(int n, in
       for (int k = 0; k < 64; k++) {
         if (k % 16 == 0 && row0 + k * words >= row1) break;   // lanes past the last row hold 0
         const uint64_t take = 0 - (d >> k & 1);
-        x |= row_word(x, k) & take;
-        d |= row_word(d, k) & take;
+        x |= readlane_u64(x, k) & take;
+        d |= readlane_u64(d, k) & take;
       }
     }
     __syncthreads();
@@ -620,12 +621,6 @@ __global__ __launch_bounds__(256) void k_set_quantities(
 // of a union is then one wave OR reduction, a sum one wave sum.
 constexpr int kLaneWords = 8;
 
-__device__ __forceinline__ uint64_t readlane_u64(uint64_t x, int l) {
-  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, l);
-  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(x >> 32), l);
-  return ((uint64_t)hi << 32) | lo;
-}
-
 __device__ __forceinline__ uint64_t wave_or_u64(uint64_t x) {
   for (int off = 32; off > 0; off >>= 1) x |= __shfl_xor(x, off, kWave);
   return x;
@@ -852,8 +847,8 @@ __global__ __launch_bounds__(256) void k_pair_write(
                                ? mask[j * mw + x / kWave] & ((1ull << (x & (kWave - 1))) - 1)
                                : 0ull;
     const int nw = (int)((j + kWave - 1) / kWave);
-    sp.split[threadIdx.x / 2][2 * j + threadIdx.x % 2] = x / kWave < nw ? p0 + s_pre[x / kWave] + __popcll(below)
-                                                : pred_ptr[j + 1];
+    sp.split[threadIdx.x / 2][2 * j + threadIdx.x % 2] =
+        x / kWave < nw ? p0 + s_pre[x / kWave] + __popcll(below) : pred_ptr[j + 1];
   }
   const int sj = size[j];
   const int64_t tj = (int64_t)Tsum[j] - Tbd[j], mbj = Mbd[j], cj = 2 * (int64_t)Msum[j] + A[j];
@@ -954,7 +949,8 @@ struct ShapeOut {
 };
 
 __global__ __launch_bounds__(kScanThreads) void k_shape(int64_t F, const int32_t* size,
-                                                        const int32_t* w, const int32_t* Msum, const int64_t* counts,
+                                                        const int32_t* w, const int32_t* Msum,
+                                                        const int64_t* counts,
                                                         const int64_t* walg, int64_t* row_off,
                                                         int64_t* pred_ptr, DevStatus* st,
                                                         ShapeOut o) {

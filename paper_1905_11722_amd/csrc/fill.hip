@@ -46,20 +46,6 @@ __device__ __forceinline__ constexpr uint32_t cell_inf() {
   return sizeof(T) == 2 ? 0xFFFFu : 0xFFFFFFFFu;
 }
 
-__device__ __forceinline__ int64_t wave_sum_i64(int64_t x) {
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, kWave);
-  return x;
-}
-
-__device__ __forceinline__ int64_t word_cost(uint64_t bits, int word, const int32_t* c) {
-  int64_t s = 0;
-  while (bits) {
-    s += c[word * 64 + __builtin_ctzll(bits)];
-    bits &= bits - 1;
-  }
-  return s;
-}
-
 // Tables of one launch (z, or y of the selection).
 constexpr int kTables = 64;
 struct InitTables {
@@ -261,8 +247,8 @@ __device__ __forceinline__ void level_tile(int32_t tile, int32_t wj, int64_t rj,
   constexpr int kB = (int)sizeof(T);
   constexpr int kVec = 16 / kB;
   constexpr int kTileCells = kWave * kVec;
-  const int32_t hi_t = wj - tile * kTileCells;                   // the tile is [hi_t - kTileCells, hi_t)
-  if (hi_t <= 0) return;                                         // the whole workgroup leaves
+  const int32_t hi_t = wj - tile * kTileCells;         // the tile is [hi_t - kTileCells, hi_t)
+  if (hi_t <= 0) return;                               // the whole workgroup leaves
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
   const int32_t t0 = hi_t - kVec * (lane + 1);                   // the lane's first cell
@@ -752,7 +738,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(SelectTables tabs,
 // T(V \ U_k).  At each step the workgroup scans the predecessors of L'
 // (ascending family index, kTraceThreads at a time) for optarg[L', t']:
 // the smallest index whose cell passes the budget test and reproduces the
-// target value.  The re-evaluation runs on wave 0, lane w holding word w.
+// target value.
 constexpr int kTraceThreads = 512;
 constexpr int kTraceLds = 2048;       // families up to this size keep their per-set arrays in LDS
 
@@ -831,7 +817,8 @@ __global__ __launch_bounds__(kTraceThreads) void k_trace(
       const bool hit = inrow && x != cell_inf<Cell>() && (int64_t)x <= (int64_t)Beff - c &&
                        (uint32_t)(x + dm) == mj;
       const unsigned long long bal = __ballot(hit);
-      if (lane == 0) s_first[par][wave] = bal ? wave * kWave + __ffsll((long long)bal) - 1 : INT32_MAX;
+      if (lane == 0)
+        s_first[par][wave] = bal ? wave * kWave + __ffsll((long long)bal) - 1 : INT32_MAX;
       s_src[par][tid] = i;
       s_dt[par][tid] = dt;
       __syncthreads();
@@ -855,8 +842,8 @@ __global__ __launch_bounds__(kTraceThreads) void k_trace(
   }
   if (t != 0) bad = true;                            // the walk must end at (empty, 0)
   __syncthreads();
-  finish_schedule<kTraceThreads>(bad ? -1 : k, n, words, fstride, bits, bd, A, T, M, T_total, chain, out,
-                      s_chain, s_M);
+  finish_schedule<kTraceThreads>(bad ? -1 : k, n, words, fstride, bits, bd, A, T, M, T_total,
+                                 chain, out, s_chain, s_M);
 }
 
 // The traceback through an optarg slice.  When t* is small, every step of
@@ -959,8 +946,9 @@ __global__ __launch_bounds__(kArgWaves* kWave) void k_trace_args(
   nxt[j * S + t] = e;
 }
 
-// optarg of the whole table when it is small: 64 cells of target blockIdx.y
-// per workgroup, its predecessor list over the workgroup's waves as in
+// optarg of the whole table where lists are long or the table is small (the
+// rule stands at launch_arg_all): 64 cells of target blockIdx.y per
+// workgroup, its predecessor list over the workgroup's waves as in
 // k_trace_args.
 template <class Cell>
 __global__ __launch_bounds__(kArgWaves* kWave) void k_arg_split(
@@ -1043,8 +1031,8 @@ __global__ __launch_bounds__(kTraceThreads) void k_trace_follow(
     s_k = bad ? -1 : k;
   }
   __syncthreads();
-  finish_schedule<kTraceThreads>(s_k, n, words, fstride, bits, bd, A, T, M, T_total, chain, out, s_chain,
-                      s_M);
+  finish_schedule<kTraceThreads>(s_k, n, words, fstride, bits, bd, A, T, M, T_total, chain, out,
+                                 s_chain, s_M);
 }
 
 }  // namespace
@@ -1354,10 +1342,10 @@ hipError_t launch_trace(rc_solution sol, const ScheduleOut& out, hipStream_t s) 
                      : trace_t<uint16_t>(sol, sol->m, out, s);
 }
 
-// optarg of the whole table in as few launches as the rows' lengths allow: no cell's optarg depends on
-// another's, so the rows need no order (one launch per size level, each
-// waiting for its longest predecessor list, took 5.4 ms on resnet50_t10's
-// 167 levels).  A list of at least 64 pairs on average is split over the
+// optarg of the whole table in as few launches as the rows' lengths allow: no
+// cell's optarg depends on another's, so the rows need no order (one launch
+// per size level, each waiting for its longest predecessor list, took 5.4 ms
+// on resnet50_t10's 167 levels).  A list of at least 64 pairs on average is split over the
 // waves of a workgroup, and so are the lists of a table too small to fill
 // the chip: there the longest list decides the time.  On long rows with
 // short lists (U-Net: 25 pairs, 61 M cells) the extra waves only repeat the

@@ -906,7 +906,8 @@ int rc_family_sets(rc_family f, uint64_t* bits_host, void* stream) {
   hipStream_t s = as_stream(stream);
   std::vector<uint64_t> wm((size_t)words * f->fstride);
   if (!wm.empty())
-    RC_HIP(hipMemcpyAsync(wm.data(), f->bits, sizeof(uint64_t) * wm.size(), hipMemcpyDeviceToHost, s));
+    RC_HIP(hipMemcpyAsync(wm.data(), f->bits, sizeof(uint64_t) * wm.size(),
+                          hipMemcpyDeviceToHost, s));
   RC_HIP(hipStreamSynchronize(s));
   for (int64_t i = 0; i < f->F; i++)
     for (int w = 0; w < words; w++) bits_host[i * words + w] = wm[(size_t)w * f->fstride + i];
@@ -939,11 +940,12 @@ static void destroy_events(rc_solution sol) {
 // 6 TB/s, partly beside each other; a block launch of 16 rows about 9.5 us,
 // 27 ns per cell of its halo and the same reads.  Few levels of many sets or of
 // very long rows take the level launches, many levels of short rows the
-// blocks, of long ones the wavefront (ms, level / block / wavefront:
-// densenet121_t10 2.24 / 0.29 / 0.92, resnet50_t10 0.66 / 0.12 / 0.34, a
-// 16-node chain 0.046 / 0.013 / 0.039, layered24 0.077 / 0.084 / 0.11,
-// ladder40 0.16 / 0.35 / 0.53, U-Net 0.44 / - / 0.65, ResNet-50 0.86 / - /
-// 0.63, DenseNet-121 4.0 / - / 1.7).
+// blocks, of long ones the wavefront.  Whole fills in ms, level / block / the
+// wavefront that the family takes, its records included: densenet121_t10 2.27
+// / 0.30 / 0.94, resnet50_t10 0.68 / 0.13 / 0.35, a 16-node chain 0.065 /
+// 0.017 / 0.061, layered24 0.097 / 0.094 / 0.12, ladder40 0.18 / 0.35 / 0.55,
+// U-Net 0.45 / - / 0.68, ResNet-50 0.88 / - / 0.66, DenseNet-121 4.1 / - /
+// 1.8.
 static int cheapest_fill(rc_family f) {
   const int64_t levels = (int64_t)f->level_ptr.size() - 1;
   const int64_t slots = (f->blk_kind == kBlocksGhost ? 3 : wide_slots_per_cu(3)) *
@@ -1099,10 +1101,6 @@ static float elapsed(hipEvent_t a, hipEvent_t b) {
   if (!a || !b || hipEventElapsedTime(&ms, a, b) != hipSuccess) return -1.f;
   return ms;
 }
-
-extern "C" {
-
-}  // extern "C"
 
 // Status of a launcher that failed: it reports the family's allocator
 // returning NULL as hipErrorOutOfMemory.

@@ -399,7 +399,7 @@ hipError_t launch_min_budget(rc_family f, int32_t hi0, void* scratch, int64_t** 
                              hipStream_t s);
 // Memory-indexed table of Algorithm 1's recursion (dual.hip): D[F * W]
 // uint32, W = min(B, M(V)) + 1; t and the least m of the objective into
-// st->t_sel / st->m_sel (-1 when no chain reaches V)  level_pairs[l]: the
+// st->t_sel / st->m_sel (-1 when no chain reaches V).  level_pairs[l]: the
 // most pairs of a target of size level l.  e0/e1 (may be null) are recorded
 // around the table's launches.
 hipError_t launch_dual(rc_family f, const std::vector<int64_t>& level_pairs, int32_t B, int32_t W,

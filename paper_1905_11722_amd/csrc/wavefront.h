@@ -95,7 +95,7 @@ __device__ __forceinline__ WinDma win_dma(const int32_t* hd, bool valid, int32_t
   const int32_t emin = __builtin_amdgcn_readfirstlane(g.x);
   const int32_t far = __builtin_amdgcn_readfirstlane(g.y);     // emax + P_i
   const bool live = valid && u0 + emin <= 0 && u0 + cw - 1 + far >= 0;
-  const int32_t to_end = 1 - u0 - er;                          // cells from the window start to the row end
+  const int32_t to_end = 1 - u0 - er;          // cells from the window start to the row end
   WinDma w;
   w.base = m + ((((int64_t)bhi << 32) | blo) + u0);
   w.hi = live ? to_end >> 3 : 0;

@@ -106,7 +106,8 @@ __device__ __forceinline__ Td load_td(__amdgpu_buffer_rsrc_t rt, int32_t r) {
   typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
   const int32_t o = r * kWTd * 4;
   const i32x4 a = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rt, 0, o, 0));
-  const i32x4 d = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rt, 0, o + 16, 0));
+  const i32x4 d =
+      __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rt, 0, o + 16, 0));
   Td t;
   t.tau[0] = as_u16x2(a.x);
   t.tau[1] = as_u16x2(a.y);
@@ -141,10 +142,10 @@ __device__ __forceinline__ void load_window(__amdgpu_buffer_rsrc_t rm, int32_t n
 // budgets no cell of its source row can exceed (kNoTest, set with the record)
 // takes the addition and the minimum alone, two of the four instructions,
 // where kSkip: with one panel wave per workgroup, whose launches fill every
-// slot of the GPU (a sweep of 32 ResNet-50 budgets, 8.46 -> 8.13 ms; two
-// thirds of its panel work are such records).  With three the branch costs
-// more than it saves (DenseNet-121's step 2.00 -> 2.18 ms, 17% such records),
-// and the tested form gives the same values.
+// slot of the GPU (a sweep of 32 ResNet-50 budgets, 8.46 -> 8.13 ms; 63% of
+// its panel work are such records).  With three the branch costs more than it
+// saves (DenseNet-121's step 2.00 -> 2.18 ms; 2.3% of its panel records, 0.7%
+// of the panel work), and the tested form gives the same values.
 template <bool kSkip>
 __device__ __forceinline__ void relax_record(const Td& t, const uint32_t (&x)[4], Acc& nx) {
   if (kSkip &&
@@ -301,7 +302,8 @@ __device__ __forceinline__ void push_pair4(RowLds& L, int q, const u16x2 (&x)[4]
   for (int k = 0; k < 4; k++) v[k] = a[64 * k];
 #pragma unroll
   for (int k = 0; k < 4; k++)
-    a[64 * k] = __builtin_bit_cast(uint32_t, relax2(__builtin_bit_cast(u16x2, v[k]), x[k], tau, dm));
+    a[64 * k] =
+        __builtin_bit_cast(uint32_t, relax2(__builtin_bit_cast(u16x2, v[k]), x[k], tau, dm));
 }
 
 // Issues the loads of the row's cells at u = ubase + lane + 64 k (k < 4);
@@ -404,7 +406,8 @@ __device__ __forceinline__ bool row_step(const WParams& p, int32_t c, int s, int
     const int32_t e0 = lane_word(pdv, kWpE + 2 * q), e1 = lane_word(pdv, kWpE + 2 * q + 1);
     const bool n0 = e0 >= 0 && e0 <= kWH, n1 = e1 >= 0 && e1 <= kWH;
     const int32_t o0 = n0 ? e0 : 0, o1 = n1 ? e1 : 0;     // every read in range, used or not
-    const u16x2 tau = as_u16x2(lane_word(pdv, kWpTau + q)), dm = as_u16x2(lane_word(pdv, kWpDm + q));
+    const u16x2 tau = as_u16x2(lane_word(pdv, kWpTau + q));
+    const u16x2 dm = as_u16x2(lane_word(pdv, kWpDm + q));
     uint16_t r0[4], r1[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) {
@@ -452,9 +455,8 @@ __device__ __forceinline__ bool row_step(const WParams& p, int32_t c, int s, int
 // table: 14% faster with four than with three, the batched sweep 20%).
 template <int NP>
 __global__ __launch_bounds__((NP + 1) * kWave)
-__attribute__((amdgpu_waves_per_eu((wide_slots_per_cu(NP) * (NP + 1) + 3) / 4))) void k_fill_wide(WParams p0,
-                                                                        const WParams* ps,
-                                                                        int32_t nb) {
+__attribute__((amdgpu_waves_per_eu((wide_slots_per_cu(NP) * (NP + 1) + 3) / 4))) void
+k_fill_wide(WParams p0, const WParams* ps, int32_t nb) {
   __shared__ __attribute__((aligned(16))) uint32_t s_part[NP][kJB / 2 * 4][kWave];
   __shared__ __attribute__((aligned(16))) RowLds s_rows;
   __shared__ int32_t s_col, s_abort;
@@ -533,7 +535,8 @@ __attribute__((amdgpu_waves_per_eu((wide_slots_per_cu(NP) * (NP + 1) + 3) / 4)))
             u16x2 m = __builtin_bit_cast(u16x2, s_rows.nxt[q][lane + 64 * k]);
 #pragma unroll
             for (int w = 0; w < NP; w++)
-              m = __builtin_elementwise_min(m, __builtin_bit_cast(u16x2, s_part[w][q * 4 + k][lane]));
+              m = __builtin_elementwise_min(
+                  m, __builtin_bit_cast(u16x2, s_part[w][q * 4 + k][lane]));
             s_rows.acc[q][lane + 64 * k] = __builtin_bit_cast(uint32_t, m);
             s_rows.nxt[q][lane + 64 * k] = kInfPair;
           }
@@ -649,7 +652,8 @@ __device__ __forceinline__ uint32_t live_slots(const BlockRecords& R, int64_t r,
 __device__ void setup_records(int64_t b, int32_t F, int32_t K, int32_t Beff, const int32_t* w,
                               const int64_t* row_off, const int64_t* rec_ptr,
                               const BlockRecords& R, const int64_t* wptr, const int32_t* Msum,
-                              char* slab, const WSlab& o, uint64_t* s_key, int32_t* s_n, int32_t* s_emax) {
+                              char* slab, const WSlab& o, uint64_t* s_key, int32_t* s_n,
+                              int32_t* s_emax) {
   const int64_t end = panel_end(b);
   const int64_t rbase = rec_ptr[b];
   if (threadIdx.x == 0) {
@@ -800,7 +804,7 @@ __device__ void setup_push(int64_t b, int s, int64_t F, int64_t nblk, int32_t Be
   for (int t = 0; t < 2 * kJB; t++) {
     d[kWpE + t] = e[t];
     if (e[t] < 0) continue;
-    const int64_t jt = t < kJB ? j0 + t : j0 + t;     // slot t of the next block is j0 + kJB + t - kJB
+    const int64_t jt = j0 + t;      // slots 8..15 are the next block's rows, from j0 + kJB on
     maxPt = max(maxPt, w[jt] - 1);
     emax = max(emax, e[t]);
     if (e[t] <= kWH) {
