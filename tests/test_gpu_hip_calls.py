@@ -4,6 +4,7 @@ which notes a few calls and passes them on or refuses them."""
 
 import json
 import os
+import shutil
 import subprocess
 import sys
 
@@ -29,6 +30,8 @@ def child(tmp_path_factory):
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
+    if shutil.which("gcc") is None:
+        pytest.skip("no C compiler")
     lib = str(tmp_path_factory.mktemp("hip_calls") / "hip_calls.so")
     subprocess.check_call(["gcc", "-O1", "-Wall", "-Werror", "-shared", "-fPIC",
                            os.path.join(ROOT, "tests", "hip_calls.c"), "-o", lib, "-ldl"])
